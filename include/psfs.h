@@ -127,6 +127,10 @@ int psfs_set_params(psfs_plan *plan, const psfs_params *params);
  * checked on the device only when the input check below is on). The caller
  * keeps them alive while work that reads them runs. */
 int psfs_set_background(psfs_plan *plan, int view, const float *mean_dev, const float *var_dev);
+/* psfs_set_cameras followed by psfs_set_background of every view, in one call
+ * (host arrays of n device pointers); nothing is set when one is refused. */
+int psfs_set_views(psfs_plan *plan, int n, const psfs_camera *cams, const float *const *mean_dev,
+                   const float *const *var_dev);
 
 /* Optional device check of the background model (Eq. 1 is defined only for
  * positive finite variances). flags_dev: a caller-owned, 4-byte aligned device
@@ -402,6 +406,16 @@ size_t psfs_diff_workspace_bytes(const psfs_plan *plan);
 int psfs_diff_forward(psfs_plan *plan, const uint8_t *const *images_dev, const uint8_t *labels_dev,
                       const int32_t *sub, float *logits_dev, float *loss_dev,
                       void *workspace_dev, size_t workspace_bytes, void *stream);
+
+/* psfs_set_views with camera matrices that lie on the device (P_dev: FP32
+ * [n][12]) and psfs_diff_forward in one call. The plan must have n cameras of
+ * the sizes in cams; cams[k].P receives the matrices. Waits until P_dev has
+ * been computed and copied (so it cannot be captured into a graph), and
+ * refuses non-finite matrices; the plan is unchanged when it fails. */
+int psfs_diff_forward_at(psfs_plan *plan, int n, psfs_camera *cams, const float *P_dev, const float *const *mean_dev,
+                         const float *const *var_dev, const uint8_t *const *images_dev, const uint8_t *labels_dev,
+                         const int32_t *sub, float *logits_dev, float *loss_dev, void *workspace_dev,
+                         size_t workspace_bytes, void *stream);
 
 /* Gradient of grad_loss * loss with respect to every view's background mean
  * and variance (FP32 [H][W][3] each; host arrays of n device pointers) and

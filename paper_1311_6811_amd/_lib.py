@@ -50,6 +50,7 @@ class PsfsError(RuntimeError):
 
 
 _lib = None
+_binding = None
 
 vp = C.c_void_p
 i32p = C.POINTER(C.c_int32)
@@ -66,6 +67,7 @@ SIGNATURES = {
     "psfs_set_grid": (C.c_int, [vp, C.POINTER(psfs_grid)]),
     "psfs_set_params": (C.c_int, [vp, C.POINTER(psfs_params)]),
     "psfs_set_background": (C.c_int, [vp, C.c_int, vp, vp]),
+    "psfs_set_views": (C.c_int, [vp, C.c_int, C.POINTER(psfs_camera), C.POINTER(vp), C.POINTER(vp)]),
     "psfs_set_input_check": (C.c_int, [vp, vp]),
     "psfs_input_status": (C.c_int, [vp]),
     "psfs_lmap_floats": (C.c_int64, [vp]),
@@ -88,6 +90,8 @@ SIGNATURES = {
     "psfs_threshold": (C.c_int, [vp, C.c_int64, C.c_float, vp, vp]),
     "psfs_diff_workspace_bytes": (C.c_size_t, [vp]),
     "psfs_diff_forward": (C.c_int, [vp, C.POINTER(vp), vp, i32p, vp, vp, vp, C.c_size_t, vp]),
+    "psfs_diff_forward_at": (C.c_int, [vp, C.c_int, C.POINTER(psfs_camera), vp, C.POINTER(vp), C.POINTER(vp),
+                                       C.POINTER(vp), vp, i32p, vp, vp, vp, C.c_size_t, vp]),
     "psfs_diff_backward": (C.c_int, [vp, C.POINTER(vp), vp, i32p, vp, vp, C.POINTER(vp), C.POINTER(vp), vp, vp,
                                      C.c_size_t, vp]),
     "psfs_batch_create": (C.c_int, [C.POINTER(vp), C.POINTER(psfs_params), C.c_int, C.POINTER(psfs_frame)]),
@@ -122,6 +126,15 @@ def lib():
     return _lib
 
 
+def binding():
+    """The native tensor checks (csrc/binding.cpp); raises if never built."""
+    global _binding
+    if _binding is None:
+        from . import _binding as B          # built beside this file
+        _binding = B
+    return _binding
+
+
 def check(status: int) -> int:
     if status < 0:
         raise PsfsError(status, lib().psfs_last_error().decode())
@@ -129,7 +142,4 @@ def check(status: int) -> int:
 
 
 def ptr_array(ptrs):
-    arr = (vp * max(len(ptrs), 1))()
-    for i, p in enumerate(ptrs):
-        arr[i] = p
-    return arr
+    return (vp * max(len(ptrs), 1))(*ptrs)

@@ -20,10 +20,20 @@ LOG_U_DEFAULT = -3.0 * math.log(256.0)
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """Raw handle of the current stream (torch.cuda.current_stream() builds a
+    Stream object around it first: 2 us a call)."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
-def _dev(t: torch.Tensor, dtype: torch.dtype, name: str, shape=None) -> int:
+def _dev(t: torch.Tensor, dtype: torch.dtype, name: str, shape=None, index=None) -> int:
+    """Device pointer of a tensor of this dtype (and shape, if given); `index`
+    numbers the name of a tensor of a list. Valid tensors take the first test
+    alone: a call checks dozens of them."""
+    if (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == dtype and t.is_contiguous()
+            and (shape is None or t.shape == shape)):
+        return t.data_ptr()
+    if index is not None:
+        name = f"{name}[{index}]"
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a GPU tensor")
     if t.dtype != dtype:
@@ -35,12 +45,20 @@ def _dev(t: torch.Tensor, dtype: torch.dtype, name: str, shape=None) -> int:
     return t.data_ptr()
 
 
+def _devs(ts, dtype: torch.dtype, name: str, shapes, null: bool = False):
+    """Pointer array of a list of tensors, one of each shape (with `null`, a
+    None entry of `ts` gives a NULL pointer)."""
+    ok = L.binding().pointers(ts if type(ts) is list else list(ts), dtype, shapes, null)
+    if ok is not None:
+        return (L.vp * max(len(ts), 1)).from_buffer_copy(ok or bytes(8))
+    return L.ptr_array([None if null and t is None else _dev(t, dtype, name, s, k)
+                        for k, (t, s) in enumerate(zip(ts, shapes))])
+
+
 def make_camera(width: int, height: int, P) -> L.psfs_camera:
     c = L.psfs_camera()
     c.width, c.height = int(width), int(height)
-    flat = np.asarray(P, np.float32).reshape(12)
-    for e in range(12):
-        c.P[e] = float(flat[e])
+    c.P = tuple(np.asarray(P, np.float32).reshape(12).tolist())
     return c
 
 
@@ -76,7 +94,7 @@ class Plan:
         # held by the object: module globals may be gone when it is collected at exit
         self._destroy = L.lib().psfs_plan_destroy
         self._keep = {}
-        self.cams = []
+        self.cams, self._hw, self._hw3 = [], [], []
         self.grid = None
         self.set_params(prior, log_u, threshold, sampling)
         if cams is not None:
@@ -98,8 +116,14 @@ class Plan:
     def set_cameras(self, cams: Sequence) -> None:
         arr = (L.psfs_camera * max(len(cams), 1))(*[make_camera(c.width, c.height, c.P) for c in cams])
         L.check(L.lib().psfs_set_cameras(self._h, len(cams), arr))
-        self.cams = list(cams)
+        self._took_cameras(cams)
         self._keep = {k: v for k, v in self._keep.items() if not k.startswith("bg")}
+
+    def _took_cameras(self, cams: Sequence) -> None:
+        self.cams = list(cams)
+        hw = [(int(c.height), int(c.width)) for c in cams]
+        if hw != self._hw:
+            self._hw, self._hw3 = hw, [(h, w, 3) for h, w in hw]
 
     def set_grid(self, grid) -> None:
         g = make_grid(grid.nx, grid.ny, grid.nz, grid.origin, grid.voxel)
@@ -140,6 +164,27 @@ class Plan:
         for k, (m, v) in enumerate(zip(means, vars_)):
             self.set_background(k, m, v)
 
+    def _set_views(self, views: Sequence, cams, means: Sequence[torch.Tensor], vars_: Sequence[torch.Tensor]) -> None:
+        """set_cameras and set_backgrounds in one call; `cams` is the array of
+        psfs_camera that holds the matrices of `views`."""
+        hw = [(int(c.height), int(c.width)) for c in views]
+        mp, vp_ = self._backgrounds(self._hw3 if hw == self._hw else [(h, w, 3) for h, w in hw], means, vars_)
+        L.check(L.lib().psfs_set_views(self._h, len(views), cams, mp, vp_))
+        self._took_views(views, means, vars_)
+
+    @staticmethod
+    def _backgrounds(hw3, means, vars_):
+        have = min(len(means), len(vars_))
+        if have < len(hw3):
+            raise L.PsfsError(-3, f"background of view {have} not set")
+        return _devs(means, torch.float32, "mean", hw3), _devs(vars_, torch.float32, "var", hw3)
+
+    def _took_views(self, views, means, vars_) -> None:
+        self._took_cameras(views)
+        if len(self._keep) > 1:
+            self._keep = {k: v for k, v in self._keep.items() if not k.startswith("bg")}
+        self._keep["bg"] = (means, vars_)
+
     # --------------------------------------------------------- buffers
     def set_input_check(self, flags: Optional[torch.Tensor]) -> None:
         """Device check of the background model (variances positive and
@@ -176,9 +221,7 @@ class Plan:
     def _images(self, images: Sequence[torch.Tensor]):
         if len(images) != self.n:
             raise ValueError(f"expected {self.n} images, got {len(images)}")
-        ptrs = [_dev(im, torch.uint8, f"images[{k}]", (c.height, c.width, 3))
-                for k, (im, c) in enumerate(zip(images, self.cams))]
-        return L.ptr_array(ptrs)
+        return _devs(images, torch.uint8, "images", self._hw3)
 
     def _map(self, t: torch.Tensor, frames: int, name: str) -> int:
         """Device pointer of a map buffer that must hold `frames` interleaved
@@ -293,18 +336,19 @@ class Plan:
         if images is not None:
             if len(images) != 4:
                 raise ValueError(f"expected the images of 4 frames, got {len(images)}")
-            flat = [p for fr in images for p in self._images(fr)[:self.n]]
-            ims = L.ptr_array(flat)
+            for fr in images:
+                if len(fr) != self.n:
+                    raise ValueError(f"expected {self.n} images, got {len(fr)}")
+            ims = _devs([im for fr in images for im in fr], torch.uint8, "images", self._hw3 * 4)
             nxt = self._map(lmap4_next, 4, "lmap4_next")
         pp = op = cur = None
         if posts is not None:
             if len(posts) != 4 or (occs is not None and len(occs) != 4):
                 raise ValueError("expected 4 posteriors (and 4 occupancies or None)")
             shape = (self.grid.nz, self.grid.ny, self.grid.nx)
-            pp = L.ptr_array([_dev(t, torch.float32, f"posts[{f}]", shape) for f, t in enumerate(posts)])
+            pp = _devs(posts, torch.float32, "posts", [shape] * 4)
             if occs is not None:
-                op = L.ptr_array([_dev(t, torch.uint8, f"occs[{f}]", shape) if t is not None else None
-                                  for f, t in enumerate(occs)])
+                op = _devs(occs, torch.uint8, "occs", [shape] * 4, null=True)
             cur = self._map(lmap4_cur, 4, "lmap4_cur")
         L.check(L.lib().psfs_pipeline_step_quad(self._h, ims, nxt, cur, pp, op, _stream()))
 
@@ -351,10 +395,8 @@ class Plan:
         npart = int(cylinders.shape[0])
         if len(silhouettes) != self.n or len(edges) != self.n:
             raise ValueError(f"expected {self.n} silhouette and edge maps")
-        sil = L.ptr_array([_dev(m, torch.float32, f"silhouettes[{k}]", (c.height, c.width))
-                           for k, (m, c) in enumerate(zip(silhouettes, self.cams))])
-        edg = L.ptr_array([_dev(m, torch.float32, f"edges[{k}]", (c.height, c.width))
-                           for k, (m, c) in enumerate(zip(edges, self.cams))])
+        sil = _devs(silhouettes, torch.float32, "silhouettes", self._hw)
+        edg = _devs(edges, torch.float32, "edges", self._hw)
         o = out or {}
         log_w = o.get("log_w")
         log_w = log_w if log_w is not None else torch.empty(npart, dtype=torch.float64, device="cuda")
@@ -381,8 +423,7 @@ class Plan:
         if masks is not None:
             if len(masks) != self.n:
                 raise ValueError(f"expected {self.n} masks, got {len(masks)}")
-            mp = L.ptr_array([_dev(m, torch.uint8, f"masks[{k}]", (c.height, c.width)) if m is not None else None
-                              for k, (m, c) in enumerate(zip(masks, self.cams))])
+            mp = _devs(masks, torch.uint8, "masks", self._hw, null=True)
         out = out if out is not None else torch.empty(L.FG_BINS, dtype=torch.float32, device="cuda")
         ws = workspace if workspace is not None else torch.empty(4 * L.FG_BINS, dtype=torch.uint8, device="cuda")
         L.check(L.lib().psfs_foreground_model(self._h, ims, mp, self._map(lmap, 1, "lmap") if lmap is not None else None,
@@ -447,6 +488,23 @@ class Plan:
                                           ws.numel(), _stream()))
         return logits, loss, ws
 
+    def _diff_forward_at(self, P: torch.Tensor, means, vars_, images, labels: torch.Tensor, sub):
+        """diff_forward at the camera matrices P (contiguous FP32 [n][3][4] on
+        the current GPU) and at these backgrounds, which the plan takes. The
+        plan has n cameras of the views' sizes. Returns (cams, logits, loss,
+        workspace), with the matrices in the psfs_camera array `cams`."""
+        g, n = self.grid, self.n
+        shape = (g.nz, g.ny, g.nx)
+        cams = (L.psfs_camera * max(n, 1))(*[(w, h) for h, w in self._hw])
+        mp, vp_ = self._backgrounds(self._hw3, means, vars_)
+        ims, lab = self._images(images), _dev(labels, torch.uint8, "labels", shape)
+        logits = torch.empty(shape, dtype=torch.float32, device="cuda")
+        loss = torch.empty((), dtype=torch.float32, device="cuda")
+        ws = self.new_diff_workspace()
+        L.check(L.lib().psfs_diff_forward_at(self._h, n, cams, P.data_ptr(), mp, vp_, ims, lab, self._sub(sub),
+                                             logits.data_ptr(), loss.data_ptr(), ws.data_ptr(), ws.numel(), _stream()))
+        return cams, logits, loss, ws
+
     def diff_backward(self, images, labels, logits, grad_loss: torch.Tensor, workspace, sub=None,
                       gmeans=None, gvars=None, gP=None):
         """Gradients of grad_loss * loss w.r.t. background means, variances
@@ -454,12 +512,14 @@ class Plan:
         g = self.grid
         shape = (g.nz, g.ny, g.nx)
         ims = self._images(images)
-        gl = grad_loss.detach().to(device="cuda", dtype=torch.float32).contiguous().reshape(())
-        gmeans = gmeans if gmeans is not None else [torch.empty((c.height, c.width, 3), dtype=torch.float32, device="cuda") for c in self.cams]
-        gvars = gvars if gvars is not None else [torch.empty((c.height, c.width, 3), dtype=torch.float32, device="cuda") for c in self.cams]
+        gl = grad_loss.detach()
+        if not (gl.is_cuda and gl.dtype == torch.float32 and gl.dim() == 0 and gl.get_device() == torch.cuda.current_device()):
+            gl = gl.to(device="cuda", dtype=torch.float32).contiguous().reshape(())
+        gmeans = gmeans if gmeans is not None else L.binding().empties(self._hw3)
+        gvars = gvars if gvars is not None else L.binding().empties(self._hw3)
         gP = gP if gP is not None else torch.empty((max(self.n, 1), 3, 4), dtype=torch.float32, device="cuda")
-        gm_ptr = L.ptr_array([_dev(t, torch.float32, f"gmean[{k}]", (c.height, c.width, 3)) for k, (t, c) in enumerate(zip(gmeans, self.cams))])
-        gv_ptr = L.ptr_array([_dev(t, torch.float32, f"gvar[{k}]", (c.height, c.width, 3)) for k, (t, c) in enumerate(zip(gvars, self.cams))])
+        gm_ptr = _devs(gmeans, torch.float32, "gmean", self._hw3)
+        gv_ptr = _devs(gvars, torch.float32, "gvar", self._hw3)
         L.check(L.lib().psfs_diff_backward(self._h, ims, _dev(labels, torch.uint8, "labels", shape), self._sub(sub),
                                            _dev(logits, torch.float32, "logits", shape), gl.data_ptr(), gm_ptr, gv_ptr,
                                            _dev(gP, torch.float32, "gP"), _dev(workspace, torch.uint8, "workspace"),

@@ -1,4 +1,5 @@
-"""Builds libpsfs.so (the HIP kernels and the C ABI) for gfx950, in-tree.
+"""Builds libpsfs.so (the HIP kernels and the C ABI) for gfx950 and
+_binding.so (the tensor checks of the Python binding), in-tree.
 
 Usage: ``python -m paper_1311_6811_amd.build`` (or ``build()`` from Python).
 Every HIP source is compiled with hipcc for gfx950 only; packed FP32 vector
@@ -12,6 +13,9 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
+
+import torch
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -19,6 +23,8 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libpsfs.so")
+BINDING = os.path.join(PKG, "_binding.so")
+TORCH = os.path.dirname(os.path.abspath(torch.__file__))
 
 ARCH = "gfx950"
 HIPCC = os.environ.get("HIPCC", shutil.which("hipcc") or "/opt/rocm/bin/hipcc")
@@ -39,11 +45,28 @@ def _compile(src: str, verbose: bool) -> str:
     return obj
 
 
+def _build_binding(verbose: bool) -> None:
+    tmp = BINDING + ".tmp"
+    cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           "-isystem", os.path.join(TORCH, "include"), "-isystem", sysconfig.get_path("include"),
+           os.path.join(CSRC, "binding.cpp"), "-o", tmp, "-L", os.path.join(TORCH, "lib"),
+           "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on binding.cpp:\n{r.stdout}\n{r.stderr}")
+    os.replace(tmp, BINDING)
+
+
 def build(verbose: bool = False, jobs: int = 8) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
-    with cf.ThreadPoolExecutor(max_workers=min(jobs, len(srcs))) as ex:
+    with cf.ThreadPoolExecutor(max_workers=min(jobs, len(srcs) + 1)) as ex:
+        binding = ex.submit(_build_binding, verbose)
         objs = list(ex.map(lambda s: _compile(s, verbose), srcs))
+        binding.result()
     tmp = LIB + ".tmp"
     cmd = [HIPCC, "-shared", "-fPIC", f"--offload-arch={ARCH}", "-o", tmp, *objs]
     if verbose:

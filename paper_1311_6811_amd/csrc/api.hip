@@ -13,6 +13,15 @@
 #include "host_util.h"
 #include "particles.h"
 
+// Where psfs_diff_forward_at receives the camera matrices: pinned host memory
+// and the event that marks the copy's end, made at the plan's first such call
+// on a device and kept until the plan is destroyed.
+struct CameraMail {
+    float *P = nullptr;                             // [PSFS_MAX_VIEWS][12]
+    hipEvent_t arrived = nullptr;
+    int device = -1;
+};
+
 struct psfs_plan {
     int n = -1;                                     // -1: cameras not set
     psfs_camera cams[PSFS_MAX_VIEWS];
@@ -24,6 +33,7 @@ struct psfs_plan {
     const float *fg = nullptr;                      // learned foreground model (log density per bin)
     uint32_t *check = nullptr;                      // input-check flags (caller's device word), or off
     int tile = -1;
+    CameraMail mail;
 };
 
 namespace psfs {
@@ -165,6 +175,49 @@ int64_t fill_slm(const psfs_plan *p, const uint8_t *const *images, float *lmap, 
         if (np > max_np) max_np = np;
     }
     return max_np;
+}
+
+int check_camera(int k, const psfs_camera &c)
+{
+    if (c.width < 1 || c.height < 1 || c.width > 65535 || c.height > 65535 ||
+        static_cast<int64_t>(c.width) * c.height >= (int64_t(1) << 30))
+        return fail(PSFS_E_RANGE, "view %d: image size %dx%d out of range", k, c.width, c.height);
+    if (!finite_all(c.P, 12)) return fail(PSFS_E_RANGE, "view %d: camera matrix not finite", k);
+    return PSFS_OK;
+}
+
+int check_background(const float *mean_dev, const float *var_dev)
+{
+    if (!mean_dev || !var_dev) return fail(PSFS_E_ARG, "background pointer is NULL");
+    if (!aligned(mean_dev, 16) || !aligned(var_dev, 16)) return fail(PSFS_E_ARG, "background pointers must be 16-byte aligned");
+    return PSFS_OK;
+}
+
+void free_mail(CameraMail &m)
+{
+    if (m.arrived) {
+        hipEventSynchronize(m.arrived);
+        hipEventDestroy(m.arrived);
+    }
+    if (m.P) hipHostFree(m.P);
+    m = CameraMail{};
+}
+
+int open_mail(CameraMail &m)
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
+    if (m.P && m.device == dev) return PSFS_OK;
+    free_mail(m);
+    e = hipHostMalloc(reinterpret_cast<void **>(&m.P), sizeof(float) * 12 * PSFS_MAX_VIEWS, hipHostMallocDefault);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&m.arrived, hipEventDisableTiming);
+    if (e != hipSuccess) {
+        free_mail(m);
+        return hip_fail(e, "host buffer of the camera matrices");
+    }
+    m.device = dev;
+    return PSFS_OK;
 }
 
 int enqueue_likelihood(const psfs_plan *p, const uint8_t *const *images, float *lmap, hipStream_t s,
@@ -373,20 +426,19 @@ int psfs_plan_create(psfs_plan **out)
     PSFS_GUARD_END
 }
 
-void psfs_plan_destroy(psfs_plan *plan) { delete plan; }
+void psfs_plan_destroy(psfs_plan *plan)
+{
+    if (plan) free_mail(plan->mail);
+    delete plan;
+}
 
 int psfs_set_cameras(psfs_plan *plan, int n, const psfs_camera *cams)
 {
     if (!plan) return fail(PSFS_E_ARG, "plan is NULL");
     if (n < 0 || n > PSFS_MAX_VIEWS) return fail(PSFS_E_RANGE, "view count %d outside 0..%d", n, PSFS_MAX_VIEWS);
     if (n > 0 && !cams) return fail(PSFS_E_ARG, "cams is NULL");
-    for (int k = 0; k < n; ++k) {
-        const psfs_camera &c = cams[k];
-        if (c.width < 1 || c.height < 1 || c.width > 65535 || c.height > 65535 ||
-            static_cast<int64_t>(c.width) * c.height >= (int64_t(1) << 30))
-            return fail(PSFS_E_RANGE, "view %d: image size %dx%d out of range", k, c.width, c.height);
-        if (!finite_all(c.P, 12)) return fail(PSFS_E_RANGE, "view %d: camera matrix not finite", k);
-    }
+    for (int k = 0; k < n; ++k)
+        if (int rc = check_camera(k, cams[k])) return rc;
     plan->n = n;
     for (int k = 0; k < n; ++k) plan->cams[k] = cams[k];
     for (int k = 0; k < PSFS_MAX_VIEWS; ++k) plan->mean[k] = plan->var[k] = nullptr;
@@ -422,10 +474,24 @@ int psfs_set_background(psfs_plan *plan, int view, const float *mean_dev, const 
     int rc = need_cameras(plan);
     if (rc) return rc;
     if (view < 0 || view >= plan->n) return fail(PSFS_E_RANGE, "view %d outside 0..%d", view, plan->n - 1);
-    if (!mean_dev || !var_dev) return fail(PSFS_E_ARG, "background pointer is NULL");
-    if (!aligned(mean_dev, 16) || !aligned(var_dev, 16)) return fail(PSFS_E_ARG, "background pointers must be 16-byte aligned");
+    if ((rc = check_background(mean_dev, var_dev))) return rc;
     plan->mean[view] = mean_dev;
     plan->var[view] = var_dev;
+    return PSFS_OK;
+}
+
+int psfs_set_views(psfs_plan *plan, int n, const psfs_camera *cams, const float *const *mean_dev,
+                   const float *const *var_dev)
+{
+    if (n > 0 && (!mean_dev || !var_dev)) return fail(PSFS_E_ARG, "background array is NULL");
+    if (n <= PSFS_MAX_VIEWS)
+        for (int k = 0; k < n; ++k)
+            if (int rc = check_background(mean_dev[k], var_dev[k])) return rc;
+    if (int rc = psfs_set_cameras(plan, n, cams)) return rc;
+    for (int k = 0; k < n; ++k) {
+        plan->mean[k] = mean_dev[k];
+        plan->var[k] = var_dev[k];
+    }
     return PSFS_OK;
 }
 
@@ -944,6 +1010,62 @@ int psfs_diff_forward(psfs_plan *plan, const uint8_t *const *images_dev, const u
     // the differentiable variant keeps the uniform foreground density (the
     // pixel chain differentiates that form)
     if ((rc = enqueue_likelihood(plan, images_dev, const_cast<float *>(a.lmap), s, false))) return rc;
+    hipError_t e = launch_diff_forward(a, loss_dev, s);
+    if (e != hipSuccess) return hip_fail(e, "differentiable forward launch");
+    return PSFS_OK;
+    PSFS_GUARD_END
+}
+
+int psfs_diff_forward_at(psfs_plan *plan, int n, psfs_camera *cams, const float *P_dev, const float *const *mean_dev,
+                         const float *const *var_dev, const uint8_t *const *images_dev, const uint8_t *labels_dev,
+                         const int32_t *sub, float *logits_dev, float *loss_dev, void *workspace_dev,
+                         size_t workspace_bytes, void *stream)
+{
+    PSFS_GUARD_BEGIN
+    int rc = need_cameras(plan);
+    if (rc) return rc;
+    if (n != plan->n) return fail(PSFS_E_ARG, "%d cameras given, the plan has %d", n, plan->n);
+    if (n > 0 && (!cams || !P_dev || !aligned(P_dev, 4))) return fail(PSFS_E_ARG, "cams or P is NULL");
+    if (n > 0 && (!mean_dev || !var_dev)) return fail(PSFS_E_ARG, "background array is NULL");
+    psfs_plan next = *plan;                         // the plan takes the views once all of them are valid
+    for (int k = 0; k < n; ++k) {
+        if (cams[k].width != plan->cams[k].width || cams[k].height != plan->cams[k].height)
+            return fail(PSFS_E_ARG, "view %d is %dx%d, the plan's is %dx%d", k, cams[k].width, cams[k].height,
+                        plan->cams[k].width, plan->cams[k].height);
+        if ((rc = check_background(mean_dev[k], var_dev[k]))) return rc;
+        next.mean[k] = mean_dev[k];
+        next.var[k] = var_dev[k];
+    }
+    DiffArgs a;
+    DiffLayout L;
+    if ((rc = prepare_diff(&next, images_dev, labels_dev, sub, workspace_dev, workspace_bytes, a, L))) return rc;
+    if (!loss_dev) return fail(PSFS_E_ARG, "loss is NULL");
+    if (nvox(plan->grid) > 0 && (!logits_dev || !aligned(logits_dev, 16))) return fail(PSFS_E_ARG, "logits must be a 16-byte aligned device pointer");
+    if ((rc = check_device())) return rc;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    // The matrices travel to the host (the kernels take them as arguments, and
+    // a non-finite one is refused) while the likelihood maps, which do not
+    // depend on them, are computed.
+    if (n > 0) {
+        if ((rc = open_mail(plan->mail))) return rc;
+        next.mail = plan->mail;
+        hipError_t e = hipMemcpyAsync(plan->mail.P, P_dev, sizeof(float) * 12 * n, hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipEventRecord(plan->mail.arrived, s);
+        if (e != hipSuccess) return hip_fail(e, "reading the camera matrices");
+    }
+    if ((rc = enqueue_likelihood(&next, images_dev, const_cast<float *>(a.lmap), s, false))) return rc;
+    if (n > 0) {
+        hipError_t e = hipEventSynchronize(plan->mail.arrived);
+        if (e != hipSuccess) return hip_fail(e, "waiting for the camera matrices");
+        for (int k = 0; k < n; ++k) {
+            std::memcpy(next.cams[k].P, plan->mail.P + 12 * k, sizeof(next.cams[k].P));
+            if ((rc = check_camera(k, next.cams[k]))) return rc;
+        }
+    }
+    if ((rc = prepare_diff(&next, images_dev, labels_dev, sub, workspace_dev, workspace_bytes, a, L))) return rc;
+    a.logits = logits_dev;
+    *plan = next;
+    for (int k = 0; k < n; ++k) cams[k] = next.cams[k];
     hipError_t e = launch_diff_forward(a, loss_dev, s);
     if (e != hipSuccess) return hip_fail(e, "differentiable forward launch");
     return PSFS_OK;
