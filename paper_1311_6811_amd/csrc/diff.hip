@@ -25,16 +25,17 @@
 // reproducible bit for bit; the rounding error per term is <= 2^-20 G.
 #include <algorithm>
 
-#include "kernels_common.h"
+#include "pixel_box.h"
 
 namespace psfs {
 namespace {
 
 using namespace dev;
 
-constexpr int kBlock = 256;
+constexpr int kBlock = kBoxThreads;
 constexpr int kWaves = kBlock / 64;
-constexpr int kBoxCap = 4096;           // floats of one view's pixel box staged in LDS
+constexpr int kBoxCap = 4096;           // floats of one view's pixel box staged in LDS (backward)
+constexpr int kFwdArena = 7500;         // floats of the forward's staged boxes
 constexpr int kStageIters = kBoxCap / kBlock;
 
 struct Coords {
@@ -82,73 +83,6 @@ __device__ __forceinline__ int adjoint_exponent(float grad_loss, float inv_count
     return 19 - e;
 }
 
-// Projection rows of view v at an FP64 voxel column (X, Y), from the camera
-// matrix widened on the host (kernel arguments: scalar operands of the FMAs).
-__device__ __forceinline__ Proj64 proj64_view(const DiffArgs &a, int v, double X, double Y)
-{
-    const double *P = a.Pd[v];
-    Proj64 p;
-    p.ax = fma(P[0], X, fma(P[1], Y, P[3]));
-    p.bx = fma(P[4], X, fma(P[5], Y, P[7]));
-    p.cx = fma(P[8], X, fma(P[9], Y, P[11]));
-    p.pz0 = P[2];
-    p.pz1 = P[6];
-    p.pz2 = P[10];
-    return p;
-}
-
-// 1/c in FP64: the hardware reciprocal (relative error ~5e-8 on this GPU)
-// refined by one Newton step (~2e-15; a projected coordinate of ~1000 px is
-// then placed to ~1e-12 px).
-__device__ __forceinline__ double rcp64(double c)
-{
-    const double r = __builtin_amdgcn_rcp(c);
-    return fma(r, fma(-c, r, 1.0), r);
-}
-
-// One view's projection of a voxel centre, in FP64 (see the forward kernel).
-struct Tap4 {
-    float fx, fy;
-    double x0, y0;
-    float u, v, rc;
-};
-
-// Projection of a voxel centre known to lie in front of the camera (depth
-// c > 0): a voxel of a workgroup whose pixel box is valid, since the depth is
-// affine in the position and positive at every corner of the voxel box.
-__device__ __forceinline__ void project64_front(const Proj64 &p, double Zd, Tap4 &t)
-{
-    const double c = fma(p.pz2, Zd, p.cx);
-    const double r = rcp64(c);
-    const double u = fma(p.pz0, Zd, p.ax) * r;
-    const double w = fma(p.pz1, Zd, p.bx) * r;
-    t.x0 = floor(u);
-    t.y0 = floor(w);
-    t.fx = static_cast<float>(u - t.x0);
-    t.fy = static_cast<float>(w - t.y0);
-    t.u = static_cast<float>(u);
-    t.v = static_cast<float>(w);
-    t.rc = static_cast<float>(r);
-}
-
-// The same for any voxel centre: false when it is not in front.
-__device__ __forceinline__ bool project64(const Proj64 &p, double Zd, Tap4 &t)
-{
-    if (!(fma(p.pz2, Zd, p.cx) > 0.0)) return false;
-    project64_front(p, Zd, t);
-    return true;
-}
-
-// Pixel box [x0, x0+w) x [y0, y0+h) holding both bilinear taps in x and y of
-// every voxel centre of the workgroup's voxel box, for every view: the
-// projection maps the box into the hull of its 8 projected corners (all in
-// front of the camera), widened by 1e-6 px for the lanes' own FP64 rounding.
-// Lanes 8v..8v+7 project the corners of view v; the box is stored in LDS.
-// ok = 0 when a corner is not in front or the box exceeds kBoxCap floats.
-struct PixBox {
-    int x0, y0, w, h, ok;
-};
-
 // Workgroup of either pass = 16 x 16 voxel columns x kFZ slices, a lane one
 // column and its kFZ voxels. Its views' pixel boxes hold ~0.7 pixels per
 // voxel at 128^3 x 8 views of 640x480 (~0.9 for 8 x 8 x 16 or 8 x 8 x 32
@@ -183,65 +117,6 @@ __device__ __forceinline__ Coords block_coords(int nx, int ny, int nz)
     }
     c.kb = static_cast<int>(zc) * kFZ;
     return c;
-}
-
-template <int EX, int EY, int EZ>
-__device__ __forceinline__ void compute_boxes(const DiffArgs &a, const Coords &q, PixBox *boxes)
-{
-    for (int t0 = 0; t0 < 8 * a.n; t0 += kBlock) {
-        const int t = t0 + static_cast<int>(threadIdx.x);
-        const int v = t < 8 * a.n ? t >> 3 : 0;
-        const int corner = t & 7;
-        const ViewGeom &g = a.view[v];
-        const double X = static_cast<double>(a.ox) + static_cast<double>(a.h) * ((corner & 1 ? q.bi + EX - 1 : q.bi) + 0.5);
-        const double Y = static_cast<double>(a.oy) + static_cast<double>(a.h) * ((corner & 2 ? q.bj + EY - 1 : q.bj) + 0.5);
-        const double Z = static_cast<double>(a.oz) + static_cast<double>(a.h) * ((corner & 4 ? q.kb + EZ - 1 : q.kb) + 0.5);
-        const Proj64 p = proj64_view(a, v, X, Y);
-        const double c = fma(p.pz2, Z, p.cx);
-        double ok = c > 0.0 ? 1.0 : 0.0;
-        const double u = fma(p.pz0, Z, p.ax) / c, w = fma(p.pz1, Z, p.bx) / c;
-        double umin = u, umax = u, wmin = w, wmax = w;
-#pragma unroll
-        for (int m = 1; m <= 4; m <<= 1) {
-            umin = fmin(umin, __shfl_xor(umin, m, 64));
-            umax = fmax(umax, __shfl_xor(umax, m, 64));
-            wmin = fmin(wmin, __shfl_xor(wmin, m, 64));
-            wmax = fmax(wmax, __shfl_xor(wmax, m, 64));
-            ok = fmin(ok, __shfl_xor(ok, m, 64));
-        }
-        if (t < 8 * a.n && corner == 0) {
-            PixBox b{0, 0, 0, 0, 0};
-            // NaN or huge coordinates fail these range tests
-            if (ok > 0.5 && umin > -1e6 && umax < 1e6 && wmin > -1e6 && wmax < 1e6) {
-                b.x0 = static_cast<int>(floor(umin - 1e-6));
-                b.y0 = static_cast<int>(floor(wmin - 1e-6));
-                b.w = static_cast<int>(floor(umax + 1e-6)) + 2 - b.x0;
-                b.h = static_cast<int>(floor(wmax + 1e-6)) + 2 - b.y0;
-                // sides are checked before the product so it cannot overflow
-                b.ok = (b.w > 0 && b.h > 0 && b.w <= kBoxCap && b.h <= kBoxCap && b.w * b.h <= kBoxCap) ? 1 : 0;
-            }
-            boxes[v] = b;
-        }
-    }
-}
-
-__device__ __forceinline__ PixBox read_box(const PixBox *boxes, int v)
-{
-    PixBox b;
-    b.x0 = __builtin_amdgcn_readfirstlane(boxes[v].x0);
-    b.y0 = __builtin_amdgcn_readfirstlane(boxes[v].y0);
-    b.w = __builtin_amdgcn_readfirstlane(boxes[v].w);
-    b.h = __builtin_amdgcn_readfirstlane(boxes[v].h);
-    b.ok = __builtin_amdgcn_readfirstlane(boxes[v].ok);
-    return b;
-}
-
-// Element e of a box, row-major: r = e / w without an integer division
-// ((e + 1/2) / w is at least 1/(2w) away from an integer for e < 2^22).
-__device__ __forceinline__ void box_rc(int e, int w, float inv_w, int &r, int &c)
-{
-    r = static_cast<int>((static_cast<float>(e) + 0.5f) * inv_w);
-    c = e - r * w;
 }
 
 // Copies a view's map over the box into LDS; pixels outside the image read as
@@ -286,55 +161,16 @@ __device__ __forceinline__ void stage_box(float *lds, const PixBox &b, const flo
 
 __global__ __launch_bounds__(kBlock) void diff_fwd_kernel(DiffArgs a)
 {
-    __shared__ float lmap_box[kBoxCap];
+    __shared__ float arena[kFwdArena];
     __shared__ PixBox boxes[kMaxViews];
     const Coords q = block_coords<false>(a.nx, a.ny, a.nz);
-    compute_boxes<kFX, kFY, kFZ>(a, q, boxes);
-    const double Xd = static_cast<double>(a.ox) + static_cast<double>(a.h) * (q.i + 0.5);
-    const double Yd = static_cast<double>(a.oy) + static_cast<double>(a.h) * (q.j + 0.5);
+    compute_boxes<kFX, kFY, kFZ>(a, q.bi, q.bj, q.kb, kFwdArena, boxes);
+    const double Xd = centre64(a.ox, a.h, q.i), Yd = centre64(a.oy, a.h, q.j);
     float L[kFZ];
 #pragma unroll
     for (int kk = 0; kk < kFZ; ++kk) L[kk] = a.L0;
     __syncthreads();
-
-    for (int v = 0; v < a.n; ++v) {
-        const ViewGeom &g = a.view[v];
-        const float *map = a.lmap + g.map_off;
-        const Proj64 p = proj64_view(a, v, Xd, Yd);
-        const PixBox box = read_box(boxes, v);
-        if (box.ok) {
-            __syncthreads();                // the previous view's reads are done
-            stage_box(lmap_box, box, map, g.W, g.H);
-            __syncthreads();
-            // box element of tap (x0, y0): (y0 - box.y0) w + (x0 - box.x0),
-            // exact in FP64 (integers far below 2^53)
-            const double wd = static_cast<double>(box.w);
-            const double od = static_cast<double>(box.y0) * wd + static_cast<double>(box.x0);
-            const int emax = box.w * box.h - box.w - 2;
-            // every voxel centre of the workgroup is in front of the camera and
-            // has both taps in the box (taps outside the image read the 0s the
-            // staging wrote there); the clamp only keeps the reads in the box
-#pragma unroll
-            for (int kk = 0; kk < kFZ; ++kk) {
-                const double Zd = static_cast<double>(a.oz) + static_cast<double>(a.h) * (q.kb + kk + 0.5);
-                Tap4 t;
-                project64_front(p, Zd, t);
-                const int e = min(max(static_cast<int>(fma(t.y0, wd, t.x0 - od)), 0), emax);
-                const float *s = lmap_box + e;
-                const float top = fmaf(t.fx, s[1] - s[0], s[0]);
-                const float bot = fmaf(t.fx, s[box.w + 1] - s[box.w], s[box.w]);
-                L[kk] += fmaf(t.fy, bot - top, top);
-            }
-        } else {
-#pragma unroll
-            for (int kk = 0; kk < kFZ; ++kk) {
-                const double Zd = static_cast<double>(a.oz) + static_cast<double>(a.h) * (q.kb + kk + 0.5);
-                Tap4 t;
-                if (!project64(p, Zd, t)) continue;
-                L[kk] += bilinear_sample(map, g.W, g.H, t.x0, t.y0, t.fx, t.fy);
-            }
-        }
-    }
+    add_bilinear<kFZ, kFwdArena>(a, Xd, Yd, q.kb, arena, boxes, L);
 
     double part = 0.0;
     if (q.i < a.nx && q.j < a.ny) {
@@ -400,8 +236,7 @@ __global__ __launch_bounds__(kBlock) void diff_bwd_kernel(DiffArgs a)
     const Coords q = block_coords<true>(a.nx, a.ny, a.nz);
     const float X = a.ox + a.h * (static_cast<float>(q.i) + 0.5f);
     const float Y = a.oy + a.h * (static_cast<float>(q.j) + 0.5f);
-    const double Xd = static_cast<double>(a.ox) + static_cast<double>(a.h) * (q.i + 0.5);
-    const double Yd = static_cast<double>(a.oy) + static_cast<double>(a.h) * (q.j + 0.5);
+    const double Xd = centre64(a.ox, a.h, q.i), Yd = centre64(a.oy, a.h, q.j);
     const float gl = *a.grad_loss;
     const float qscale = ldexpf(1.0f, adjoint_exponent(gl, a.inv_count));
 
@@ -419,7 +254,7 @@ __global__ __launch_bounds__(kBlock) void diff_bwd_kernel(DiffArgs a)
     }
     // a workgroup with no voxel in the loss region contributes nothing
     const bool block_any = __syncthreads_or(any ? 1 : 0) != 0;
-    if (block_any) compute_boxes<kFX, kFY, kFZ>(a, q, boxes);
+    if (block_any) compute_boxes<kFX, kFY, kFZ>(a, q.bi, q.bj, q.kb, kBoxCap, boxes);
     // the adjoint box starts at zero once; each view's flush clears the
     // entries it reads, and a view scatters only inside its own box
     for (int e = threadIdx.x; e < kBoxCap; e += kBlock) adj_box[e] = 0;
@@ -450,7 +285,7 @@ __global__ __launch_bounds__(kBlock) void diff_bwd_kernel(DiffArgs a)
 #pragma unroll
             for (int kk = 0; kk < kFZ; ++kk) {
                 if (gv[kk] == 0.0f) continue;
-                const double Zd = static_cast<double>(a.oz) + static_cast<double>(a.h) * (q.kb + kk + 0.5);
+                const double Zd = centre64(a.oz, a.h, q.kb + kk);
                 Tap4 t;
                 project64_front(p, Zd, t);
                 const float fx = t.fx, fy = t.fy, gk = gv[kk];
@@ -477,7 +312,7 @@ __global__ __launch_bounds__(kBlock) void diff_bwd_kernel(DiffArgs a)
 #pragma unroll
             for (int kk = 0; kk < kFZ; ++kk) {
                 if (gv[kk] == 0.0f) continue;
-                const double Zd = static_cast<double>(a.oz) + static_cast<double>(a.h) * (q.kb + kk + 0.5);
+                const double Zd = centre64(a.oz, a.h, q.kb + kk);
                 Tap4 t;
                 if (!project64(p, Zd, t)) continue;
                 if (!(t.x0 >= -1.0 && t.x0 < g.W && t.y0 >= -1.0 && t.y0 < g.H)) continue;

@@ -8,7 +8,7 @@
 // gives P(S_k|V=1) = SLM_k and P(S_k|V=0) = 1/2, so each view that sees a voxel
 // adds log(2*SLM_k) to the logit of Eq. 3. With SLM = u/(u+N) (Eq. 1-2, equal
 // pixel priors), log(2*SLM) = log 2 - softplus(log N - log u).
-#include "kernels_common.h"
+#include "pixel_box.h"
 
 namespace psfs {
 
@@ -57,10 +57,10 @@ __host__ __device__ int64_t tile_count_of(const FuseArgs &a)
     return static_cast<int64_t>((a.nx + TX - 1) / TX) * ((a.ny + TY - 1) / TY) * ((a.nz + KZ - 1) / KZ);
 }
 
-template <int TX, int TY, int KZ, int SAMPLING>
+template <int TX, int TY, int KZ>
 __global__ __launch_bounds__(TX * TY) void fuse_kernel(FuseArgs a)
 {
-    fuse_tile<TX, TY, KZ, SAMPLING>(a, xcd_remap(blockIdx.x, tile_count_of<TX, TY, KZ>(a)));
+    fuse_tile<TX, TY, KZ, PSFS_NEAREST>(a, xcd_remap(blockIdx.x, tile_count_of<TX, TY, KZ>(a)));
 }
 
 // Likelihood maps of the next frame (Eq. 1-2, SlmArgs) and fusion of the
@@ -473,6 +473,48 @@ __global__ __launch_bounds__(kSBThreads) void pipe_block_kernel(SlmArgs s, FuseA
     }
 }
 
+// Bilinear fusion of a 16 x 16 x KZ voxel block per workgroup from pixel boxes
+// staged in LDS (add_bilinear): the differentiable forward's sampling with
+// this pass's outputs. Bound by the FP64 projection's instructions. The column
+// kernels gather four taps of every voxel-view from the map, four loads with a
+// bounds test each: 61 us at 128^3 x 8 views of 640x480, 515 us at 224^3 x 12
+// of 1280x720; here 32 and 206 us. The arena of 7500 floats (30 KB) leaves room
+// for five workgroups per CU, as many as the registers allow: 8192 floats (four
+// workgroups) 32 and 219 us, 6000 floats (fewer views per barrier) 34 and 204 us.
+constexpr int kBilArena = 7500;
+
+template <int KZ>
+__global__ __launch_bounds__(kBoxThreads) void fuse_bilinear_kernel(BilinearArgs a)
+{
+    __shared__ float arena[kBilArena];
+    __shared__ PixBox boxes[kMaxViews];
+    const uint32_t nbx = static_cast<uint32_t>((a.nx + 15) / 16), nby = static_cast<uint32_t>((a.ny + 15) / 16);
+    const uint32_t nbz = static_cast<uint32_t>((a.nz + KZ - 1) / KZ);
+    const int64_t nb = static_cast<int64_t>(nbx) * nby * nbz;
+    uint32_t bi, bj, bk;
+    octant_tile(static_cast<uint32_t>(xcd_remap(blockIdx.x, nb)), nbx, nby, nbz, bi, bj, bk);
+    const int i0 = static_cast<int>(bi) * 16, j0 = static_cast<int>(bj) * 16, k0 = static_cast<int>(bk) * KZ;
+    compute_boxes<16, 16, KZ>(a, i0, j0, k0, kBilArena, boxes);
+    const int i = i0 + static_cast<int>(threadIdx.x % 16), j = j0 + static_cast<int>(threadIdx.x / 16);
+    const double Xd = centre64(a.ox, a.h, i), Yd = centre64(a.oy, a.h, j);
+    float L[KZ];
+#pragma unroll
+    for (int kk = 0; kk < KZ; ++kk) L[kk] = a.L0;
+    __syncthreads();
+    add_bilinear<KZ, kBilArena>(a, Xd, Yd, k0, arena, boxes, L);
+    if (i >= a.nx || j >= a.ny) return;
+    const int64_t plane = static_cast<int64_t>(a.nx) * a.ny;
+    int64_t idx = (static_cast<int64_t>(k0) * a.ny + j) * a.nx + i;
+#pragma unroll
+    for (int kk = 0; kk < KZ; ++kk, idx += plane) {
+        if (k0 + kk < a.nz) {
+            const float p = sigmoid_fast(L[kk]);
+            a.post[idx] = p;
+            if (a.occ) a.occ[idx] = p > a.tau ? 1 : 0;
+        }
+    }
+}
+
 __global__ __launch_bounds__(256) void threshold_kernel(const float *post, int64_t n, float tau, uint8_t *occ)
 {
     const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
@@ -482,11 +524,16 @@ __global__ __launch_bounds__(256) void threshold_kernel(const float *post, int64
 
 // Tile kBlockTile is the kSBX x kSBY x kSBZ voxel block: the one-frame
 // nearest paths fuse it from pixel boxes staged in LDS (fuse_block_kernel),
-// bilinear sampling with 16 x 16 columns of 8 voxels.
+// the pipelined bilinear step with 16 x 16 columns of 8 voxels. Bilinear fusion
+// by itself has one kernel for every tile (launch_fuse_bilinear).
 constexpr TileCfg kTiles[] = {
     {8, 32, 4}, {8, 32, 8}, {8, 16, 4}, {8, 32, 2}, {32, 8, 4}, {16, 16, 4}, {kSBX, kSBY, kSBZ},
 };
 constexpr int kBlockTile = 6;
+// Bilinear blocks are 8 voxels deep when at least kBilBlocks of them (two per
+// CU) cover the grid, else 4 or 2 deep: on a 64^3 grid, whose 128 blocks of 8
+// would use half of the CUs, 2 deep takes 8.6 us.
+constexpr int64_t kBilBlocks = 512;
 
 hipError_t launch_fuse_block(const FuseArgs &a, hipStream_t s)
 {
@@ -540,22 +587,48 @@ hipError_t launch_pipe_s(const SlmArgs &sa, const FuseArgs &fa, int tile, int64_
     }
 }
 
-template <int S>
-hipError_t launch_fuse_s(const FuseArgs &a, int tile, hipStream_t s)
+hipError_t launch_fuse_bilinear(const FuseArgs &f, hipStream_t s)
 {
-    if (S == PSFS_NEAREST && tile == kBlockTile) return launch_fuse_block(a, s);
+    BilinearArgs a{};
+    for (int v = 0; v < f.n; ++v) {
+        a.view[v] = f.view[v];
+        for (int e = 0; e < 12; ++e) a.Pd[v][e] = static_cast<double>(f.view[v].P[e]);
+    }
+    a.lmap = f.lmap;
+    a.post = f.post;
+    a.occ = f.occ;
+    a.n = f.n;
+    a.nx = f.nx; a.ny = f.ny; a.nz = f.nz;
+    a.ox = f.ox; a.oy = f.oy; a.oz = f.oz; a.h = f.h;
+    a.L0 = f.L0;
+    a.tau = f.tau;
+    const int64_t columns = static_cast<int64_t>((a.nx + 15) / 16) * ((a.ny + 15) / 16);
+    auto blocks = [&](int kz) { return columns * ((a.nz + kz - 1) / kz); };
+    const int kz = blocks(8) >= kBilBlocks ? 8 : blocks(4) >= kBilBlocks ? 4 : 2;
+    const dim3 grid(static_cast<unsigned>(blocks(kz))), block(kBoxThreads);
+    if (grid.x == 0) return hipSuccess;
+    switch (kz) {
+    case 8: hipLaunchKernelGGL((fuse_bilinear_kernel<8>), grid, block, 0, s, a); break;
+    case 4: hipLaunchKernelGGL((fuse_bilinear_kernel<4>), grid, block, 0, s, a); break;
+    default: hipLaunchKernelGGL((fuse_bilinear_kernel<2>), grid, block, 0, s, a); break;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_fuse_nearest(const FuseArgs &a, int tile, hipStream_t s)
+{
+    if (tile == kBlockTile) return launch_fuse_block(a, s);
     const TileCfg &c = kTiles[tile];
     const int64_t nb = static_cast<int64_t>((a.nx + c.tx - 1) / c.tx) * ((a.ny + c.ty - 1) / c.ty) *
                        ((a.nz + c.kz - 1) / c.kz);
     const dim3 grid(static_cast<unsigned>(nb)), block(c.tx * c.ty);
     switch (tile) {
-    case 0: hipLaunchKernelGGL((fuse_kernel<8, 32, 4, S>), grid, block, 0, s, a); break;
-    case 1: hipLaunchKernelGGL((fuse_kernel<8, 32, 8, S>), grid, block, 0, s, a); break;
-    case 2: hipLaunchKernelGGL((fuse_kernel<8, 16, 4, S>), grid, block, 0, s, a); break;
-    case 3: hipLaunchKernelGGL((fuse_kernel<8, 32, 2, S>), grid, block, 0, s, a); break;
-    case 4: hipLaunchKernelGGL((fuse_kernel<32, 8, 4, S>), grid, block, 0, s, a); break;
-    case 5: hipLaunchKernelGGL((fuse_kernel<16, 16, 4, S>), grid, block, 0, s, a); break;
-    case 6: hipLaunchKernelGGL((fuse_kernel<16, 16, 8, S>), grid, block, 0, s, a); break;
+    case 0: hipLaunchKernelGGL((fuse_kernel<8, 32, 4>), grid, block, 0, s, a); break;
+    case 1: hipLaunchKernelGGL((fuse_kernel<8, 32, 8>), grid, block, 0, s, a); break;
+    case 2: hipLaunchKernelGGL((fuse_kernel<8, 16, 4>), grid, block, 0, s, a); break;
+    case 3: hipLaunchKernelGGL((fuse_kernel<8, 32, 2>), grid, block, 0, s, a); break;
+    case 4: hipLaunchKernelGGL((fuse_kernel<32, 8, 4>), grid, block, 0, s, a); break;
+    case 5: hipLaunchKernelGGL((fuse_kernel<16, 16, 4>), grid, block, 0, s, a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -577,8 +650,7 @@ hipError_t launch_slm(const SlmArgs &a, int64_t max_npix, hipStream_t s)
 
 hipError_t launch_fuse(const FuseArgs &a, int tile, int sampling, hipStream_t s)
 {
-    return sampling == PSFS_BILINEAR ? launch_fuse_s<PSFS_BILINEAR>(a, tile, s)
-                                     : launch_fuse_s<PSFS_NEAREST>(a, tile, s);
+    return sampling == PSFS_BILINEAR ? launch_fuse_bilinear(a, s) : launch_fuse_nearest(a, tile, s);
 }
 
 hipError_t launch_pipeline(const SlmArgs &sa, const FuseArgs &fa, int tile, int sampling, int64_t max_npix,

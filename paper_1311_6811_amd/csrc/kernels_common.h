@@ -519,6 +519,15 @@ __device__ __forceinline__ float map_load(__amdgpu_buffer_rsrc_t r, uint32_t off
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, static_cast<int>(off), 0, 0));
 }
 
+// 1/c in FP64: the hardware reciprocal (relative error ~5e-8 on this GPU)
+// refined by one Newton step (~2e-15; a projected coordinate of ~1000 px is
+// then placed to ~1e-12 px).
+__device__ __forceinline__ double rcp64(double c)
+{
+    const double r = __builtin_amdgcn_rcp(c);
+    return fma(r, fma(-c, r, 1.0), r);
+}
+
 // Projection rows of one view evaluated in FP64 at an FP64 voxel centre:
 // the z-independent part once per voxel column, then one FMA per row.
 struct Proj64 {
@@ -535,6 +544,46 @@ __device__ __forceinline__ Proj64 proj64_column(const ViewGeom &g, double X, dou
     p.pz1 = g.P[6];
     p.pz2 = g.P[10];
     return p;
+}
+
+// One view's projection of a voxel centre, in FP64.
+struct Tap4 {
+    float fx, fy;
+    double x0, y0;
+    float u, v, rc;
+};
+
+// Projection of a voxel centre known to lie in front of the camera (depth
+// c > 0), for instance a voxel of a workgroup whose pixel box is valid: the
+// depth is affine in the position and positive at every corner of the box.
+__device__ __forceinline__ void project64_front(const Proj64 &p, double Zd, Tap4 &t)
+{
+#pragma clang fp contract(off)          // u - floor(u) of the rounded u in every kernel: the same bits
+    const double c = fma(p.pz2, Zd, p.cx);
+    const double r = rcp64(c);
+    const double u = fma(p.pz0, Zd, p.ax) * r;
+    const double w = fma(p.pz1, Zd, p.bx) * r;
+    t.x0 = floor(u);
+    t.y0 = floor(w);
+    t.fx = static_cast<float>(u - t.x0);
+    t.fy = static_cast<float>(w - t.y0);
+    t.u = static_cast<float>(u);
+    t.v = static_cast<float>(w);
+    t.rc = static_cast<float>(r);
+}
+
+// The same for any voxel centre: false when it is not in front.
+__device__ __forceinline__ bool project64(const Proj64 &p, double Zd, Tap4 &t)
+{
+    if (!(fma(p.pz2, Zd, p.cx) > 0.0)) return false;
+    project64_front(p, Zd, t);
+    return true;
+}
+
+// FP64 voxel centre coordinate of the bilinear paths.
+__device__ __forceinline__ double centre64(float o, float h, int i)
+{
+    return fma(static_cast<double>(h), i + 0.5, static_cast<double>(o));
 }
 
 // Bit v of the result is set when every voxel centre of this wave's box
@@ -678,23 +727,16 @@ __device__ __forceinline__ void fuse_column(const Views &views, int n, const flo
         // du * (l10 - l00) of the sample, and FP32 cannot place u closer than
         // ~3e-5 px at u ~ 640. The projection is therefore evaluated in FP64
         // (full rate on CDNA4, like unpacked FP32), from the FP64 voxel centre.
-        const double Xd = static_cast<double>(a.ox) + static_cast<double>(a.h) * (i + 0.5);
-        const double Yd = static_cast<double>(a.oy) + static_cast<double>(a.h) * (j + 0.5);
+        const double Xd = centre64(a.ox, a.h, i), Yd = centre64(a.oy, a.h, j);
         for (int v = 0; v < n; ++v) {
             const ViewGeom &g = views(v);
             const float *map = lmap + g.map_off;
             const Proj64 p = proj64_column(g, Xd, Yd);
 #pragma unroll
             for (int kk = 0; kk < KZ; ++kk) {
-                const double Zd = static_cast<double>(a.oz) + static_cast<double>(a.h) * (k0 + kk + 0.5);
-                const double c = fma(p.pz2, Zd, p.cx);
-                if (!(c > 0.0)) continue;
-                const double r = 1.0 / c;
-                const double u = fma(p.pz0, Zd, p.ax) * r;
-                const double w = fma(p.pz1, Zd, p.bx) * r;
-                const double x0 = floor(u), y0 = floor(w);
-                const float fx = static_cast<float>(u - x0), fy = static_cast<float>(w - y0);
-                L[kk] += bilinear_sample(map, g.W, g.H, x0, y0, fx, fy);
+                Tap4 t;
+                if (!project64(p, centre64(a.oz, a.h, k0 + kk), t)) continue;
+                L[kk] += bilinear_sample(map, g.W, g.H, t.x0, t.y0, t.fx, t.fy);
             }
         }
     }

@@ -68,6 +68,19 @@ struct FuseArgs {
     float tau;                          // threshold on the posterior
 };
 
+// Bilinear fusion from staged pixel boxes: FuseArgs with the camera matrices
+// widened to FP64 (the operands of the FP64 projection).
+struct BilinearArgs {
+    ViewGeom view[kMaxViews];
+    double Pd[kMaxViews][12];
+    const float *lmap;
+    float *post;
+    uint8_t *occ;                       // nullable
+    int32_t n, nx, ny, nz;
+    float ox, oy, oz, h;
+    float L0, tau;
+};
+
 // Frame B's images of a two-frame pass (frame A's travel in SlmArgs).
 struct PairImages {
     const uint8_t *img[kMaxViews];
