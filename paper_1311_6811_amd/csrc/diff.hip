@@ -35,6 +35,7 @@ using namespace dev;
 constexpr int kBlock = kBoxThreads;
 constexpr int kWaves = kBlock / 64;
 constexpr int kBoxCap = 4096;           // floats of one view's pixel box staged in LDS (backward)
+constexpr int kBwdBlocks = 1024;        // workgroups of the backward (four per CU): smaller grids split their views
 constexpr int kFwdArena = 7500;         // floats of the forward's staged boxes
 constexpr int kStageIters = kBoxCap / kBlock;
 
@@ -227,10 +228,157 @@ __global__ __launch_bounds__(256) void zero_kernel(float *p, int64_t n4)
         reinterpret_cast<f32x4 *>(p)[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 }
 
+// A lane's sums over its voxels of one view: g_r and g_r Z for the rows r of P.
+struct CamSums {
+    float su = 0.0f, suz = 0.0f, sv = 0.0f, svz = 0.0f, sc = 0.0f, scz = 0.0f;
+};
+
+// Fixed-point terms of one voxel's four taps.
+struct TapTerms {
+    int q00, q10, q01, q11;
+};
+
+__device__ __forceinline__ TapTerms tap_terms(float gk, float fx, float fy, float qscale)
+{
+    return TapTerms{static_cast<int>(rintf(gk * (1.0f - fx) * (1.0f - fy) * qscale)),
+                    static_cast<int>(rintf(gk * fx * (1.0f - fy) * qscale)),
+                    static_cast<int>(rintf(gk * (1.0f - fx) * fy * qscale)), static_cast<int>(rintf(gk * fx * fy * qscale))};
+}
+
+__device__ __forceinline__ void add_camera_terms(CamSums &s, float gk, const Tap4 &t, float Z, float l00, float l10,
+                                                 float l01, float l11)
+{
+    const float dldu = (1.0f - t.fy) * (l10 - l00) + t.fy * (l11 - l01);
+    const float dldv = (1.0f - t.fx) * (l01 - l00) + t.fx * (l11 - l10);
+    const float gu = gk * dldu * t.rc, gw = gk * dldv * t.rc;
+    const float gc = -(gu * t.u + gw * t.v);
+    s.su += gu; s.suz = fmaf(gu, Z, s.suz);
+    s.sv += gw; s.svz = fmaf(gw, Z, s.svz);
+    s.sc += gc; s.scz = fmaf(gc, Z, s.scz);
+}
+
+// Whether a voxel's adjoint terms can round to anything but 0 (NaN: yes):
+// every tap weight is at most 1 and rintf(0.5) is 0.
+__device__ __forceinline__ bool scatters(float gk, float qscale) { return !(fabsf(gk) * qscale <= 0.5f); }
+
+// The lane's voxels of one view, from the view's box staged
+// at `map_box`; with SCATTER their adjoint terms go to `adj_box`. As in the
+// forward kernel there are no per-voxel depth or range tests: a voxel whose
+// taps all fall outside the image reads four 0s, adds 0 to the camera sums and
+// scatters only into box pixels outside the image, which the flush skips: the
+// same as skipping it.
+template <bool SCATTER>
+__device__ __forceinline__ void box_voxels(const DiffArgs &a, const Proj64 &p, const PixBox &box, const float *map_box,
+                                           int *adj_box, int kb, const float (&gv)[kFZ], float qscale,
+                                           CamSums &s)
+{
+    const double wd = static_cast<double>(box.w);
+    const double od = static_cast<double>(box.y0) * wd + static_cast<double>(box.x0);
+    const int emax = box.w * box.h - box.w - 2;
+#pragma unroll
+    for (int kk = 0; kk < kFZ; ++kk) {
+        if (gv[kk] == 0.0f) continue;
+        const double Zd = centre64(a.oz, a.h, kb + kk);
+        Tap4 t;
+        project64_front(p, Zd, t);
+        const int e = min(max(static_cast<int>(fma(t.y0, wd, t.x0 - od)), 0), emax);
+        const float l00 = map_box[e], l10 = map_box[e + 1], l01 = map_box[e + box.w], l11 = map_box[e + box.w + 1];
+        if (SCATTER && scatters(gv[kk], qscale)) {
+            const TapTerms q = tap_terms(gv[kk], t.fx, t.fy, qscale);
+            atomicAdd(&adj_box[e], q.q00);
+            atomicAdd(&adj_box[e + 1], q.q10);
+            atomicAdd(&adj_box[e + box.w], q.q01);
+            atomicAdd(&adj_box[e + box.w + 1], q.q11);
+        }
+        add_camera_terms(s, gv[kk], t, static_cast<float>(Zd), l00, l10, l01, l11);
+    }
+}
+
+// The lane's voxels of a view without a box: taps from the map, adjoint terms
+// into the global sums.
+__device__ __forceinline__ void map_voxels(const DiffArgs &a, const ViewGeom &g, const Proj64 &p, int kb,
+                                           const float (&gv)[kFZ], float qscale, CamSums &s)
+{
+    const float *map = a.lmap + g.map_off;
+    unsigned long long *adj = reinterpret_cast<unsigned long long *>(a.adj) + g.map_off;
+#pragma unroll
+    for (int kk = 0; kk < kFZ; ++kk) {
+        if (gv[kk] == 0.0f) continue;
+        const double Zd = centre64(a.oz, a.h, kb + kk);
+        Tap4 t;
+        if (!project64(p, Zd, t)) continue;
+        if (!(t.x0 >= -1.0 && t.x0 < g.W && t.y0 >= -1.0 && t.y0 < g.H)) continue;
+        const int ix = static_cast<int>(t.x0), iy = static_cast<int>(t.y0);
+        const bool xin0 = ix >= 0, xin1 = ix + 1 < g.W, yin0 = iy >= 0, yin1 = iy + 1 < g.H;
+        const int64_t base = static_cast<int64_t>(iy) * g.W + ix;
+        const float l00 = xin0 && yin0 ? map[base] : 0.0f, l10 = xin1 && yin0 ? map[base + 1] : 0.0f;
+        const float l01 = xin0 && yin1 ? map[base + g.W] : 0.0f, l11 = xin1 && yin1 ? map[base + g.W + 1] : 0.0f;
+        if (scatters(gv[kk], qscale)) {
+            const TapTerms q = tap_terms(gv[kk], t.fx, t.fy, qscale);
+            if (xin0 && yin0) atomicAdd(adj + base, widen(q.q00));
+            if (xin1 && yin0) atomicAdd(adj + base + 1, widen(q.q10));
+            if (xin0 && yin1) atomicAdd(adj + base + g.W, widen(q.q01));
+            if (xin1 && yin1) atomicAdd(adj + base + g.W + 1, widen(q.q11));
+        }
+        add_camera_terms(s, gv[kk], t, static_cast<float>(Zd), l00, l10, l01, l11);
+    }
+}
+
+// dLoss/dP row r of one view = sum over the lanes' voxels of g_r (X, Y, Z, 1):
+// the wave's sums of the 12 entries through its 768 floats of LDS, in a fixed
+// order: lane 4e + m adds lanes 16m .. 16m+15 of entry e, then a quad
+// butterfly; lane 4e writes out[e].
+__device__ __forceinline__ void wave_camera_sums(const CamSums &s, float X, float Y, float *red, float *out)
+{
+    const int lane = static_cast<int>(threadIdx.x & 63);
+    const float vals[12] = {X * s.su, Y * s.su, s.suz, s.su, X * s.sv, Y * s.sv, s.svz, s.sv, X * s.sc, Y * s.sc, s.scz, s.sc};
+#pragma unroll
+    for (int e = 0; e < 12; ++e) red[e * 64 + lane] = vals[e];
+    wave_lds_sync();
+    float t = 0.0f;
+    if (lane < 48) {
+        const f32x4 *src = reinterpret_cast<const f32x4 *>(red + (lane >> 2) * 64 + (lane & 3) * 16);
+        const f32x4 r0 = src[0], r1 = src[1], r2 = src[2], r3 = src[3];
+        t = (((r0.x + r0.y) + (r0.z + r0.w)) + ((r1.x + r1.y) + (r1.z + r1.w))) +
+            (((r2.x + r2.y) + (r2.z + r2.w)) + ((r3.x + r3.y) + (r3.z + r3.w)));
+    }
+    t += dpp<0xb1>(t);
+    t += dpp<0x4e>(t);
+    if (lane < 48 && (lane & 3) == 0) out[lane >> 2] = t;
+    wave_lds_sync();
+}
+
+// Adds a view's adjoint box to the global sums and clears what it read.
+__device__ __forceinline__ void flush_box(const PixBox &box, int *adj_box, unsigned long long *adj, int W, int H)
+{
+    const int area = box.w * box.h;
+    const float inv_w = 1.0f / static_cast<float>(box.w);
+    for (int e = threadIdx.x; e < area; e += kBlock) {
+        int r, c;
+        box_rc(e, box.w, inv_w, r, c);
+        const int x = box.x0 + c, y = box.y0 + r;
+        const int val = adj_box[e];
+        adj_box[e] = 0;
+        if (x >= 0 && x < W && y >= 0 && y < H && val != 0) atomicAdd(adj + static_cast<int64_t>(y) * W + x, widen(val));
+    }
+}
+
+// Workgroup (b, y): views [n y / gridDim.y, n (y + 1) / gridDim.y) of block b.
+// Bound by the instructions of the FP64 projection and of the camera terms.
+// Only voxels whose term can round to something (scatters) quantise and add
+// their four tap terms: away from the body the sigmoid differs from the label
+// by less than 2^-20, so most workgroups have no such voxel, and these need no
+// adjoint box, no flush and fewer barriers (their views' boxes are staged in
+// groups, as in the forward). Where a view's box is larger than its LDS, what
+// is left of the global atomics is the surface's. Backward pass (zeroing, this
+// kernel, pixel chain) at 160^3 x 8 views of 1280x720: 1706 -> 225 us; 224^3 x 12: 765 -> 458;
+// 128^3 x 8 of 640x480: 94 -> 87. Grids of fewer than kBwdBlocks blocks split
+// their views over gridDim.y (61 x 53 x 47 x 5 views, 96 blocks: 41 -> 26 us).
 __global__ __launch_bounds__(kBlock) void diff_bwd_kernel(DiffArgs a)
 {
-    __shared__ __align__(16) float lmap_box[kBoxCap];
-    __shared__ int adj_box[kBoxCap];
+    constexpr int kRed = 12 * 64;                       // floats of one wave's camera reduction
+    constexpr int kGroup = 2 * kBoxCap - kWaves * kRed; // floats of a group's boxes
+    __shared__ __align__(16) float arena[2 * kBoxCap];
     __shared__ float cam[kWaves][kMaxViews * 12];
     __shared__ PixBox boxes[kMaxViews];
     const Coords q = block_coords<true>(a.nx, a.ny, a.nz);
@@ -239,9 +387,11 @@ __global__ __launch_bounds__(kBlock) void diff_bwd_kernel(DiffArgs a)
     const double Xd = centre64(a.ox, a.h, q.i), Yd = centre64(a.oy, a.h, q.j);
     const float gl = *a.grad_loss;
     const float qscale = ldexpf(1.0f, adjoint_exponent(gl, a.inv_count));
+    const int v_lo = a.n * static_cast<int>(blockIdx.y) / static_cast<int>(gridDim.y);
+    const int v_hi = a.n * static_cast<int>(blockIdx.y + 1) / static_cast<int>(gridDim.y);
 
     float gv[kFZ];
-    bool any = false;
+    bool any = false, hot = false;
 #pragma unroll
     for (int kk = 0; kk < kFZ; ++kk) {
         const int k = q.kb + kk;
@@ -250,143 +400,73 @@ __global__ __launch_bounds__(kBlock) void diff_bwd_kernel(DiffArgs a)
             const int64_t idx = (static_cast<int64_t>(k) * a.ny + q.j) * a.nx + q.i;
             gv[kk] = gl * (sigmoidf_stable(a.logits[idx]) - static_cast<float>(a.labels[idx])) * a.inv_count;
             any = any || gv[kk] != 0.0f;
+            hot = hot || scatters(gv[kk], qscale);
         }
     }
+    const int wave = threadIdx.x >> 6;
     // a workgroup with no voxel in the loss region contributes nothing
     const bool block_any = __syncthreads_or(any ? 1 : 0) != 0;
-    if (block_any) compute_boxes<kFX, kFY, kFZ>(a, q.bi, q.bj, q.kb, kBoxCap, boxes);
-    // the adjoint box starts at zero once; each view's flush clears the
-    // entries it reads, and a view scatters only inside its own box
-    for (int e = threadIdx.x; e < kBoxCap; e += kBlock) adj_box[e] = 0;
-    __syncthreads();
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const bool block_hot = __syncthreads_or(hot ? 1 : 0) != 0;
+    if (!block_any) {
+        for (int e = 12 * v_lo + static_cast<int>(threadIdx.x); e < 12 * v_hi; e += kBlock)
+            a.cam_part[static_cast<int64_t>(blockIdx.x) * a.n * 12 + e] = 0.0f;
+        return;
+    }
+    compute_boxes<kFX, kFY, kFZ>(a, q.bi, q.bj, q.kb, block_hot ? kBoxCap : kGroup, boxes);
 
-    for (int v = 0; v < a.n; ++v) {
-        const ViewGeom &g = a.view[v];
-        const float *map = a.lmap + g.map_off;
-        unsigned long long *adj = reinterpret_cast<unsigned long long *>(a.adj) + g.map_off;
-        const Proj64 p = proj64_view(a, v, Xd, Yd);
-        PixBox box{0, 0, 0, 0, 0};
-        if (block_any) box = read_box(boxes, v);
-        if (box.ok) {
-            __syncthreads();                // the previous view's flush is done
-            stage_box(lmap_box, box, map, g.W, g.H);
-            __syncthreads();
+    if (block_hot) {
+        float *map_box = arena;
+        int *adj_box = reinterpret_cast<int *>(arena + kBoxCap);
+        // the adjoint box starts at zero once; each view's flush clears the
+        // entries it reads, and a view scatters only inside its own box
+        for (int e = threadIdx.x; e < kBoxCap; e += kBlock) adj_box[e] = 0;
+        __syncthreads();
+        for (int v = v_lo; v < v_hi; ++v) {
+            const ViewGeom &g = a.view[v];
+            const Proj64 p = proj64_view(a, v, Xd, Yd);
+            const PixBox box = read_box(boxes, v);
+            CamSums s;
+            __syncthreads();                // the previous view's flush and camera sums are done
+            if (box.ok) {
+                stage_box(map_box, box, a.lmap + g.map_off, g.W, g.H);
+                __syncthreads();
+                box_voxels<true>(a, p, box, map_box, adj_box, q.kb, gv, qscale, s);
+                __syncthreads();            // every scatter into the box is done
+                flush_box(box, adj_box, reinterpret_cast<unsigned long long *>(a.adj) + g.map_off, g.W, g.H);
+            } else {
+                map_voxels(a, g, p, q.kb, gv, qscale, s);
+            }
+            // the staged box is free: each wave reduces in its own 768 floats of it
+            wave_camera_sums(s, X, Y, map_box + wave * kRed, &cam[wave][v * 12]);
         }
-        float su = 0.0f, suz = 0.0f, sv = 0.0f, svz = 0.0f, sc = 0.0f, scz = 0.0f;
-        if (box.ok) {
-            const double wd = static_cast<double>(box.w);
-            const double od = static_cast<double>(box.y0) * wd + static_cast<double>(box.x0);
-            const int emax = box.w * box.h - box.w - 2;
-            // as in the forward kernel: no per-voxel depth or range tests. A
-            // voxel whose taps all fall outside the image reads four 0s, adds
-            // 0 to the camera sums and scatters only into box pixels outside
-            // the image, which the flush skips: the same as skipping it.
-#pragma unroll
-            for (int kk = 0; kk < kFZ; ++kk) {
-                if (gv[kk] == 0.0f) continue;
-                const double Zd = centre64(a.oz, a.h, q.kb + kk);
-                Tap4 t;
-                project64_front(p, Zd, t);
-                const float fx = t.fx, fy = t.fy, gk = gv[kk];
-                const int q00 = static_cast<int>(rintf(gk * (1.0f - fx) * (1.0f - fy) * qscale));
-                const int q10 = static_cast<int>(rintf(gk * fx * (1.0f - fy) * qscale));
-                const int q01 = static_cast<int>(rintf(gk * (1.0f - fx) * fy * qscale));
-                const int q11 = static_cast<int>(rintf(gk * fx * fy * qscale));
-                const int e = min(max(static_cast<int>(fma(t.y0, wd, t.x0 - od)), 0), emax);
-                const float l00 = lmap_box[e], l10 = lmap_box[e + 1], l01 = lmap_box[e + box.w], l11 = lmap_box[e + box.w + 1];
-                atomicAdd(&adj_box[e], q00);
-                atomicAdd(&adj_box[e + 1], q10);
-                atomicAdd(&adj_box[e + box.w], q01);
-                atomicAdd(&adj_box[e + box.w + 1], q11);
-                const float dldu = (1.0f - fy) * (l10 - l00) + fy * (l11 - l01);
-                const float dldv = (1.0f - fx) * (l01 - l00) + fx * (l11 - l10);
-                const float gu = gk * dldu * t.rc, gw = gk * dldv * t.rc;
-                const float gc = -(gu * t.u + gw * t.v);
-                const float Z = static_cast<float>(Zd);
-                su += gu; suz = fmaf(gu, Z, suz);
-                sv += gw; svz = fmaf(gw, Z, svz);
-                sc += gc; scz = fmaf(gc, Z, scz);
+    } else {
+        __syncthreads();                    // boxes visible
+        float *red = arena + kGroup + wave * kRed;
+        for (int v0 = v_lo; v0 < v_hi;) {
+            const int v1 = stage_group<kGroup>(a, v0, v_hi, boxes, arena);
+            __syncthreads();                // every wave's loads have landed
+            int off = 0;
+            for (int v = v0; v < v1; ++v) {
+                const Proj64 p = proj64_view(a, v, Xd, Yd);
+                const PixBox box = read_box(boxes, v);
+                CamSums s;
+                if (box.ok) {
+                    box_voxels<false>(a, p, box, arena + off, nullptr, q.kb, gv, qscale, s);
+                    off += box.w * box.h;
+                } else {
+                    map_voxels(a, a.view[v], p, q.kb, gv, qscale, s);
+                }
+                wave_camera_sums(s, X, Y, red, &cam[wave][v * 12]);
             }
-        } else {
-#pragma unroll
-            for (int kk = 0; kk < kFZ; ++kk) {
-                if (gv[kk] == 0.0f) continue;
-                const double Zd = centre64(a.oz, a.h, q.kb + kk);
-                Tap4 t;
-                if (!project64(p, Zd, t)) continue;
-                if (!(t.x0 >= -1.0 && t.x0 < g.W && t.y0 >= -1.0 && t.y0 < g.H)) continue;
-                const int ix = static_cast<int>(t.x0), iy = static_cast<int>(t.y0);
-                const bool xin0 = ix >= 0, xin1 = ix + 1 < g.W, yin0 = iy >= 0, yin1 = iy + 1 < g.H;
-                const float fx = t.fx, fy = t.fy, gk = gv[kk];
-                const int q00 = static_cast<int>(rintf(gk * (1.0f - fx) * (1.0f - fy) * qscale));
-                const int q10 = static_cast<int>(rintf(gk * fx * (1.0f - fy) * qscale));
-                const int q01 = static_cast<int>(rintf(gk * (1.0f - fx) * fy * qscale));
-                const int q11 = static_cast<int>(rintf(gk * fx * fy * qscale));
-                const int64_t base = static_cast<int64_t>(iy) * g.W + ix;
-                float l00 = 0.0f, l10 = 0.0f, l01 = 0.0f, l11 = 0.0f;
-                if (xin0 && yin0) { l00 = map[base]; atomicAdd(adj + base, widen(q00)); }
-                if (xin1 && yin0) { l10 = map[base + 1]; atomicAdd(adj + base + 1, widen(q10)); }
-                if (xin0 && yin1) { l01 = map[base + g.W]; atomicAdd(adj + base + g.W, widen(q01)); }
-                if (xin1 && yin1) { l11 = map[base + g.W + 1]; atomicAdd(adj + base + g.W + 1, widen(q11)); }
-                const float dldu = (1.0f - fy) * (l10 - l00) + fy * (l11 - l01);
-                const float dldv = (1.0f - fx) * (l01 - l00) + fx * (l11 - l10);
-                const float gu = gk * dldu * t.rc, gw = gk * dldv * t.rc;
-                const float gc = -(gu * t.u + gw * t.v);
-                const float Z = static_cast<float>(Zd);
-                su += gu; suz = fmaf(gu, Z, suz);
-                sv += gw; svz = fmaf(gw, Z, svz);
-                sc += gc; scz = fmaf(gc, Z, scz);
-            }
-        }
-        if (box.ok) {
-            __syncthreads();                // every scatter into the box is done
-            const int area = box.w * box.h;
-            const float inv_w = 1.0f / static_cast<float>(box.w);
-            for (int e = threadIdx.x; e < area; e += kBlock) {
-                int r, c;
-                box_rc(e, box.w, inv_w, r, c);
-                const int x = box.x0 + c, y = box.y0 + r;
-                const int val = adj_box[e];
-                adj_box[e] = 0;
-                if (x >= 0 && x < g.W && y >= 0 && y < g.H && val != 0)
-                    atomicAdd(adj + static_cast<int64_t>(y) * g.W + x, widen(val));
-            }
-        }
-        // dLoss/dP row r = sum over the lane's voxels of g_r * (X, Y, Z, 1)
-        if (block_any) {
-            const float vals[12] = {X * su, Y * su, suz, su, X * sv, Y * sv, svz, sv, X * sc, Y * sc, scz, sc};
-            // Wave sums of the 12 entries through LDS, in a fixed order: the
-            // wave writes its 12 x 64 values, lane 4e + m adds lanes
-            // 16m .. 16m+15 of entry e, then a quad butterfly. The staged box
-            // is free here (every wave has passed the view's scatter barrier,
-            // and the next view stages after a barrier): each wave uses its
-            // own 768 floats of it.
-            float *red = lmap_box + wave * (12 * 64);
-#pragma unroll
-            for (int e = 0; e < 12; ++e) red[e * 64 + lane] = vals[e];
-            wave_lds_sync();
-            float s = 0.0f;
-            if (lane < 48) {
-                const f32x4 *src = reinterpret_cast<const f32x4 *>(red + (lane >> 2) * 64 + (lane & 3) * 16);
-                const f32x4 r0 = src[0], r1 = src[1], r2 = src[2], r3 = src[3];
-                s = (((r0.x + r0.y) + (r0.z + r0.w)) + ((r1.x + r1.y) + (r1.z + r1.w))) +
-                    (((r2.x + r2.y) + (r2.z + r2.w)) + ((r3.x + r3.y) + (r3.z + r3.w)));
-            }
-            s += dpp<0xb1>(s);
-            s += dpp<0x4e>(s);
-            if (lane < 48 && (lane & 3) == 0) cam[wave][v * 12 + (lane >> 2)] = s;
-            wave_lds_sync();
-        } else if (lane < 12) {
-            cam[wave][v * 12 + lane] = 0.0f;
+            v0 = v1;
+            if (v0 < v_hi) __syncthreads(); // the group's reads are done
         }
     }
     __syncthreads();
-    const int ne = a.n * 12;
-    for (int e = threadIdx.x; e < ne; e += kBlock) {
+    for (int e = 12 * v_lo + static_cast<int>(threadIdx.x); e < 12 * v_hi; e += kBlock) {
         float s = 0.0f;
         for (int w = 0; w < kWaves; ++w) s += cam[w][e];
-        a.cam_part[static_cast<int64_t>(blockIdx.x) * ne + e] = s;
+        a.cam_part[static_cast<int64_t>(blockIdx.x) * a.n * 12 + e] = s;
     }
 }
 
@@ -565,7 +645,10 @@ hipError_t launch_diff_backward(const DiffArgs &a, const ChainArgs &c, int64_t m
         hipLaunchKernelGGL(zero_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s, a.adj, n4);
     }
     const int64_t nb = diff_bwd_blocks(a.nx, a.ny, a.nz);
-    if (nb > 0 && a.n > 0) hipLaunchKernelGGL(diff_bwd_kernel, dim3(static_cast<unsigned>(nb)), dim3(kBlock), 0, s, a);
+    if (nb > 0 && a.n > 0) {
+        const int64_t split = std::min<int64_t>(a.n, (kBwdBlocks + nb - 1) / nb);
+        hipLaunchKernelGGL(diff_bwd_kernel, dim3(static_cast<unsigned>(nb), static_cast<unsigned>(split)), dim3(kBlock), 0, s, a);
+    }
     if (a.n > 0) {
         // the pixel chain also sums the camera-gradient partials (camera_gradient)
         ChainArgs ca = c;

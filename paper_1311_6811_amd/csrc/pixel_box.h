@@ -120,6 +120,23 @@ __device__ __forceinline__ void stage_box_async(float *lds, const PixBox &b, con
     }
 }
 
+// Starts staging the boxes of views v0, v0 + 1, ... (below v_hi) that fit the
+// CAP floats of `arena` together, one after another; returns the first view
+// that is left for the next group. Views without a valid box take no room.
+template <int CAP, class Args>
+__device__ __forceinline__ int stage_group(const Args &a, int v0, int v_hi, const PixBox *boxes, float *arena)
+{
+    int v = v0, off = 0;
+    for (; v < v_hi; ++v) {
+        const PixBox box = read_box(boxes, v);
+        if (!box.ok) continue;
+        if (off + box.w * box.h > CAP) break;
+        stage_box_async(arena + off, box, a.lmap + a.view[v].map_off, a.view[v].W, a.view[v].H);
+        off += box.w * box.h;
+    }
+    return v;
+}
+
 // L[kk] += the bilinear sample of every view, in view order, at the lane's
 // KZ voxels (Xd, Yd, slice kb + kk) of the workgroup's 16 x 16 x KZ voxel
 // block. The views are taken in groups whose boxes fit the CAP floats of
@@ -130,16 +147,9 @@ __device__ __forceinline__ void add_bilinear(const Args &a, double Xd, double Yd
                                              const PixBox *boxes, float (&L)[KZ])
 {
     for (int v0 = 0; v0 < a.n;) {
-        int v1 = v0, off = 0;
-        for (; v1 < a.n; ++v1) {
-            const PixBox box = read_box(boxes, v1);
-            if (!box.ok) continue;
-            if (off + box.w * box.h > CAP) break;
-            stage_box_async(arena + off, box, a.lmap + a.view[v1].map_off, a.view[v1].W, a.view[v1].H);
-            off += box.w * box.h;
-        }
+        const int v1 = stage_group<CAP>(a, v0, a.n, boxes, arena);
         __syncthreads();                    // every wave's loads have landed
-        off = 0;
+        int off = 0;
         for (int v = v0; v < v1; ++v) {
             const ViewGeom &g = a.view[v];
             const Proj64 p = proj64_view(a, v, Xd, Yd);
