@@ -26,14 +26,15 @@ constexpr unsigned long long kEmpty = ~0ull;
 // Pixel offset (within the view's buffer) and depth of list entry q in view g,
 // or false when the view does not see it. Same FP32 arithmetic as the
 // fusion's checked path, so both pick the same pixel.
-__device__ __forceinline__ bool locate(const ColourArgs &a, const ViewGeom &g, int64_t vox, uint32_t &pix,
+__device__ __forceinline__ bool locate(const ColourArgs &a, const ViewGeom &g, int32_t vox, uint32_t &pix,
                                        float &depth)
 {
     if (vox < 0 || vox >= a.nvox) return false;
-    const int64_t plane = static_cast<int64_t>(a.nx) * a.ny;
-    const int k = static_cast<int>(vox / plane);
-    const int64_t rem = vox - static_cast<int64_t>(k) * plane;
-    const int j = static_cast<int>(rem / a.nx), i = static_cast<int>(rem - static_cast<int64_t>(j) * a.nx);
+    // 0 <= vox < nx ny nz < 2^31: 32-bit divisions
+    const uint32_t v = static_cast<uint32_t>(vox), nx = static_cast<uint32_t>(a.nx);
+    const uint32_t row = v / nx;
+    const int i = static_cast<int>(v - row * nx), k = static_cast<int>(row / static_cast<uint32_t>(a.ny));
+    const int j = static_cast<int>(row - static_cast<uint32_t>(k) * static_cast<uint32_t>(a.ny));
     const float X = a.ox + a.h * (static_cast<float>(i) + 0.5f);
     const float Y = a.oy + a.h * (static_cast<float>(j) + 0.5f);
     const float Z = a.oz + a.h * (static_cast<float>(k) + 0.5f);
