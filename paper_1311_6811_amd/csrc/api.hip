@@ -10,6 +10,7 @@
 #include <new>
 #include <string>
 
+#include "block_tile.h"
 #include "host_util.h"
 #include "particles.h"
 
@@ -95,6 +96,102 @@ int64_t padded_pixels(int width, int height)
 }
 
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
+
+namespace {
+
+// Pixels of view c's box around the 16 x 16 x 8 voxel block in the middle of the
+// grid; a large number when a corner is not in front of the camera.
+double block_area(const psfs_camera &c, const psfs_grid &grid)
+{
+    const int dims[3] = {grid.nx, grid.ny, grid.nz}, edge[3] = {dev::kSBX, dev::kSBY, dev::kSBZ};
+    double lo[2] = {0.0, 0.0}, hi[2] = {0.0, 0.0};
+    for (int corner = 0; corner < 8; ++corner) {
+        double row[3] = {c.P[3], c.P[7], c.P[11]};
+        for (int d = 0; d < 3; ++d) {
+            const double x = grid.origin[d] + grid.voxel * (0.5 * dims[d] + ((corner >> d) & 1 ? 0.5 : -0.5) * edge[d]);
+            for (int r = 0; r < 3; ++r) row[r] += c.P[4 * r + d] * x;
+        }
+        if (!(row[2] > 0.0)) return 1e9;
+        for (int r = 0; r < 2; ++r) {
+            const double u = row[r] / row[2];
+            lo[r] = corner == 0 || u < lo[r] ? u : lo[r];
+            hi[r] = corner == 0 || u > hi[r] ? u : hi[r];
+        }
+    }
+    return std::fmin(1e9, (hi[0] - lo[0] + 4.0) * (hi[1] - lo[1] + 2.0));
+}
+
+double mean_block_area(const psfs_camera *cams, int n, const psfs_grid &grid)
+{
+    double area = 0.0;
+    for (int k = 0; k < n; ++k) area += block_area(cams[k], grid) / n;
+    return area;
+}
+
+}  // namespace
+
+// The block tile's cost per workgroup (boxes, one barrier per group of views) is
+// hidden only where the CUs run several rounds of blocks, sooner with many views
+// (128^3 x 8 views of 640x480, 1024 blocks: column tile 0 18.5 us, block 21.5;
+// 160^3 x 8, 2000 blocks: 33.8 / 31.4; 208^3 x 8, 4394 blocks: 67 / 53; 192^3 x 4 at
+// 520x390: 23.5 / 29.7). It saves the column tile's L1 accesses, which are the more
+// the further apart neighbouring voxels project (192^3 x 7 at 236x177, boxes of 149
+// pixels: 0.88 times the column's speed; at 520x390, 550 pixels: 0.97; 256^3 x 12 at
+// 1280x720, 2100 pixels: 1.4), and more again where the map's rows lie a multiple of 256
+// bytes apart (192^3 x 8: column 51.6 us at a width of 640, 45.3 at 656; the block
+// 46.5 and 44.7). Boxes beyond the arena are gathered (128^3 x 12 at 1280x720, 6800
+// pixels: 34 / 37).
+bool block_pays(const psfs_camera *cams, int n, const psfs_grid &grid)
+{
+    if (n < 5 || dev::block_count(grid) * (n + 4) < 21000) return false;
+    int strided = 0;
+    for (int k = 0; k < n; ++k) strided += cams[k].width % 64 == 0;
+    const double area = mean_block_area(cams, n, grid);
+    return area >= (2 * strided > n ? 160.0 : 650.0) && area <= dev::kSArena;
+}
+
+// The boxes hold every pixel, the gathers of the column kernel only those that
+// the voxels read: with few voxels per pixel the gathers win. Column kernel against
+// boxes: 80^3 x 8 views of 640x480 (boxes of 3900 pixels for a block of 8 slices)
+// 28 / 26 us, 64^3 x 8 (6000) 18 / 24 us; at 1280x720 112^3 x 8 (5400) 64 / 42 us, 96^3 x 4
+// (5600) 19 / 22 us, 64^3 x 4 (12700) 11 / 19 us.
+bool bilinear_boxes_pay(const psfs_camera *cams, int n, const psfs_grid &grid)
+{
+    const double area = mean_block_area(cams, n, grid);
+    return area <= 4200.0 || (area <= 6500.0 && dev::block_count(grid) >= 500);
+}
+
+// The projection maps the box of the centres into the hull of its 8 projected
+// corners when these are all in front of the camera. A lane's FP32 coordinate is
+// within 1.8e-7 (S_u + |u| S_c) / c + 1.8e-7 |u| of the exact one (S: the sum of
+// a row's absolute terms), largest at a corner; five times that and 1/64 px are
+// kept free at the image's border.
+bool grid_inside(const ViewGeom &g, const psfs_grid &grid)
+{
+    const int dims[3] = {grid.nx, grid.ny, grid.nz}, pad[3] = {32, 32, 8};      // largest tile along each axis
+    double lo[3], hi[3];
+    for (int d = 0; d < 3; ++d) {
+        const int64_t n = (static_cast<int64_t>(dims[d]) + pad[d] - 1) / pad[d] * pad[d];
+        lo[d] = grid.origin[d] + grid.voxel * 0.5;
+        hi[d] = grid.origin[d] + grid.voxel * (static_cast<double>(n) - 0.5);
+    }
+    for (int corner = 0; corner < 8; ++corner) {
+        const double X[3] = {corner & 1 ? hi[0] : lo[0], corner & 2 ? hi[1] : lo[1], corner & 4 ? hi[2] : lo[2]};
+        double row[3], sum[3];
+        for (int r = 0; r < 3; ++r) {
+            const float *P = g.P + 4 * r;
+            row[r] = P[0] * X[0] + P[1] * X[1] + P[2] * X[2] + P[3];
+            sum[r] = std::fabs(P[0] * X[0]) + std::fabs(P[1] * X[1]) + std::fabs(P[2] * X[2]) + std::fabs(static_cast<double>(P[3]));
+        }
+        if (!(row[2] > 1e-4 * sum[2])) return false;            // NaN too
+        for (int r = 0; r < 2; ++r) {
+            const double u = row[r] / row[2];
+            const double margin = 0.015625 + 9e-7 * ((sum[r] + std::fabs(u) * sum[2]) / row[2] + std::fabs(u));
+            if (!(margin < 0.25 && u >= margin && u <= (r == 0 ? g.W : g.H) - margin)) return false;
+        }
+    }
+    return true;
+}
 
 }  // namespace host
 
@@ -250,6 +347,7 @@ void fill_geometry(const psfs_plan *p, int sampling, FuseArgs &a)
         g.W = p->cams[k].width;
         g.H = p->cams[k].height;
         g.map_off = map_offset(p, k);
+        if (sampling == PSFS_NEAREST && p->has_grid && grid_inside(g, p->grid)) a.inside |= 1u << k;
     }
     a.nx = p->grid.nx;
     a.ny = p->grid.ny;
@@ -263,6 +361,13 @@ void fill_geometry(const psfs_plan *p, int sampling, FuseArgs &a)
     a.tau = p->params.threshold;
 }
 
+// The plan's tile, or the better one for its grid and rig when none was set.
+int launch_tile(const psfs_plan *p)
+{
+    if (p->tile >= 0) return p->tile;
+    return p->params.sampling == PSFS_NEAREST && block_pays(p->cams, p->n, p->grid) ? block_tile() : default_tile();
+}
+
 int enqueue_fuse(const psfs_plan *p, const float *lmap, float *post, uint8_t *occ, hipStream_t s)
 {
     if (nvox(p->grid) == 0) return PSFS_OK;
@@ -273,8 +378,8 @@ int enqueue_fuse(const psfs_plan *p, const float *lmap, float *post, uint8_t *oc
     a.lmap = lmap;
     a.post = post;
     a.occ = occ;
-    const int tile = p->tile >= 0 ? p->tile : default_tile();
-    hipError_t e = launch_fuse(a, tile, p->params.sampling, s);
+    const bool boxes = p->params.sampling == PSFS_BILINEAR && bilinear_boxes_pay(p->cams, p->n, p->grid);
+    hipError_t e = launch_fuse(a, launch_tile(p), p->params.sampling, boxes, s);
     if (e != hipSuccess) return hip_fail(e, "fusion kernel launch");
     return PSFS_OK;
 }
@@ -649,8 +754,7 @@ int psfs_pipeline_step(psfs_plan *plan, const uint8_t *const *images_dev, float 
     fa.occ = fa.post ? occ_dev : nullptr;
     if (sa.n == 0 && !fa.post) return PSFS_OK;
     if ((rc = check_device())) return rc;
-    const int tile = plan->tile >= 0 ? plan->tile : default_tile();
-    hipError_t e = launch_pipeline(sa, fa, tile, plan->params.sampling, max_np, static_cast<hipStream_t>(stream));
+    hipError_t e = launch_pipeline(sa, fa, launch_tile(plan), plan->params.sampling, max_np, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(e, "pipelined kernel launch");
     return PSFS_OK;
     PSFS_GUARD_END

@@ -13,7 +13,7 @@
 // parts as separate launches instead. Per-pixel and per-column code is that
 // of the single-frame kernels, so a batched frame is bit-identical to the
 // same frame reconstructed alone.
-#include "kernels_common.h"
+#include "block_tile.h"
 
 namespace psfs {
 namespace {
@@ -67,6 +67,33 @@ __global__ __launch_bounds__(TX * TY) void batch_pipe_kernel(BatchArgs a, int fl
     }
 }
 
+// As batch_pipe_kernel, the fusion from pixel boxes staged in LDS (block_tile.h):
+// the steps of the block tile whose frame's grid and rig make that the faster way
+// (block_pays; the other steps run tile 0). One kernel for both kinds of fusion
+// made every step ~10 % slower (its LDS and code serve the likelihood too).
+__global__ __launch_bounds__(kSBThreads) void batch_pipe_block_kernel(BatchArgs a, int fl, int ff, PipeArgs p)
+{
+    static_assert(kSBThreads == 256, "four waves per workgroup, as batch_slm_block and tile 0");
+    constexpr size_t kStageBytes = 4 * sizeof(SlmStage), kArenaBytes = kSArena * sizeof(float);
+    __shared__ __align__(16) unsigned char lds[kStageBytes > kArenaBytes ? kStageBytes : kArenaBytes];
+    __shared__ SBox boxes[kMaxViews];
+    const int round = static_cast<int>(blockIdx.x) / kNumXcd, x = static_cast<int>(blockIdx.x) % kNumXcd;
+    if (round < p.slm_rounds) {
+        batch_slm_block(a, fl, round * kNumXcd + x, p.slm_per_view, reinterpret_cast<SlmStage *>(lds));
+        return;
+    }
+    const int64_t tile = static_cast<int64_t>(x) * p.fuse_rounds + (round - p.slm_rounds);
+    if (tile >= p.fuse_tiles) return;
+    const BatchFrame &fr = a.frames[ff];
+    const GridDesc &g = fr.grid;
+    uint32_t bi, bj, bk;
+    octant_tile(static_cast<uint32_t>(tile), static_cast<uint32_t>((g.nx + kSBX - 1) / kSBX),
+                static_cast<uint32_t>((g.ny + kSBY - 1) / kSBY), static_cast<uint32_t>((g.nz + kSBZ - 1) / kSBZ), bi, bj, bk);
+    const BatchView *views = a.views + fr.view0;
+    fuse_block([&](int v) -> const ViewGeom & { return views[v].g; }, fr.n, a.lmap, g, bi, bj, bk, a.L0, a.tau, fr.post,
+               fr.occ, reinterpret_cast<float *>(lds), boxes);
+}
+
 // The separate launches of the 128-lane tile: a frame's likelihood, then its fusion.
 __global__ __launch_bounds__(256) void batch_slm_kernel(BatchArgs a, int fl, int per_view)
 {
@@ -100,7 +127,14 @@ hipError_t launch_pipe_s(const BatchArgs &a, int tile, int fl, int ff, const Pip
     case 3: return launch_pipe_t<8, 32, 2, S>(a, fl, ff, p, s);
     case 4: return launch_pipe_t<32, 8, 4, S>(a, fl, ff, p, s);
     case 5: return launch_pipe_t<16, 16, 4, S>(a, fl, ff, p, s);
-    case 6: return launch_pipe_t<16, 16, 8, S>(a, fl, ff, p, s);
+    case 6:
+        if (S == PSFS_BILINEAR) return launch_pipe_t<16, 16, 8, PSFS_BILINEAR>(a, fl, ff, p, s);
+        {
+            const int64_t blocks = static_cast<int64_t>(p.slm_rounds + p.fuse_rounds) * kNumXcd;
+            if (blocks == 0) return hipSuccess;
+            hipLaunchKernelGGL(batch_pipe_block_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kSBThreads), 0, s, a, fl, ff, p);
+            return hipGetLastError();
+        }
     default: return hipErrorInvalidValue;
     }
 }

@@ -26,6 +26,8 @@ struct psfs_batch {
     int device = -1;
     int cus = 0;
     int tile = 0;
+    bool automatic = true;                  // no tile was set: nearest frames run the block tile
+    std::vector<char> block;                // per user frame: block_pays at creation (the launches depend on it)
     std::vector<psfs_frame> user;           // caller's frame structs (pointers to their arrays not kept)
     std::vector<int> order;                 // order[i] = user frame placed i-th in the chain (chain_order)
     std::vector<psfs_camera> cams;          // all cameras, user frame order
@@ -35,7 +37,8 @@ struct psfs_batch {
     std::vector<BatchView> views;           // device table image (cost order)
     std::vector<BatchFrame> frames;
     std::vector<int64_t> slm_per_view;      // per table frame: likelihood workgroups per view
-    std::vector<int64_t> fuse_tiles;        // per table frame: fusion bricks of the current tile
+    std::vector<int> tiles;                 // per table frame: tile of its fusion
+    std::vector<int64_t> fuse_tiles;        // per table frame: fusion bricks of that tile
     int64_t map_floats = 0;
     void *dtable = nullptr;
     void *staging = nullptr;                // pinned host image of dtable
@@ -141,6 +144,13 @@ void take_frames(psfs_batch *b, int nframes, const psfs_frame *frames)
     }
 }
 
+// The tile the chain runs; on the block tile the nearest frames that tile 0
+// fuses faster run that one.
+int chain_tile(const psfs_batch *b)
+{
+    return b->automatic && b->params.sampling == PSFS_NEAREST ? block_tile() : b->tile;
+}
+
 // Builds the descriptor table (and the per-frame launch sizes) for the
 // current frames and tile.
 void build_table(psfs_batch *b)
@@ -151,12 +161,14 @@ void build_table(psfs_batch *b)
     b->frames.clear();
     b->slm_per_view.clear();
     b->fuse_tiles.clear();
+    b->tiles.clear();
     int64_t map_off = 0;
+    const int tile = chain_tile(b);
     for (int oi = 0; oi < nf; ++oi) {
         const int f = b->order[oi];
         const psfs_frame &u = b->user[f];
         BatchFrame fr{};
-        fr.grid = GridDesc{u.grid.nx, u.grid.ny, u.grid.nz, u.grid.origin[0], u.grid.origin[1], u.grid.origin[2], u.grid.voxel};
+        fr.grid = GridDesc{u.grid.nx, u.grid.ny, u.grid.nz, u.grid.origin[0], u.grid.origin[1], u.grid.origin[2], u.grid.voxel, 0u};
         fr.n = u.n;
         fr.view0 = static_cast<int32_t>(b->views.size());
         fr.post = u.posterior_dev;
@@ -176,6 +188,7 @@ void build_table(psfs_batch *b)
             v.g.W = c.width;
             v.g.H = c.height;
             v.g.map_off = map_off;
+            if (nearest && grid_inside(v.g, u.grid)) fr.grid.inside |= 1u << k;
             v.img = b->imgs[ci];
             v.mean = b->means[ci];
             v.var = b->vars[ci];
@@ -186,7 +199,8 @@ void build_table(psfs_batch *b)
         }
         b->frames.push_back(fr);
         b->slm_per_view.push_back(batch_slm_blocks_per_view(max_np));
-        b->fuse_tiles.push_back(batch_bricks(u.grid.nx, u.grid.ny, u.grid.nz, b->tile));
+        b->tiles.push_back(nearest && tile == block_tile() && !b->block[f] ? default_tile() : tile);
+        b->fuse_tiles.push_back(batch_bricks(u.grid.nx, u.grid.ny, u.grid.nz, b->tiles.back()));
     }
     b->map_floats = map_off;
     b->dirty = true;
@@ -263,7 +277,7 @@ hipError_t enqueue_batch(const psfs_batch *b, void *ws, hipStream_t s)
     const int nf = static_cast<int>(b->frames.size());
     for (int i = 0; i <= nf; ++i) {
         const int fl = i < nf ? i : -1, ff = i - 1;
-        hipError_t e = launch_batch_step(a, b->tile, b->params.sampling, fl, fl >= 0 ? b->slm_per_view[fl] : 0,
+        hipError_t e = launch_batch_step(a, ff >= 0 ? b->tiles[ff] : b->tiles[fl], b->params.sampling, fl, fl >= 0 ? b->slm_per_view[fl] : 0,
                                          fl >= 0 ? b->frames[fl].n : 0, ff, ff >= 0 ? b->fuse_tiles[ff] : 0, s);
         if (e != hipSuccess) return e;
     }
@@ -335,6 +349,7 @@ int psfs_batch_create(psfs_batch **out, const psfs_params *params, int nframes, 
     take_frames(b, nframes, frames);
     chain_order(frames, nframes, b->order);
     b->tile = default_tile();
+    for (int f = 0; f < nframes; ++f) b->block.push_back(block_pays(frames[f].cams, frames[f].n, frames[f].grid));
     build_table(b);
     b->dtable_bytes = align256(b->views.size() * sizeof(BatchView)) + align256(b->frames.size() * sizeof(BatchFrame));
     e = hipMalloc(&b->dtable, b->dtable_bytes);
@@ -390,7 +405,7 @@ int psfs_batch_run(psfs_batch *b, void *workspace_dev, size_t workspace_bytes_, 
     if (e != hipSuccess) return hip_fail(e, "hipStreamIsCapturing");
     // the null stream cannot be captured, and a caller's capture records the launches itself
     if (!s || st != hipStreamCaptureStatusNone) return run_eager(b, workspace_dev, s);
-    if (!b->exec || b->graph_ws != workspace_dev || b->graph_tile != b->tile) {
+    if (!b->exec || b->graph_ws != workspace_dev || b->graph_tile != chain_tile(b)) {
         drop_graph(b);
         e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
         if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
@@ -403,7 +418,7 @@ int psfs_batch_run(psfs_batch *b, void *workspace_dev, size_t workspace_bytes_, 
         e = hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0);
         if (e != hipSuccess) { drop_graph(b); return hip_fail(e, "hipGraphInstantiate"); }
         b->graph_ws = workspace_dev;
-        b->graph_tile = b->tile;
+        b->graph_tile = chain_tile(b);
     }
     e = hipGraphLaunch(b->exec, s);
     if (e != hipSuccess) return hip_fail(e, "hipGraphLaunch");
@@ -432,11 +447,10 @@ int psfs_batch_set_tile(psfs_batch *b, int tile)
     PSFS_GUARD_BEGIN
     if (!b) return fail(PSFS_E_ARG, "batch is NULL");
     if (tile < -1 || tile >= tile_count()) return fail(PSFS_E_RANGE, "tile %d outside -1..%d", tile, tile_count() - 1);
-    const int t = tile < 0 ? default_tile() : tile;
-    if (t != b->tile) {
-        b->tile = t;
-        build_table(b);
-    }
+    const int before = chain_tile(b);
+    b->automatic = tile < 0;
+    b->tile = tile < 0 ? default_tile() : tile;
+    if (chain_tile(b) != before) build_table(b);
     return PSFS_OK;
     PSFS_GUARD_END
 }

@@ -8,6 +8,7 @@
 // gives P(S_k|V=1) = SLM_k and P(S_k|V=0) = 1/2, so each view that sees a voxel
 // adds log(2*SLM_k) to the logit of Eq. 3. With SLM = u/(u+N) (Eq. 1-2, equal
 // pixel priors), log(2*SLM) = log 2 - softplus(log N - log u).
+#include "block_tile.h"
 #include "pixel_box.h"
 
 namespace psfs {
@@ -46,7 +47,7 @@ __device__ __forceinline__ void fuse_tile(const FuseArgs &a, int64_t b)
     const int i = static_cast<int>(txi) * TX + static_cast<int>(threadIdx.x % TX);
     const int j = static_cast<int>(tyi) * TY + static_cast<int>(threadIdx.x / TX);
     const int k0 = static_cast<int>(zc) * KZ;
-    const GridDesc gd{a.nx, a.ny, a.nz, a.ox, a.oy, a.oz, a.h};
+    const GridDesc gd{a.nx, a.ny, a.nz, a.ox, a.oy, a.oz, a.h, a.inside};
     fuse_column<TX, KZ, SAMPLING>([&](int v) -> const ViewGeom & { return a.view[v]; }, a.n, a.lmap, gd, i, j, k0,
                               a.L0, a.tau, a.post, a.occ);
 }
@@ -57,10 +58,10 @@ __host__ __device__ int64_t tile_count_of(const FuseArgs &a)
     return static_cast<int64_t>((a.nx + TX - 1) / TX) * ((a.ny + TY - 1) / TY) * ((a.nz + KZ - 1) / KZ);
 }
 
-template <int TX, int TY, int KZ>
+template <int TX, int TY, int KZ, int SAMPLING>
 __global__ __launch_bounds__(TX * TY) void fuse_kernel(FuseArgs a)
 {
-    fuse_tile<TX, TY, KZ, PSFS_NEAREST>(a, xcd_remap(blockIdx.x, tile_count_of<TX, TY, KZ>(a)));
+    fuse_tile<TX, TY, KZ, SAMPLING>(a, xcd_remap(blockIdx.x, tile_count_of<TX, TY, KZ>(a)));
 }
 
 // Likelihood maps of the next frame (Eq. 1-2, SlmArgs) and fusion of the
@@ -139,7 +140,7 @@ __global__ __launch_bounds__(TX * TY) void pipe_pair_kernel(SlmArgs s, PairImage
         const int pos = quad_lane_pos(static_cast<int>(threadIdx.x & 63));
         const int i = static_cast<int>(txi) * TX + (pos % TX);
         const int j = static_cast<int>(tyi) * TY + static_cast<int>(threadIdx.x >> 6) * (64 / TX) + pos / TX;
-        const GridDesc gd{f.nx, f.ny, f.nz, f.ox, f.oy, f.oz, f.h};
+        const GridDesc gd{f.nx, f.ny, f.nz, f.ox, f.oy, f.oz, f.h, f.inside};
         fuse_column_pair<TX, KZ>([&](int v) -> const ViewGeom & { return f.view[v]; }, f.n, f.lmap, gd, i, j,
                                  static_cast<int>(zc) * KZ, f.L0, f.tau, f.post, f.occ, post_b, occ_b,
                                  reinterpret_cast<float *>(&stage[threadIdx.x >> 6]));
@@ -186,7 +187,7 @@ __global__ __launch_bounds__(TX * TY) void pipe_quad_kernel(SlmArgs s, QuadImage
         const int pos = quad_lane_pos(static_cast<int>(threadIdx.x & 63));
         const int i = static_cast<int>(txi) * TX + (pos % TX);
         const int j = static_cast<int>(tyi) * TY + static_cast<int>(threadIdx.x >> 6) * (64 / TX) + pos / TX;
-        const GridDesc gd{f.nx, f.ny, f.nz, f.ox, f.oy, f.oz, f.h};
+        const GridDesc gd{f.nx, f.ny, f.nz, f.ox, f.oy, f.oz, f.h, f.inside};
         float *const post[4] = {f.post, qo.post[0], qo.post[1], qo.post[2]};
         uint8_t *const occ[4] = {f.occ, qo.occ[0], qo.occ[1], qo.occ[2]};
         fuse_column_quad<TX, KZ>([&](int v) -> const ViewGeom & { return f.view[v]; }, f.n, f.lmap, gd, i, j,
@@ -195,233 +196,11 @@ __global__ __launch_bounds__(TX * TY) void pipe_quad_kernel(SlmArgs s, QuadImage
     }
 }
 
-// ---- one-frame nearest fusion from pixel boxes staged in LDS ----------------
-// A workgroup of kSBThreads lanes fuses a kSBX x kSBY x kSBZ block of voxels
-// (lane t: column (t % 16, (t / 16) % 16), voxels kSBKZ (t / 256) ..
-// kSBKZ (t / 256) + kSBKZ - 1 of the block's slices). Per view, the voxel
-// centres of the block project into the hull of its 8 projected corner
-// centres (the depth is affine and positive at every corner, so on the block
-// the projection is continuous and maps the box into that hull); the pixel
-// box around the hull, widened by a bound on the FP32 rounding of the
-// per-voxel projection, holds every pixel a voxel-view of the block reads.
-// The boxes of all views are copied into one LDS arena in view order by
-// direct-to-LDS 4-byte buffer loads (one wave instruction per 64 consecutive
-// box entries; pixels outside the image read as 0), so that a workgroup waits
-// once for all its loads; the voxel-views then read LDS. Views whose box does
-// not fit in what is left of the arena, or whose corners are not clearly in
-// front of the camera, are gathered directly; views whose box misses the
-// image are skipped (every voxel-view of them adds 0). Same per-voxel
-// projection arithmetic, pixel rule and view order as fuse_column: the
-// posteriors are bit-identical.
-constexpr int kSBX = 16, kSBY = 16, kSBZ = 8;
-constexpr int kSBThreads = 512;
-constexpr int kSBKZ = kSBX * kSBY * kSBZ / kSBThreads;
-constexpr int kSArena = 8192;                       // staged floats per workgroup: 32 KB
-static_assert(kSBKZ * (kSBThreads / (kSBX * kSBY)) == kSBZ, "lanes cover the block");
-
-struct SBox {
-    int x0, y0, w, area;
-    int mode;                                       // 0: misses the image, 1: stageable, 2: direct gathers
-};
-
-// Voxel centre coordinate, as every fusion path computes it.
-__device__ __forceinline__ float voxel_centre(float o, float h, int i)
-{
-    return o + h * (static_cast<float>(i) + 0.5f);
-}
-
-// Pixel boxes of every view for the block with first voxel (i_lo, j_lo, k_lo)
-// (phantom voxels past the grid edge included, so that every lane's voxel
-// lies in the hull). Lanes 8v .. 8v+7 of the first two waves take the corners
-// of view v in FP64 from the FP32 centres the voxel lanes use; lane 8v writes
-// boxes[v]. The FP32 evaluation of floor's argument for a voxel (three
-// roundings in each of the numerator and the depth, a reciprocal of 1 ulp and
-// a product) is within 1.8e-7 (S_u + |u| S_c) / c + 1.8e-7 |u| of the exact
-// value, with S the sum of the absolute terms of a row: over the block S is
-// largest and c smallest at a corner. The box is widened by 2^-6 px plus five
-// times that bound.
-template <class Views>
-__device__ __forceinline__ void block_boxes(const Views &views, int n, const GridDesc &a, int i_lo, int j_lo,
-                                            int k_lo, SBox *boxes)
-{
-    const int t = static_cast<int>(threadIdx.x);
-    if (t >= 8 * kMaxViews) return;                 // whole waves: the shuffles need every lane
-    const int v = (t >> 3) < n ? (t >> 3) : 0;
-    const int corner = t & 7;
-    const ViewGeom &g = views(v);
-    const double X = voxel_centre(a.ox, a.h, i_lo + ((corner & 1) ? kSBX - 1 : 0));
-    const double Y = voxel_centre(a.oy, a.h, j_lo + ((corner & 2) ? kSBY - 1 : 0));
-    const double Z = voxel_centre(a.oz, a.h, k_lo + ((corner & 4) ? kSBZ - 1 : 0));
-    double row[3], sum[3];
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        const double t0 = static_cast<double>(g.P[4 * q]) * X, t1 = static_cast<double>(g.P[4 * q + 1]) * Y;
-        const double t2 = static_cast<double>(g.P[4 * q + 2]) * Z, t3 = static_cast<double>(g.P[4 * q + 3]);
-        row[q] = (t0 + t1) + (t2 + t3);
-        sum[q] = (fabs(t0) + fabs(t1)) + (fabs(t2) + fabs(t3));
-    }
-    const double c = row[2];
-    // NaN fails every comparison below; the 2^20 limits keep the conversions exact
-    bool ok = c > 1e-4 * sum[2] && sum[2] < 1e30;
-    const double u = ok ? row[0] / c : 0.0, w = ok ? row[1] / c : 0.0;
-    ok = ok && fabs(u) < 1048576.0 && fabs(w) < 1048576.0;
-    double umin = u, umax = u, wmin = w, wmax = w, cmin = ok ? c : -1.0;
-    double su = sum[0], sw = sum[1], sc = sum[2], au = fabs(u), aw = fabs(w);
-#pragma unroll
-    for (int m = 1; m <= 4; m <<= 1) {
-        umin = fmin(umin, __shfl_xor(umin, m, 64));
-        umax = fmax(umax, __shfl_xor(umax, m, 64));
-        wmin = fmin(wmin, __shfl_xor(wmin, m, 64));
-        wmax = fmax(wmax, __shfl_xor(wmax, m, 64));
-        cmin = fmin(cmin, __shfl_xor(cmin, m, 64));
-        su = fmax(su, __shfl_xor(su, m, 64));
-        sw = fmax(sw, __shfl_xor(sw, m, 64));
-        sc = fmax(sc, __shfl_xor(sc, m, 64));
-        au = fmax(au, __shfl_xor(au, m, 64));
-        aw = fmax(aw, __shfl_xor(aw, m, 64));
-    }
-    if ((t >> 3) >= n || corner != 0) return;
-    SBox b{0, 0, 0, 0, 2};
-    if (cmin > 0.0) {
-        const double mu = 0.015625 + 9e-7 * ((su + au * sc) / cmin + au);
-        const double mw = 0.015625 + 9e-7 * ((sw + aw * sc) / cmin + aw);
-        if (mu < 0.25 && mw < 0.25) {
-            const int x0 = static_cast<int>(floor(umin - mu)), x1 = static_cast<int>(floor(umax + mu));
-            const int y0 = static_cast<int>(floor(wmin - mw)), y1 = static_cast<int>(floor(wmax + mw));
-            const int bw = x1 - x0 + 1, bh = y1 - y0 + 1;
-            if (x1 < 0 || x0 >= g.W || y1 < 0 || y0 >= g.H)
-                b.mode = 0;
-            else if (bw <= kSArena && bh <= kSArena && bw * bh <= kSArena)
-                b = SBox{x0, y0, bw, bw * bh, 1};
-        }
-    }
-    boxes[v] = b;
-}
-
-__device__ __forceinline__ SBox read_sbox(const SBox *boxes, int v)
-{
-    SBox b;
-    b.x0 = __builtin_amdgcn_readfirstlane(boxes[v].x0);
-    b.y0 = __builtin_amdgcn_readfirstlane(boxes[v].y0);
-    b.w = __builtin_amdgcn_readfirstlane(boxes[v].w);
-    b.area = __builtin_amdgcn_readfirstlane(boxes[v].area);
-    b.mode = __builtin_amdgcn_readfirstlane(boxes[v].mode);
-    return b;
-}
-
-template <class Views>
-__device__ __forceinline__ void fuse_block(const Views &views, int n, const float *lmap, const GridDesc &a,
-                                           uint32_t bi, uint32_t bj, uint32_t bk, float L0, float tau, float *post,
-                                           uint8_t *occ, float *arena, SBox *boxes)
-{
-    const int t = static_cast<int>(threadIdx.x);
-    const int wave = t >> 6, lane = t & 63;
-    const int i_lo = static_cast<int>(bi) * kSBX, j_lo = static_cast<int>(bj) * kSBY, k_lo = static_cast<int>(bk) * kSBZ;
-    const int i = i_lo + (t % kSBX), j = j_lo + (t / kSBX) % kSBY, k0 = k_lo + kSBKZ * (t / (kSBX * kSBY));
-    block_boxes(views, n, a, i_lo, j_lo, k_lo, boxes);
-    const float X = voxel_centre(a.ox, a.h, i), Y = voxel_centre(a.oy, a.h, j);
-    float Z[kSBKZ], L[kSBKZ];
-#pragma unroll
-    for (int kk = 0; kk < kSBKZ; ++kk) {
-        Z[kk] = voxel_centre(a.oz, a.h, k0 + kk);
-        L[kk] = L0;
-    }
-    __syncthreads();                                // boxes visible
-
-    // Stage every view's box that fits in what is left of the arena, in view
-    // order (each wave derives the same offsets); box entry e = r w + c is
-    // pixel (x0 + c, y0 + r); pixels outside the image get an offset past the
-    // end of the map, which loads 0.
-    int off = 0;
-    for (int v = 0; v < n; ++v) {
-        const SBox b = read_sbox(boxes, v);
-        if (b.mode != 1 || off + b.area > kSArena) continue;
-        const ViewGeom &g = views(v);
-        const uint32_t W = static_cast<uint32_t>(g.W), H = static_cast<uint32_t>(g.H);
-        const __amdgpu_buffer_rsrc_t rs = map_rsrc(lmap + g.map_off, W * H * 4u);
-        const float inv_w = 1.0f / static_cast<float>(b.w);
-        for (int q = wave; q * 64 < b.area; q += kSBThreads / 64) {
-            const int e = q * 64 + lane;
-            if (e < b.area) {
-                // (e + 1/2) / w is at least 1/(2w) from an integer and e < 2^22: exact row
-                const int r = static_cast<int>((static_cast<float>(e) + 0.5f) * inv_w);
-                const int c = e - r * b.w;
-                const uint32_t x = static_cast<uint32_t>(b.x0 + c), y = static_cast<uint32_t>(b.y0 + r);
-                const uint32_t o = (x < W && y < H) ? (__umul24(y, W) + x) * 4u : 0xFFFFFFFFu;
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(arena + off + q * 64),
-                                                         4, o, 0, 0, 0);
-            }
-        }
-        off += b.area;
-    }
-    __syncthreads();                                // every wave's loads have landed
-
-    off = 0;
-    for (int v = 0; v < n; ++v) {
-        const SBox b = read_sbox(boxes, v);
-        if (b.mode == 0) continue;
-        const ViewGeom &g = views(v);
-        const float ax = fmaf(g.P[0], X, fmaf(g.P[1], Y, g.P[3]));
-        const float bx = fmaf(g.P[4], X, fmaf(g.P[5], Y, g.P[7]));
-        const float cx = fmaf(g.P[8], X, fmaf(g.P[9], Y, g.P[11]));
-        if (b.mode == 1 && off + b.area <= kSArena) {
-            // box entry of pixel (x, y): (y - y0) w + (x - x0), exact in FP32
-            // (integers below 2^24); the clamp only keeps the reads in the box
-            const float *sb = arena + off;
-            const float wf = static_cast<float>(b.w);
-            const float od = static_cast<float>(b.y0) * wf + static_cast<float>(b.x0);
-            const float emax = static_cast<float>(b.area - 1);
-#pragma unroll
-            for (int kk = 0; kk < kSBKZ; ++kk) {
-                const float r = __builtin_amdgcn_rcpf(fmaf(g.P[10], Z[kk], cx));
-                const float x = floorf(fmaf(g.P[2], Z[kk], ax) * r);
-                const float y = floorf(fmaf(g.P[6], Z[kk], bx) * r);
-                const float ef = __builtin_amdgcn_fmed3f(fmaf(y, wf, x - od), 0.0f, emax);
-                L[kk] += sb[static_cast<int>(ef)];
-            }
-            off += b.area;
-        } else {
-            const uint32_t W = static_cast<uint32_t>(g.W), H = static_cast<uint32_t>(g.H);
-            const __amdgpu_buffer_rsrc_t rs = map_rsrc(lmap + g.map_off, W * H * 4u);
-            float val[kSBKZ];
-#pragma unroll
-            for (int kk = 0; kk < kSBKZ; ++kk) {
-                const float c = fmaf(g.P[10], Z[kk], cx);
-                const float r = __builtin_amdgcn_rcpf(c);
-                const int x = static_cast<int>(floorf(fmaf(g.P[2], Z[kk], ax) * r));
-                const int y = static_cast<int>(floorf(fmaf(g.P[6], Z[kk], bx) * r));
-                const bool ok = c > 0.0f && static_cast<uint32_t>(x) < W && static_cast<uint32_t>(y) < H;
-                val[kk] = map_load(rs, ok ? (__umul24(static_cast<uint32_t>(y), W) + static_cast<uint32_t>(x)) * 4u
-                                          : 0xFFFFFFFFu);
-            }
-#pragma unroll
-            for (int kk = 0; kk < kSBKZ; ++kk) L[kk] += val[kk];
-        }
-    }
-    if (i >= a.nx || j >= a.ny) return;
-    const int64_t plane = static_cast<int64_t>(a.nx) * a.ny;
-    int64_t idx = (static_cast<int64_t>(k0) * a.ny + j) * a.nx + i;
-#pragma unroll
-    for (int kk = 0; kk < kSBKZ; ++kk, idx += plane) {
-        if (k0 + kk < a.nz) {
-            const float p = sigmoid_fast(L[kk]);
-            post[idx] = p;
-            if (occ) occ[idx] = p > tau ? 1 : 0;
-        }
-    }
-}
-
-template <class T>
-__host__ __device__ int64_t block_count(const T &a)
-{
-    return static_cast<int64_t>((a.nx + kSBX - 1) / kSBX) * ((a.ny + kSBY - 1) / kSBY) * ((a.nz + kSBZ - 1) / kSBZ);
-}
-
 // One-frame nearest fusion, one voxel block per workgroup; the blocks of one
 // XCD form one contiguous octant-ordered range.
 __global__ __launch_bounds__(kSBThreads) void fuse_block_kernel(FuseArgs f)
 {
-    __shared__ float arena[kSArena];
+    __shared__ __align__(16) float arena[kSArena];
     __shared__ SBox boxes[kMaxViews];
     const int64_t nb = block_count(f);
     const uint32_t b = static_cast<uint32_t>(xcd_remap(blockIdx.x, nb));
@@ -429,7 +208,7 @@ __global__ __launch_bounds__(kSBThreads) void fuse_block_kernel(FuseArgs f)
     const uint32_t nbz = static_cast<uint32_t>((f.nz + kSBZ - 1) / kSBZ);
     uint32_t bi, bj, bk;
     octant_tile(b, nbx, nby, nbz, bi, bj, bk);
-    const GridDesc gd{f.nx, f.ny, f.nz, f.ox, f.oy, f.oz, f.h};
+    const GridDesc gd{f.nx, f.ny, f.nz, f.ox, f.oy, f.oz, f.h, f.inside};
     fuse_block([&](int v) -> const ViewGeom & { return f.view[v]; }, f.n, f.lmap, gd, bi, bj, bk, f.L0, f.tau,
                f.post, f.occ, arena, boxes);
 }
@@ -467,7 +246,7 @@ __global__ __launch_bounds__(kSBThreads) void pipe_block_kernel(SlmArgs s, FuseA
         const uint32_t nbz = static_cast<uint32_t>((f.nz + kSBZ - 1) / kSBZ);
         uint32_t bi, bj, bk;
         octant_tile(static_cast<uint32_t>(blk), nbx, nby, nbz, bi, bj, bk);
-        const GridDesc gd{f.nx, f.ny, f.nz, f.ox, f.oy, f.oz, f.h};
+        const GridDesc gd{f.nx, f.ny, f.nz, f.ox, f.oy, f.oz, f.h, f.inside};
         fuse_block([&](int v) -> const ViewGeom & { return f.view[v]; }, f.n, f.lmap, gd, bi, bj, bk, f.L0, f.tau,
                    f.post, f.occ, reinterpret_cast<float *>(lds), boxes);
     }
@@ -525,7 +304,8 @@ __global__ __launch_bounds__(256) void threshold_kernel(const float *post, int64
 // Tile kBlockTile is the kSBX x kSBY x kSBZ voxel block: the one-frame
 // nearest paths fuse it from pixel boxes staged in LDS (fuse_block_kernel),
 // the pipelined bilinear step with 16 x 16 columns of 8 voxels. Bilinear fusion
-// by itself has one kernel for every tile (launch_fuse_bilinear).
+// by itself runs from boxes (launch_fuse_bilinear) or on tile 0's columns,
+// whatever the tile.
 constexpr TileCfg kTiles[] = {
     {8, 32, 4}, {8, 32, 8}, {8, 16, 4}, {8, 32, 2}, {32, 8, 4}, {16, 16, 4}, {kSBX, kSBY, kSBZ},
 };
@@ -623,12 +403,12 @@ hipError_t launch_fuse_nearest(const FuseArgs &a, int tile, hipStream_t s)
                        ((a.nz + c.kz - 1) / c.kz);
     const dim3 grid(static_cast<unsigned>(nb)), block(c.tx * c.ty);
     switch (tile) {
-    case 0: hipLaunchKernelGGL((fuse_kernel<8, 32, 4>), grid, block, 0, s, a); break;
-    case 1: hipLaunchKernelGGL((fuse_kernel<8, 32, 8>), grid, block, 0, s, a); break;
-    case 2: hipLaunchKernelGGL((fuse_kernel<8, 16, 4>), grid, block, 0, s, a); break;
-    case 3: hipLaunchKernelGGL((fuse_kernel<8, 32, 2>), grid, block, 0, s, a); break;
-    case 4: hipLaunchKernelGGL((fuse_kernel<32, 8, 4>), grid, block, 0, s, a); break;
-    case 5: hipLaunchKernelGGL((fuse_kernel<16, 16, 4>), grid, block, 0, s, a); break;
+    case 0: hipLaunchKernelGGL((fuse_kernel<8, 32, 4, PSFS_NEAREST>), grid, block, 0, s, a); break;
+    case 1: hipLaunchKernelGGL((fuse_kernel<8, 32, 8, PSFS_NEAREST>), grid, block, 0, s, a); break;
+    case 2: hipLaunchKernelGGL((fuse_kernel<8, 16, 4, PSFS_NEAREST>), grid, block, 0, s, a); break;
+    case 3: hipLaunchKernelGGL((fuse_kernel<8, 32, 2, PSFS_NEAREST>), grid, block, 0, s, a); break;
+    case 4: hipLaunchKernelGGL((fuse_kernel<32, 8, 4, PSFS_NEAREST>), grid, block, 0, s, a); break;
+    case 5: hipLaunchKernelGGL((fuse_kernel<16, 16, 4, PSFS_NEAREST>), grid, block, 0, s, a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -639,6 +419,7 @@ hipError_t launch_fuse_nearest(const FuseArgs &a, int tile, hipStream_t s)
 int tile_count() { return static_cast<int>(sizeof(kTiles) / sizeof(kTiles[0])); }
 const TileCfg &tile_cfg(int tile) { return kTiles[tile]; }
 int default_tile() { return 0; }
+int block_tile() { return kBlockTile; }
 
 hipError_t launch_slm(const SlmArgs &a, int64_t max_npix, hipStream_t s)
 {
@@ -648,9 +429,14 @@ hipError_t launch_slm(const SlmArgs &a, int64_t max_npix, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_fuse(const FuseArgs &a, int tile, int sampling, hipStream_t s)
+hipError_t launch_fuse(const FuseArgs &a, int tile, int sampling, bool boxes, hipStream_t s)
 {
-    return sampling == PSFS_BILINEAR ? launch_fuse_bilinear(a, s) : launch_fuse_nearest(a, tile, s);
+    if (sampling == PSFS_NEAREST) return launch_fuse_nearest(a, tile, s);
+    if (boxes) return launch_fuse_bilinear(a, s);
+    const int64_t nb = tile_count_of<8, 32, 4>(a);
+    if (nb == 0) return hipSuccess;
+    hipLaunchKernelGGL((fuse_kernel<8, 32, 4, PSFS_BILINEAR>), dim3(static_cast<unsigned>(nb)), dim3(256), 0, s, a);
+    return hipGetLastError();
 }
 
 hipError_t launch_pipeline(const SlmArgs &sa, const FuseArgs &fa, int tile, int sampling, int64_t max_npix,

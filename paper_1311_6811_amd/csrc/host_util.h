@@ -19,6 +19,14 @@ bool finite_all(const float *v, int n);
 int check_device();
 int64_t padded_pixels(int width, int height);
 size_t align256(size_t x);
+// Whether every voxel centre of the grid, and every phantom one of the tiles that
+// reach past its edge, projects into view g (nearest sampling: P pre-offset)
+// with room for the FP32 rounding of its projection.
+bool grid_inside(const ViewGeom &g, const psfs_grid &grid);
+// Whether the block tile is the better one for the one-frame nearest fusion, and
+// boxes staged in LDS for the bilinear fusion.
+bool block_pays(const psfs_camera *cams, int n, const psfs_grid &grid);
+bool bilinear_boxes_pay(const psfs_camera *cams, int n, const psfs_grid &grid);
 
 // Autotuner cache (tune_cache.hip): $PSFS_AUTOTUNE_CACHE, else
 // $HOME/.cache/psfs/autotune.json; callers hold tune_cache_mutex() around

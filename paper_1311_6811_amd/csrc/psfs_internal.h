@@ -55,6 +55,7 @@ struct ViewGeom {
 struct GridDesc {
     int nx, ny, nz;
     float ox, oy, oz, h;                // grid origin (corner) and voxel edge
+    uint32_t inside;                    // bit v: the whole grid is inside view v (grid_inside)
 };
 
 struct FuseArgs {
@@ -66,6 +67,7 @@ struct FuseArgs {
     float ox, oy, oz, h;                // grid origin (corner) and voxel edge
     float L0;                           // logit(prior)
     float tau;                          // threshold on the posterior
+    uint32_t inside;                    // bit v: the whole grid is inside view v (nearest; grid_inside)
 };
 
 // Bilinear fusion from staged pixel boxes: FuseArgs with the camera matrices
@@ -211,9 +213,11 @@ struct TileCfg {
 int tile_count();
 const TileCfg &tile_cfg(int tile);
 int default_tile();
+int block_tile();                       // the tile that fuses from pixel boxes staged in LDS
 
 hipError_t launch_slm(const SlmArgs &a, int64_t max_npix, hipStream_t s);
-hipError_t launch_fuse(const FuseArgs &a, int tile, int sampling, hipStream_t s);
+// boxes: bilinear sampling from pixel boxes staged in LDS (else column by column).
+hipError_t launch_fuse(const FuseArgs &a, int tile, int sampling, bool boxes, hipStream_t s);
 // sa.n == 0: no likelihood part; fa.post == nullptr: no fusion part.
 hipError_t launch_pipeline(const SlmArgs &sa, const FuseArgs &fa, int tile, int sampling, int64_t max_npix,
                            hipStream_t s);
