@@ -750,6 +750,27 @@ __device__ __forceinline__ void fuse_column(const Views &views, int n, const flo
 // pair maps; the four-frame fusion half 4 % faster).
 __device__ __forceinline__ int quad_lane_pos(int l) { return (((l >> 1) & 1) << 5) + 2 * (l >> 2) + (l & 1); }
 
+// A 16-byte store of a piece of an output row at any address. Non-temporal where
+// the rows are made of whole aligned pieces; a line of any other rows is written in
+// parts by several stores, which then have to meet in the L2 (four frames at
+// 150^3 x 8 views: 81 us non-temporal, 74 us plain).
+typedef f32x4 f32x4_floats __attribute__((aligned(4)));
+typedef f32x4 f32x4_bytes __attribute__((aligned(1)));
+__device__ __forceinline__ void store_piece(f32x4 v, float *p, bool aligned)
+{
+    if (aligned)
+        __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(p));
+    else
+        *reinterpret_cast<f32x4_floats *>(p) = v;
+}
+__device__ __forceinline__ void store_piece(f32x4 v, uint8_t *p, bool aligned)
+{
+    if (aligned)
+        __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(p));
+    else
+        *reinterpret_cast<f32x4_bytes *>(p) = v;
+}
+
 // Eq. 3-9 of fuse_column (nearest sampling) for two frames of one rig at
 // once, from pair maps: each voxel-view is projected once and one 8-byte load
 // brings both frames' values; each frame's logit adds its values in view
@@ -793,14 +814,14 @@ __device__ __forceinline__ void fuse_column_pair(const Views &views, int n, cons
             Lb[kk] += val[kk].y;
         }
     }
-    // A wave whose 32 x 2 x 4 voxels all lie in the grid, with rows that start
-    // 16-byte aligned, regroups both frames' outputs through LDS and stores
-    // whole 16-byte pieces of rows non-temporally, as fuse_column_quad does.
-    bool aligned_rows = (a.nx & 15) == 0;
+    // A wave whose 32 x 2 x 4 voxels all lie in the grid regroups both frames'
+    // outputs through LDS and stores 16-byte pieces of rows, as fuse_column_quad
+    // does.
+    bool aligned = (a.nx & 15) == 0;
     for (const void *q : {static_cast<const void *>(post_a), static_cast<const void *>(post_b),
                           static_cast<const void *>(occ_a), static_cast<const void *>(occ_b)})
-        aligned_rows = aligned_rows && (reinterpret_cast<uintptr_t>(q) & 15) == 0;
-    if (aligned_rows && i_lo + 31 < a.nx && j_lo + 1 < a.ny && k0 + KZ - 1 < a.nz) {
+        aligned = aligned && (reinterpret_cast<uintptr_t>(q) & 15) == 0;
+    if (i_lo + 31 < a.nx && j_lo + 1 < a.ny && k0 + KZ - 1 < a.nz) {
         // stage entry (f * KZ + kk) * 64 + pos: voxel (i_lo + pos % 32, j_lo + pos / 32, k0 + kk), frame f
         uint8_t *stage_b = reinterpret_cast<uint8_t *>(wave_stage + 2 * KZ * 64);
 #pragma unroll
@@ -814,20 +835,18 @@ __device__ __forceinline__ void fuse_column_pair(const Views &views, int n, cons
         wave_lds_sync();
         const int r = lane >> 3, c = lane & 7;           // row r = (kk, y) = (r / 2, r % 2), 16-byte piece c
         const int64_t row = (static_cast<int64_t>(k0 + (r >> 1)) * a.ny + j_lo + (r & 1)) * a.nx + i_lo;
-        __builtin_nontemporal_store(*reinterpret_cast<const f32x4 *>(wave_stage + (r >> 1) * 64 + (r & 1) * 32 + 4 * c),
-                                    reinterpret_cast<f32x4 *>(post_a + row + 4 * c));
-        __builtin_nontemporal_store(
-            *reinterpret_cast<const f32x4 *>(wave_stage + (KZ + (r >> 1)) * 64 + (r & 1) * 32 + 4 * c),
-            reinterpret_cast<f32x4 *>(post_b + row + 4 * c));
+        store_piece(*reinterpret_cast<const f32x4 *>(wave_stage + (r >> 1) * 64 + (r & 1) * 32 + 4 * c),
+                    post_a + row + 4 * c, aligned);
+        store_piece(*reinterpret_cast<const f32x4 *>(wave_stage + (KZ + (r >> 1)) * 64 + (r & 1) * 32 + 4 * c),
+                    post_b + row + 4 * c, aligned);
         if (lane < 32) {
             // lane l: frame l / 16, row (l / 2) % 8, half l % 2 of the row's 32 bytes
             const int f = lane >> 4, rr = (lane >> 1) & 7, half = lane & 1;
             const int64_t orow = (static_cast<int64_t>(k0 + (rr >> 1)) * a.ny + j_lo + (rr & 1)) * a.nx + i_lo;
             uint8_t *const dst = f == 0 ? occ_a : occ_b;
             if (dst)
-                __builtin_nontemporal_store(
-                    *reinterpret_cast<const f32x4 *>(stage_b + (f * KZ + (rr >> 1)) * 64 + (rr & 1) * 32 + 16 * half),
-                    reinterpret_cast<f32x4 *>(dst + orow + 16 * half));
+                store_piece(*reinterpret_cast<const f32x4 *>(stage_b + (f * KZ + (rr >> 1)) * 64 + (rr & 1) * 32 + 16 * half),
+                            dst + orow + 16 * half, aligned);
         }
         return;
     }
@@ -893,22 +912,24 @@ __device__ __forceinline__ void fuse_column_quad(const Views &views, int n, cons
             L[kk][3] += val[kk].w;
         }
     }
-    // A wave whose 32 x 2 x KZ voxels all lie in the grid, with rows that
-    // start 16-byte aligned, regroups its outputs through LDS so that each
-    // store instruction writes whole 16-byte pieces of rows (8 rows of 32
-    // posteriors, or 4 frames x 8 rows of 32 occupancy bytes): one cache
-    // access per 64 bytes, where per-voxel stores cost one per 4 lanes. The
-    // stores are non-temporal: the four outputs (20 bytes per voxel) are not
+    // A wave whose 32 x 2 x KZ voxels all lie in the grid regroups its outputs
+    // through LDS so that each store instruction writes 16-byte pieces of rows
+    // (8 rows of 32 posteriors, or 4 frames x 8 rows of 32 occupancy bytes): one
+    // cache access per 64 bytes, one more where four pieces cross a 64-byte
+    // chunk, where per-voxel stores cost one per 4 lanes (rows that are not
+    // 16-byte aligned, per voxel against in pieces: 300^3 x 12 views of 1280x720
+    // 734 -> 696 us, 150^3 x 8 of 640x480 78 -> 74 us). Aligned rows are
+    // stored non-temporally: the four outputs (20 bytes per voxel) are not
     // read again by this launch and would otherwise take the L2 and MALL room
     // of the quad maps the gathers read (at 256^3 x 12 views: 335 MB of
     // outputs against 177 MB of maps per launch, fusion 374 -> 262 us).
     static_assert(TX != 32 || KZ == 4, "the regrouped stores cover 32 x 2 x 4 voxels");
-    bool aligned_rows = TX == 32 && (a.nx & 15) == 0;
+    bool aligned = (a.nx & 15) == 0;
 #pragma unroll
     for (int f = 0; f < 4; ++f)
-        aligned_rows = aligned_rows && (reinterpret_cast<uintptr_t>(post[f]) & 15) == 0 &&
-                       (reinterpret_cast<uintptr_t>(occ[f]) & 15) == 0;
-    if (aligned_rows && i_lo + 31 < a.nx && j_lo + 1 < a.ny && k0 + KZ - 1 < a.nz) {
+        aligned = aligned && (reinterpret_cast<uintptr_t>(post[f]) & 15) == 0 &&
+                  (reinterpret_cast<uintptr_t>(occ[f]) & 15) == 0;
+    if (i_lo + 31 < a.nx && j_lo + 1 < a.ny && k0 + KZ - 1 < a.nz) {
         // stage entry (f * KZ + kk) * 64 + pos: voxel (i_lo + pos % 32, j_lo + pos / 32, k0 + kk), frame f
         uint8_t *stage_b = reinterpret_cast<uint8_t *>(wave_stage);
         uint32_t ob[KZ];
@@ -927,9 +948,8 @@ __device__ __forceinline__ void fuse_column_quad(const Views &views, int n, cons
         const int64_t row = (static_cast<int64_t>(k0 + (r >> 1)) * a.ny + j_lo + (r & 1)) * a.nx + i_lo;
 #pragma unroll
         for (int f = 0; f < 4; ++f)
-            __builtin_nontemporal_store(
-                *reinterpret_cast<const f32x4 *>(wave_stage + (f * KZ + (r >> 1)) * 64 + (r & 1) * 32 + 4 * c),
-                reinterpret_cast<f32x4 *>(post[f] + row + 4 * c));
+            store_piece(*reinterpret_cast<const f32x4 *>(wave_stage + (f * KZ + (r >> 1)) * 64 + (r & 1) * 32 + 4 * c),
+                        post[f] + row + 4 * c, aligned);
         wave_lds_sync();
 #pragma unroll
         for (int kk = 0; kk < KZ; ++kk)
@@ -942,9 +962,8 @@ __device__ __forceinline__ void fuse_column_quad(const Views &views, int n, cons
             const int64_t orow = (static_cast<int64_t>(k0 + (rr >> 1)) * a.ny + j_lo + (rr & 1)) * a.nx + i_lo;
             uint8_t *const dst = f == 0 ? occ[0] : f == 1 ? occ[1] : f == 2 ? occ[2] : occ[3];
             if (dst)
-                __builtin_nontemporal_store(
-                    *reinterpret_cast<const f32x4 *>(stage_b + (f * KZ + (rr >> 1)) * 64 + (rr & 1) * 32 + 16 * half),
-                    reinterpret_cast<f32x4 *>(dst + orow + 16 * half));
+                store_piece(*reinterpret_cast<const f32x4 *>(stage_b + (f * KZ + (rr >> 1)) * 64 + (rr & 1) * 32 + 16 * half),
+                            dst + orow + 16 * half, aligned);
         }
         return;
     }
