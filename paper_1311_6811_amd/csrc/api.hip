@@ -103,7 +103,7 @@ namespace {
 // grid; a large number when a corner is not in front of the camera.
 double block_area(const psfs_camera &c, const psfs_grid &grid)
 {
-    const int dims[3] = {grid.nx, grid.ny, grid.nz}, edge[3] = {dev::kSBX, dev::kSBY, dev::kSBZ};
+    const int dims[3] = {grid.nx, grid.ny, grid.nz}, edge[3] = {16, 16, 8};
     double lo[2] = {0.0, 0.0}, hi[2] = {0.0, 0.0};
     for (int corner = 0; corner < 8; ++corner) {
         double row[3] = {c.P[3], c.P[7], c.P[11]};
@@ -121,6 +121,11 @@ double block_area(const psfs_camera &c, const psfs_grid &grid)
     return std::fmin(1e9, (hi[0] - lo[0] + 4.0) * (hi[1] - lo[1] + 2.0));
 }
 
+int64_t blocks_16x16x8(const psfs_grid &g)
+{
+    return static_cast<int64_t>((g.nx + 15) / 16) * ((g.ny + 15) / 16) * ((g.nz + 7) / 8);
+}
+
 double mean_block_area(const psfs_camera *cams, int n, const psfs_grid &grid)
 {
     double area = 0.0;
@@ -131,23 +136,22 @@ double mean_block_area(const psfs_camera *cams, int n, const psfs_grid &grid)
 }  // namespace
 
 // The block tile's cost per workgroup (boxes, one barrier per group of views) is
-// hidden only where the CUs run several rounds of blocks, sooner with many views
-// (128^3 x 8 views of 640x480, 1024 blocks: column tile 0 18.5 us, block 21.5;
-// 160^3 x 8, 2000 blocks: 33.8 / 31.4; 208^3 x 8, 4394 blocks: 67 / 53; 192^3 x 4 at
-// 520x390: 23.5 / 29.7). It saves the column tile's L1 accesses, which are the more
-// the further apart neighbouring voxels project (192^3 x 7 at 236x177, boxes of 149
-// pixels: 0.88 times the column's speed; at 520x390, 550 pixels: 0.97; 256^3 x 12 at
-// 1280x720, 2100 pixels: 1.4), and more again where the map's rows lie a multiple of 256
-// bytes apart (192^3 x 8: column 51.6 us at a width of 640, 45.3 at 656; the block
-// 46.5 and 44.7). Boxes beyond the arena are gathered (128^3 x 12 at 1280x720, 6800
-// pixels: 34 / 37).
+// hidden only where the CUs run several rounds of workgroups, sooner with many
+// views (fusion with the column tile 0 / the blocks, us: 128^3 x 8 views of 640x480
+// 19.5 / 22, x 16 34.4 / 36.3; 144^3 x 8 28.9 / 24.3 but as a step beside the next
+// frame's likelihood 37.7 / 39.8; 160^3 x 8 33.6 / 27.8 and 42.4 / 42.6; 176^3 x 6 37.7 /
+// 27.8 and 43.2 / 34.7; 256^3 x 1 30.8 / 25.1). It saves the column tile's L1 accesses,
+// which are the more the further apart neighbouring voxels project (192^3 x 7 at
+// 236x177, boxes of 149 pixels 34.4 / 35.3; x 8 at 320x240, 230 pixels 43.6 / 36.9;
+// 256^3 x 8 at 236x177, 129 pixels 78 / 68). Boxes of many pixels leave little room for a
+// group of views, and larger ones than the arena are gathered (160^3 x 12 at
+// 1280x720, 4400 pixels: fusion 59.7 / 50.6, step 108.6 / 116.4).
 bool block_pays(const psfs_camera *cams, int n, const psfs_grid &grid)
 {
-    if (n < 5 || dev::block_count(grid) * (n + 4) < 21000) return false;
-    int strided = 0;
-    for (int k = 0; k < n; ++k) strided += cams[k].width % 64 == 0;
+    const int64_t work = blocks_16x16x8(grid) * (n + 4);
+    if (n == 0 || work < 24000) return false;
     const double area = mean_block_area(cams, n, grid);
-    return area >= (2 * strided > n ? 160.0 : 650.0) && area <= dev::kSArena;
+    return area >= (work < 80000 ? 160.0 : 100.0) && area <= 4000.0;
 }
 
 // The boxes hold every pixel, the gathers of the column kernel only those that
@@ -158,7 +162,7 @@ bool block_pays(const psfs_camera *cams, int n, const psfs_grid &grid)
 bool bilinear_boxes_pay(const psfs_camera *cams, int n, const psfs_grid &grid)
 {
     const double area = mean_block_area(cams, n, grid);
-    return area <= 4200.0 || (area <= 6500.0 && dev::block_count(grid) >= 500);
+    return area <= 4200.0 || (area <= 6500.0 && blocks_16x16x8(grid) >= 500);
 }
 
 // The projection maps the box of the centres into the hull of its 8 projected

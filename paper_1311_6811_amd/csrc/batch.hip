@@ -112,7 +112,7 @@ __global__ __launch_bounds__(kSBThreads) void batch_pipe_block_kernel(BatchArgs 
     const GridDesc &g = fr.grid;
     uint32_t bi, bj, bk;
     octant_tile(static_cast<uint32_t>(tile), static_cast<uint32_t>((g.nx + kSBX - 1) / kSBX),
-                static_cast<uint32_t>((g.ny + kSBY - 1) / kSBY), static_cast<uint32_t>((g.nz + kSBZ - 1) / kSBZ), bi, bj, bk);
+                static_cast<uint32_t>((g.ny + kSBY - 1) / kSBY), static_cast<uint32_t>((g.nz + kSBDepth - 1) / kSBDepth), bi, bj, bk);
     const BatchView *views = a.views + fr.view0;
     fuse_block([&](int v) { return table_entry(&views[v].g); }, fr.n, a.lmap, g, bi, bj, bk, a.L0, a.tau,
                device_ptr(fr.post), device_ptr(fr.occ), reinterpret_cast<float *>(lds), boxes);
@@ -175,10 +175,11 @@ hipError_t launch_fuse_s(const BatchArgs &a, int ff, int64_t tiles, hipStream_t 
 
 int64_t batch_slm_blocks_per_view(int64_t max_npix) { return (max_npix + 4 * kWavePixels - 1) / (4 * kWavePixels); }
 
-int64_t batch_bricks(int nx, int ny, int nz, int tile)
+int64_t batch_bricks(int nx, int ny, int nz, int tile, bool block)
 {
     const TileCfg &c = tile_cfg(tile);
-    return static_cast<int64_t>((nx + c.tx - 1) / c.tx) * ((ny + c.ty - 1) / c.ty) * ((nz + c.kz - 1) / c.kz);
+    const int kz = block ? kSBDepth : c.kz;
+    return static_cast<int64_t>((nx + c.tx - 1) / c.tx) * ((ny + c.ty - 1) / c.ty) * ((nz + kz - 1) / kz);
 }
 
 bool batch_pipelined_tile(int tile) { return tile_cfg(tile).tx * tile_cfg(tile).ty == 256; }

@@ -200,7 +200,7 @@ void build_table(psfs_batch *b)
         b->frames.push_back(fr);
         b->slm_per_view.push_back(batch_slm_blocks_per_view(max_np));
         b->tiles.push_back(nearest && tile == block_tile() && !b->block[f] ? default_tile() : tile);
-        b->fuse_tiles.push_back(batch_bricks(u.grid.nx, u.grid.ny, u.grid.nz, b->tiles.back()));
+        b->fuse_tiles.push_back(batch_bricks(u.grid.nx, u.grid.ny, u.grid.nz, b->tiles.back(), nearest && b->tiles.back() == block_tile()));
     }
     b->map_floats = map_off;
     b->dirty = true;

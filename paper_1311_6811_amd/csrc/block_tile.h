@@ -1,13 +1,14 @@
 // One-frame nearest fusion from pixel boxes staged in LDS, shared by the
 // single-frame kernels (forward.hip) and the batch (batch.hip).
 //
-// A workgroup of kSBThreads lanes fuses a kSBX x kSBY x kSBZ block of voxels, a
-// lane one column of kSBKZ voxels. Per view, the voxel centres of the block
+// A workgroup of kSBThreads lanes fuses kSBStack blocks of kSBX x kSBY x kSBZ
+// voxels, one upon the other, a lane one column of kSBDepth voxels, kSBChunk of
+// them at a time. Per view, the voxel centres of the stack
 // project into the hull of its 8 projected corner centres (the depth is affine
-// and positive at every corner, so on the block the projection is continuous
+// and positive at every corner, so on the stack the projection is continuous
 // and maps the box into that hull); the pixel box around the hull, widened by a
 // bound on the FP32 rounding of the per-voxel projection, holds every pixel a
-// voxel-view of the block reads. The boxes of as many views as fit the arena are
+// voxel-view of the stack reads. The boxes of as many views as fit the arena are
 // copied into LDS at once (direct-to-LDS loads, pixels outside the image as 0)
 // and one barrier waits for the group. Views whose box does not fit the arena,
 // or whose corners are not clearly in front of the camera, are gathered
@@ -18,11 +19,11 @@
 // The column kernels are bound by the L1's accesses (one per 4 lanes and 64-byte
 // chunk, 0.63 per voxel-view: 200 us at 256^3 x 12 views of 1280x720, where a
 // variant without its gathers takes 93); here the L1 serves 16-byte pieces and
-// the scattered reads go to LDS (bank conflicts 35 of 146 us), and what bounds it
-// is the arithmetic. Small workgroups and a small arena (seven per CU, as many as
-// the registers allow) hide each one's waits behind the others: 512 lanes of 4
-// voxels with 32 KB 187 us, 256 lanes of 8 with 32 / 25 / 20 KB 180 / 158 / 157 us,
-// then one common sum for every kind of view 146 us.
+// the scattered reads go to LDS, and what bounds it is the arithmetic and the
+// waits of each group. Two blocks share a workgroup's boxes and row sums: one
+// block 140 us, two 120, three 121 and four 127. Chunks of 4 voxels whose Z is made
+// anew keep the registers (79) and the arena (26 KB) small enough for six
+// workgroups per CU, which hide each one's waits: 115 us (16 voxels at once 143).
 #pragma once
 
 #include "kernels_common.h"
@@ -32,10 +33,12 @@ namespace dev {
 
 constexpr int kSBX = 16, kSBY = 16, kSBZ = 8;
 constexpr int kSBThreads = 256;
-constexpr int kSBKZ = kSBX * kSBY * kSBZ / kSBThreads;
-constexpr int kSArena = 5000;                       // staged floats per workgroup: 20 KB
+constexpr int kSBStack = 2, kSBDepth = kSBStack * kSBZ;
+constexpr int kSBChunk = 4;
+static_assert(kSBDepth % kSBChunk == 0, "whole chunks");
+constexpr int kSArena = 6400;                       // staged floats per workgroup: 26 KB
 static_assert(kSArena % 4 == 0, "whole 16-byte pieces");
-static_assert(kSBKZ * (kSBThreads / (kSBX * kSBY)) == kSBZ, "lanes cover the block");
+static_assert(kSBThreads == kSBX * kSBY, "a lane takes one column of the stack");
 
 struct __align__(16) SBox {
     int x0, y0, w, area;                            // first pixel, row length (pitch) and floats in LDS
@@ -52,14 +55,14 @@ __device__ __forceinline__ float voxel_centre(float o, float h, int i)
     return o + h * (static_cast<float>(i) + 0.5f);
 }
 
-// Pixel boxes of every view for the block with first voxel (i_lo, j_lo, k_lo)
+// Pixel boxes of every view for the stack with first voxel (i_lo, j_lo, k_lo)
 // (phantom voxels past the grid edge included, so that every lane's voxel
 // lies in the hull). Lanes 8v .. 8v+7 of the first two waves take the corners
 // of view v in FP64 from the FP32 centres the voxel lanes use; lane 8v writes
 // boxes[v]. The FP32 evaluation of floor's argument for a voxel (three
 // roundings in each of the numerator and the depth, a reciprocal of 1 ulp and
 // a product) is within 1.8e-7 (S_u + |u| S_c) / c + 1.8e-7 |u| of the exact
-// value, with S the sum of the absolute terms of a row: over the block S is
+// value, with S the sum of the absolute terms of a row: over the stack S is
 // largest and c smallest at a corner. The box is widened by 2^-6 px plus five
 // times that bound.
 template <class Views>
@@ -73,7 +76,7 @@ __device__ __forceinline__ void block_boxes(const Views &views, int n, const Gri
     const ViewGeom &g = views(v);
     const double X = voxel_centre(a.ox, a.h, i_lo + ((corner & 1) ? kSBX - 1 : 0));
     const double Y = voxel_centre(a.oy, a.h, j_lo + ((corner & 2) ? kSBY - 1 : 0));
-    const double Z = voxel_centre(a.oz, a.h, k_lo + ((corner & 4) ? kSBZ - 1 : 0));
+    const double Z = voxel_centre(a.oz, a.h, k_lo + ((corner & 4) ? kSBDepth - 1 : 0));
     double row[3], sum[3];
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
@@ -141,7 +144,7 @@ __device__ __forceinline__ SBox read_sbox(const SBox *boxes, int v)
 // (addresses of whole pixels, 4-byte aligned) or of single pixels; one wave
 // instruction per 64 consecutive ones. A piece or pixel outside the image gets
 // an offset past the end of the map, which loads 0. (Pixel by pixel, the address
-// arithmetic makes the fusion at 256^3 x 12 views 196 us, in pieces 141 us.)
+// arithmetic made the fusion of single blocks at 256^3 x 12 views 196 us, in pieces 141 us.)
 __device__ __forceinline__ void stage_sbox(const ViewGeom &g, const float *lmap, const SBox &b, float *lds)
 {
     const int wave = static_cast<int>(threadIdx.x >> 6), lane = static_cast<int>(threadIdx.x & 63);
@@ -173,16 +176,13 @@ __device__ __forceinline__ void fuse_block(const Views &views, int n, const floa
 {
     const int t = static_cast<int>(threadIdx.x);
     const int wave = t >> 6, lane = t & 63;
-    const int i_lo = static_cast<int>(bi) * kSBX, j_lo = static_cast<int>(bj) * kSBY, k_lo = static_cast<int>(bk) * kSBZ;
-    const int i = i_lo + (t % kSBX), j = j_lo + (t / kSBX) % kSBY, k0 = k_lo + kSBKZ * (t / (kSBX * kSBY));
-    block_boxes(views, n, a, i_lo, j_lo, k_lo, boxes);
+    const int i_lo = static_cast<int>(bi) * kSBX, j_lo = static_cast<int>(bj) * kSBY, k0 = static_cast<int>(bk) * kSBDepth;
+    const int i = i_lo + t % kSBX, j = j_lo + t / kSBX;
+    block_boxes(views, n, a, i_lo, j_lo, k0, boxes);
     const float X = voxel_centre(a.ox, a.h, i), Y = voxel_centre(a.oy, a.h, j);
-    float Z[kSBKZ], L[kSBKZ];
+    float L[kSBDepth];
 #pragma unroll
-    for (int kk = 0; kk < kSBKZ; ++kk) {
-        Z[kk] = voxel_centre(a.oz, a.h, k0 + kk);
-        L[kk] = L0;
-    }
+    for (int kk = 0; kk < kSBDepth; ++kk) L[kk] = L0;
     __syncthreads();                                // boxes visible
 
     // The views are taken in groups whose boxes fit the arena together: their
@@ -206,45 +206,50 @@ __device__ __forceinline__ void fuse_block(const Views &views, int n, const floa
             const float ax = fmaf(g.P[0], X, fmaf(g.P[1], Y, g.P[3]));
             const float bx = fmaf(g.P[4], X, fmaf(g.P[5], Y, g.P[7]));
             const float cx = fmaf(g.P[8], X, fmaf(g.P[9], Y, g.P[11]));
-            float val[kSBKZ];
-            if (b.mode == kDirect) {
-                const __amdgpu_buffer_rsrc_t rs = map_rsrc(lmap + g.map_off, static_cast<uint32_t>(g.W) * static_cast<uint32_t>(g.H) * 4u);
-                uint32_t o[kSBKZ];
-                nearest_offsets<kSBKZ, 4>(g, ax, bx, cx, Z, false, o);
+            const __amdgpu_buffer_rsrc_t rs = map_rsrc(lmap + g.map_off, static_cast<uint32_t>(g.W) * static_cast<uint32_t>(g.H) * 4u);
+            const float wf = static_cast<float>(b.w);
+            const float od = static_cast<float>(b.y0) * wf + static_cast<float>(b.x0);
+            const float emax = static_cast<float>(b.area - 1);
+            const int base = off - (b.y0 * b.w + b.x0);
 #pragma unroll
-                for (int kk = 0; kk < kSBKZ; ++kk) val[kk] = map_load(rs, o[kk]);
-            } else {
-                int e[kSBKZ];
-                if (b.mode == kInside) {
-                    // box entry (y - y0) w + (x - x0), x and y in the image:
-                    // truncation is the floor (a read past the LDS gives 0)
-                    const int base = off - (b.y0 * b.w + b.x0);
+            for (int h = 0; h < kSBDepth; h += kSBChunk) {
+                float Z[kSBChunk], val[kSBChunk];
 #pragma unroll
-                    for (int kk = 0; kk < kSBKZ; ++kk) {
-                        const float r = __builtin_amdgcn_rcpf(fmaf(g.P[10], Z[kk], cx));
-                        const uint32_t x = static_cast<uint32_t>(fmaf(g.P[2], Z[kk], ax) * r);
-                        const uint32_t y = static_cast<uint32_t>(fmaf(g.P[6], Z[kk], bx) * r);
-                        e[kk] = static_cast<int>(__umul24(y, static_cast<uint32_t>(b.w)) + x) + base;
-                    }
+                for (int kk = 0; kk < kSBChunk; ++kk) Z[kk] = voxel_centre(a.oz, a.h, k0 + h + kk);
+                if (b.mode == kDirect) {
+                    uint32_t o[kSBChunk];
+                    nearest_offsets<kSBChunk, 4>(g, ax, bx, cx, Z, false, o);
+#pragma unroll
+                    for (int kk = 0; kk < kSBChunk; ++kk) val[kk] = map_load(rs, o[kk]);
                 } else {
-                    // exact in FP32 (integers below 2^24); the clamp keeps a read in the box
-                    const float wf = static_cast<float>(b.w);
-                    const float od = static_cast<float>(b.y0) * wf + static_cast<float>(b.x0);
-                    const float emax = static_cast<float>(b.area - 1);
+                    int e[kSBChunk];
+                    if (b.mode == kInside) {
+                        // box entry (y - y0) w + (x - x0), x and y in the image:
+                        // truncation is the floor (a read past the LDS gives 0)
 #pragma unroll
-                    for (int kk = 0; kk < kSBKZ; ++kk) {
-                        const float r = __builtin_amdgcn_rcpf(fmaf(g.P[10], Z[kk], cx));
-                        const float x = floorf(fmaf(g.P[2], Z[kk], ax) * r);
-                        const float y = floorf(fmaf(g.P[6], Z[kk], bx) * r);
-                        e[kk] = off + static_cast<int>(__builtin_amdgcn_fmed3f(fmaf(y, wf, x - od), 0.0f, emax));
+                        for (int kk = 0; kk < kSBChunk; ++kk) {
+                            const float r = __builtin_amdgcn_rcpf(fmaf(g.P[10], Z[kk], cx));
+                            const uint32_t x = static_cast<uint32_t>(fmaf(g.P[2], Z[kk], ax) * r);
+                            const uint32_t y = static_cast<uint32_t>(fmaf(g.P[6], Z[kk], bx) * r);
+                            e[kk] = static_cast<int>(__umul24(y, static_cast<uint32_t>(b.w)) + x) + base;
+                        }
+                    } else {
+                        // exact in FP32 (integers below 2^24); the clamp keeps a read in the box
+#pragma unroll
+                        for (int kk = 0; kk < kSBChunk; ++kk) {
+                            const float r = __builtin_amdgcn_rcpf(fmaf(g.P[10], Z[kk], cx));
+                            const float x = floorf(fmaf(g.P[2], Z[kk], ax) * r);
+                            const float y = floorf(fmaf(g.P[6], Z[kk], bx) * r);
+                            e[kk] = off + static_cast<int>(__builtin_amdgcn_fmed3f(fmaf(y, wf, x - od), 0.0f, emax));
+                        }
                     }
+#pragma unroll
+                    for (int kk = 0; kk < kSBChunk; ++kk) val[kk] = arena[e[kk]];
                 }
 #pragma unroll
-                for (int kk = 0; kk < kSBKZ; ++kk) val[kk] = arena[e[kk]];
-                off += (b.area + 3) & ~3;
+                for (int kk = 0; kk < kSBChunk; ++kk) L[h + kk] += val[kk];
             }
-#pragma unroll
-            for (int kk = 0; kk < kSBKZ; ++kk) L[kk] += val[kk];
+            if (b.mode != kDirect) off += (b.area + 3) & ~3;
         }
         v0 = v1;
         if (v0 < n) __syncthreads();                // the group's reads are done
@@ -253,7 +258,7 @@ __device__ __forceinline__ void fuse_block(const Views &views, int n, const floa
     const int64_t plane = static_cast<int64_t>(a.nx) * a.ny;
     int64_t idx = (static_cast<int64_t>(k0) * a.ny + j) * a.nx + i;
 #pragma unroll
-    for (int kk = 0; kk < kSBKZ; ++kk, idx += plane) {
+    for (int kk = 0; kk < kSBDepth; ++kk, idx += plane) {
         if (k0 + kk < a.nz) {
             const float p = sigmoid_fast(L[kk]);
             post[idx] = p;
@@ -265,7 +270,7 @@ __device__ __forceinline__ void fuse_block(const Views &views, int n, const floa
 template <class T>
 __host__ __device__ int64_t block_count(const T &a)
 {
-    return static_cast<int64_t>((a.nx + kSBX - 1) / kSBX) * ((a.ny + kSBY - 1) / kSBY) * ((a.nz + kSBZ - 1) / kSBZ);
+    return static_cast<int64_t>((a.nx + kSBX - 1) / kSBX) * ((a.ny + kSBY - 1) / kSBY) * ((a.nz + kSBDepth - 1) / kSBDepth);
 }
 
 }  // namespace dev

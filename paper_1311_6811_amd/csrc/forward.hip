@@ -205,7 +205,7 @@ __global__ __launch_bounds__(kSBThreads) void fuse_block_kernel(FuseArgs f)
     const int64_t nb = block_count(f);
     const uint32_t b = static_cast<uint32_t>(xcd_remap(blockIdx.x, nb));
     const uint32_t nbx = static_cast<uint32_t>((f.nx + kSBX - 1) / kSBX), nby = static_cast<uint32_t>((f.ny + kSBY - 1) / kSBY);
-    const uint32_t nbz = static_cast<uint32_t>((f.nz + kSBZ - 1) / kSBZ);
+    const uint32_t nbz = static_cast<uint32_t>((f.nz + kSBDepth - 1) / kSBDepth);
     uint32_t bi, bj, bk;
     octant_tile(b, nbx, nby, nbz, bi, bj, bk);
     const GridDesc gd{f.nx, f.ny, f.nz, f.ox, f.oy, f.oz, f.h, f.inside};
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(kSBThreads) void pipe_block_kernel(SlmArgs s, FuseA
         const int64_t blk = static_cast<int64_t>(x) * p.fuse_rounds + (round - p.slm_rounds);
         if (blk >= p.fuse_tiles) return;
         const uint32_t nbx = static_cast<uint32_t>((f.nx + kSBX - 1) / kSBX), nby = static_cast<uint32_t>((f.ny + kSBY - 1) / kSBY);
-        const uint32_t nbz = static_cast<uint32_t>((f.nz + kSBZ - 1) / kSBZ);
+        const uint32_t nbz = static_cast<uint32_t>((f.nz + kSBDepth - 1) / kSBDepth);
         uint32_t bi, bj, bk;
         octant_tile(static_cast<uint32_t>(blk), nbx, nby, nbz, bi, bj, bk);
         const GridDesc gd{f.nx, f.ny, f.nz, f.ox, f.oy, f.oz, f.h, f.inside};

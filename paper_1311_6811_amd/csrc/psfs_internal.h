@@ -243,7 +243,7 @@ hipError_t launch_diff_backward(const DiffArgs &a, const ChainArgs &c, int64_t m
 // likelihood of table frame fl beside the fusion of table frame ff, either
 // of them -1 for none).
 int64_t batch_slm_blocks_per_view(int64_t max_npix);
-int64_t batch_bricks(int nx, int ny, int nz, int tile);
+int64_t batch_bricks(int nx, int ny, int nz, int tile, bool block);
 bool batch_pipelined_tile(int tile);
 hipError_t launch_batch_step(const BatchArgs &a, int tile, int sampling, int fl, int64_t slm_per_view, int nviews_l,
                              int ff, int64_t fuse_tiles, hipStream_t s);

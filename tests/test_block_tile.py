@@ -91,3 +91,17 @@ def test_batch_with_block_frames_and_an_update():
                 plan.set_tile(0)
                 post, occ = plan.reconstruct(f.images)
                 assert torch.equal(post, f.posterior) and torch.equal(occ, f.occ)
+
+
+@pytest.mark.parametrize("nz", [1, 3, 4, 5, 8, 12, 15, 16, 17, 31, 33])
+def test_depths_that_do_not_fill_a_stack(nz):
+    plan = psfs.Plan(_rig("ring", 6, 332, 250), _Grid(33, 18, nz, 2.0))
+    lmap = _maps(plan, nz)
+    plan.set_tile(0)
+    ref, ref_occ = plan.fuse(lmap)
+    plan.set_tile(BLOCK)
+    post, occ = torch.full_like(ref, -1.0), torch.full_like(ref_occ, 7)
+    plan.pipeline_step(None, None, lmap, post, occ)
+    assert torch.equal(post, ref) and torch.equal(occ, ref_occ)
+    post, occ = plan.fuse(lmap)
+    assert torch.equal(post, ref) and torch.equal(occ, ref_occ)
