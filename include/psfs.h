@@ -494,8 +494,10 @@ int psfs_batch_tune(psfs_batch *batch, void *workspace_dev, size_t workspace_byt
  * tile = index into the library's fusion tile table (see psfs_tile_count),
  * or -1 for the tuned/default choice. A tile is a workgroup of tx x ty voxel
  * columns of kz voxels each. On the 16 x 16 x 8 tile the one-frame nearest
- * paths of a plan stage each block's per-view pixel boxes in LDS and read
- * them there; every other tile and path gathers from the maps directly. */
+ * paths of a plan or a batch take two such blocks per workgroup, stage their
+ * per-view pixel boxes in LDS and read them there; the other tiles gather from
+ * the maps directly. The default is tile 0 or, where the grid and the rig make
+ * it the faster way, the 16 x 16 x 8 tile. */
 int psfs_tile_count(void);
 int psfs_tile_describe(int tile, int32_t *tx, int32_t *ty, int32_t *kz);
 /* Fusion tile of a plan's one-frame paths (psfs_fuse, psfs_reconstruct,

@@ -196,8 +196,8 @@ __global__ __launch_bounds__(TX * TY) void pipe_quad_kernel(SlmArgs s, QuadImage
     }
 }
 
-// One-frame nearest fusion, one voxel block per workgroup; the blocks of one
-// XCD form one contiguous octant-ordered range.
+// One-frame nearest fusion, one stack of voxel blocks per workgroup; the stacks of
+// one XCD form one contiguous octant-ordered range.
 __global__ __launch_bounds__(kSBThreads) void fuse_block_kernel(FuseArgs f)
 {
     __shared__ __align__(16) float arena[kSArena];
@@ -216,9 +216,9 @@ __global__ __launch_bounds__(kSBThreads) void fuse_block_kernel(FuseArgs f)
 // Likelihood maps of the next frame and block-staged fusion of the current
 // one in one launch, laid out as pipe_kernel with kSBThreads-lane workgroups:
 // likelihood rounds first (kSBThreads / 64 waves of kWavePixels pixels per
-// workgroup), then fusion rounds (one voxel block each; the blocks of one XCD
+// workgroup), then fusion rounds (one stack of blocks each; the stacks of one XCD
 // form one contiguous octant-ordered range). The two roles share one LDS
-// allocation, so both run four workgroups (32 waves) per CU.
+// allocation, so both run six workgroups (24 waves) per CU.
 __global__ __launch_bounds__(kSBThreads) void pipe_block_kernel(SlmArgs s, FuseArgs f, PipeArgs p)
 {
     constexpr size_t kStageBytes = (kSBThreads / 64) * sizeof(SlmStage);
@@ -302,7 +302,7 @@ __global__ __launch_bounds__(256) void threshold_kernel(const float *post, int64
 }
 
 // Tile kBlockTile is the kSBX x kSBY x kSBZ voxel block: the one-frame
-// nearest paths fuse it from pixel boxes staged in LDS (fuse_block_kernel),
+// nearest paths fuse it, kSBStack to a workgroup, from pixel boxes staged in LDS,
 // the pipelined bilinear step with 16 x 16 columns of 8 voxels. Bilinear fusion
 // by itself runs from boxes (launch_fuse_bilinear) or on tile 0's columns,
 // whatever the tile.
