@@ -136,22 +136,24 @@ double mean_block_area(const psfs_camera *cams, int n, const psfs_grid &grid)
 }  // namespace
 
 // The block tile's cost per workgroup (boxes, one barrier per group of views) is
-// hidden only where the CUs run several rounds of workgroups, sooner with many
-// views (fusion with the column tile 0 / the blocks, us: 128^3 x 8 views of 640x480
-// 19.5 / 22, x 16 34.4 / 36.3; 144^3 x 8 28.9 / 24.3 but as a step beside the next
-// frame's likelihood 37.7 / 39.8; 160^3 x 8 33.6 / 27.8 and 42.4 / 42.6; 176^3 x 6 37.7 /
-// 27.8 and 43.2 / 34.7; 256^3 x 1 30.8 / 25.1). It saves the column tile's L1 accesses,
-// which are the more the further apart neighbouring voxels project (192^3 x 7 at
-// 236x177, boxes of 149 pixels 34.4 / 35.3; x 8 at 320x240, 230 pixels 43.6 / 36.9;
-// 256^3 x 8 at 236x177, 129 pixels 78 / 68). Boxes of many pixels leave little room for a
-// group of views, and larger ones than the arena are gathered (160^3 x 12 at
-// 1280x720, 4400 pixels: fusion 59.7 / 50.6, step 108.6 / 116.4).
-bool block_pays(const psfs_camera *cams, int n, const psfs_grid &grid)
+// hidden only where the CUs run enough workgroups, and behind a step's likelihood
+// rounds only where they run several rounds of them. Column tile 0 / blocks, us:
+// fusion alone 128^3 x 8 views of 640x480 19.5 / 22, 144^3 x 8 28.9 / 24.3, 160^3 x 8 33.6 /
+// 27.8; as a step 144^3 x 8 37.7 / 39.8, 160^3 x 8 42.4 / 42.6, 176^3 x 6 43.2 / 34.7.
+// What it saves are the column tile's L1 accesses, the more the further apart
+// neighbouring voxels project, with each view: 192^3 x 7 at 236x177 (boxes of 149
+// pixels) 34.4 / 35.3, x 8 at 320x240 (230) 43.6 / 36.9; 256^3 x 8 at 236x177 (129) 78 /
+// 68, x 1 at 643x477 (266) 30.8 / 25.1; 192^3 x 4 at 643x477 (434) 24.8 / 25.6; 144^3 x 4
+// (724) 14.9 / 15.2, x 6 (953) 23.1 / 19.6. Boxes of many pixels leave little room for a
+// group of views, and larger ones than the arena are gathered: 160^3 x 12 at 1280x720
+// (4400 pixels) fusion 59.7 / 50.6, step 108.6 / 116.4.
+bool block_pays(const psfs_camera *cams, int n, const psfs_grid &grid, bool step)
 {
-    const int64_t work = blocks_16x16x8(grid) * (n + 4);
-    if (n == 0 || work < 24000) return false;
+    const int64_t blocks = blocks_16x16x8(grid), work = blocks * (n + 4);
+    if (n == 0 || blocks < (step ? 2400 : 1400)) return false;
     const double area = mean_block_area(cams, n, grid);
-    return area >= (work < 80000 ? 160.0 : 100.0) && area <= 4000.0;
+    return static_cast<double>(work) * std::fmin(area, 1000.0) >= (work < 30000 ? 13e6 : 8e6) &&
+           area <= (step ? 4000.0 : 5000.0);
 }
 
 // The boxes hold every pixel, the gathers of the column kernel only those that
@@ -365,11 +367,12 @@ void fill_geometry(const psfs_plan *p, int sampling, FuseArgs &a)
     a.tau = p->params.threshold;
 }
 
-// The plan's tile, or the better one for its grid and rig when none was set.
-int launch_tile(const psfs_plan *p)
+// The plan's tile, or the better one for its grid and rig when none was set
+// (step: the fusion runs beside a frame's likelihood).
+int launch_tile(const psfs_plan *p, bool step)
 {
     if (p->tile >= 0) return p->tile;
-    return p->params.sampling == PSFS_NEAREST && block_pays(p->cams, p->n, p->grid) ? block_tile() : default_tile();
+    return p->params.sampling == PSFS_NEAREST && block_pays(p->cams, p->n, p->grid, step) ? block_tile() : default_tile();
 }
 
 int enqueue_fuse(const psfs_plan *p, const float *lmap, float *post, uint8_t *occ, hipStream_t s)
@@ -383,7 +386,7 @@ int enqueue_fuse(const psfs_plan *p, const float *lmap, float *post, uint8_t *oc
     a.post = post;
     a.occ = occ;
     const bool boxes = p->params.sampling == PSFS_BILINEAR && bilinear_boxes_pay(p->cams, p->n, p->grid);
-    hipError_t e = launch_fuse(a, launch_tile(p), p->params.sampling, boxes, s);
+    hipError_t e = launch_fuse(a, launch_tile(p, false), p->params.sampling, boxes, s);
     if (e != hipSuccess) return hip_fail(e, "fusion kernel launch");
     return PSFS_OK;
 }
@@ -758,7 +761,7 @@ int psfs_pipeline_step(psfs_plan *plan, const uint8_t *const *images_dev, float 
     fa.occ = fa.post ? occ_dev : nullptr;
     if (sa.n == 0 && !fa.post) return PSFS_OK;
     if ((rc = check_device())) return rc;
-    hipError_t e = launch_pipeline(sa, fa, launch_tile(plan), plan->params.sampling, max_np, static_cast<hipStream_t>(stream));
+    hipError_t e = launch_pipeline(sa, fa, launch_tile(plan, true), plan->params.sampling, max_np, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(e, "pipelined kernel launch");
     return PSFS_OK;
     PSFS_GUARD_END

@@ -349,7 +349,7 @@ int psfs_batch_create(psfs_batch **out, const psfs_params *params, int nframes, 
     take_frames(b, nframes, frames);
     chain_order(frames, nframes, b->order);
     b->tile = default_tile();
-    for (int f = 0; f < nframes; ++f) b->block.push_back(block_pays(frames[f].cams, frames[f].n, frames[f].grid));
+    for (int f = 0; f < nframes; ++f) b->block.push_back(block_pays(frames[f].cams, frames[f].n, frames[f].grid, true));
     build_table(b);
     b->dtable_bytes = align256(b->views.size() * sizeof(BatchView)) + align256(b->frames.size() * sizeof(BatchFrame));
     e = hipMalloc(&b->dtable, b->dtable_bytes);

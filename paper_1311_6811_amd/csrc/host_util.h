@@ -25,7 +25,7 @@ size_t align256(size_t x);
 bool grid_inside(const ViewGeom &g, const psfs_grid &grid);
 // Whether the block tile is the better one for the one-frame nearest fusion, and
 // boxes staged in LDS for the bilinear fusion.
-bool block_pays(const psfs_camera *cams, int n, const psfs_grid &grid);
+bool block_pays(const psfs_camera *cams, int n, const psfs_grid &grid, bool step);
 bool bilinear_boxes_pay(const psfs_camera *cams, int n, const psfs_grid &grid);
 
 // Autotuner cache (tune_cache.hip): $PSFS_AUTOTUNE_CACHE, else
