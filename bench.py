@@ -57,7 +57,7 @@ PAPER_CONTEXT = {"scope": "whole pipeline per frame (reconstruction + colour + t
 # are taken again.
 PIPE_COUNTER_SOURCES = ("paper_1311_6811_amd/csrc/forward.hip", "paper_1311_6811_amd/csrc/kernels_common.h",
                         "paper_1311_6811_amd/csrc/psfs_internal.h")
-PIPE_COUNTERS = {"sources_sha256": "0d5f163b56d0c23d43694339a3606ab2e9ece69e0c845808ffb22ef61f39f4b1",
+PIPE_COUNTERS = {"sources_sha256": "95d079bddedbe517c81e53b0e858043a209ef2465701b92068df4fe5d77d581a",
                  "fetch_kib": 59464.4, "fetch_scale": 2.0, "write_kib": 80982.1, "write_scale": 1.0,
                  "l2_hit_rate": 0.661}
 

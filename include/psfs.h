@@ -496,8 +496,7 @@ int psfs_batch_tune(psfs_batch *batch, void *workspace_dev, size_t workspace_byt
  * columns of kz voxels each. On the 16 x 16 x 8 tile the one-frame nearest
  * paths of a plan or a batch take two such blocks per workgroup, stage their
  * per-view pixel boxes in LDS and read them there; the other tiles gather from
- * the maps directly. The default is tile 0 or, where the grid and the rig make
- * it the faster way, the 16 x 16 x 8 tile. */
+ * the maps directly. The default follows the grid and the rig. */
 int psfs_tile_count(void);
 int psfs_tile_describe(int tile, int32_t *tx, int32_t *ty, int32_t *kz);
 /* Fusion tile of a plan's one-frame paths (psfs_fuse, psfs_reconstruct,

@@ -68,7 +68,7 @@ __global__ __launch_bounds__(TX * TY) void fuse_kernel(FuseArgs a)
 // current frame (Eq. 3-9, FuseArgs, maps written by an earlier launch) in one
 // launch; the two parts share no data. Workgroups come in rounds of kNumXcd
 // consecutive ones, which the dispatcher places one per XCD: first the
-// likelihood rounds (kNumXcd workgroups of 4 x kWavePixels pixels each), then
+// likelihood rounds (kNumXcd workgroups of kWavePixels pixels per wave), then
 // the fusion rounds (kNumXcd tiles each). The likelihood workgroups are short
 // and HBM-bound; fusion tiles take the slots they free while the stream is
 // still running, so the gather- and arithmetic-bound fusion overlaps the
@@ -78,8 +78,8 @@ __global__ __launch_bounds__(TX * TY) void fuse_kernel(FuseArgs a)
 template <int TX, int TY, int KZ, int SAMPLING>
 __global__ __launch_bounds__(TX * TY) void pipe_kernel(SlmArgs s, FuseArgs f, PipeArgs p)
 {
-    static_assert(TX * TY == 256, "four waves per workgroup");
-    __shared__ SlmStage stage[4];
+    constexpr int kWaves = TX * TY / 64;
+    __shared__ SlmStage stage[kWaves];
     const int round = static_cast<int>(blockIdx.x) / kNumXcd, x = static_cast<int>(blockIdx.x) % kNumXcd;
     if (round < p.slm_rounds) {
         const int sr = round;
@@ -88,7 +88,7 @@ __global__ __launch_bounds__(TX * TY) void pipe_kernel(SlmArgs s, FuseArgs f, Pi
         const int v = sb / p.slm_per_view;
         const SlmView &sv = s.view[v];
         const int wave = static_cast<int>(threadIdx.x >> 6);
-        const int64_t p0 = (static_cast<int64_t>(sb - v * p.slm_per_view) * 4 + wave) * kWavePixels;
+        const int64_t p0 = (static_cast<int64_t>(sb - v * p.slm_per_view) * kWaves + wave) * kWavePixels;
         float *out = s.lmap + sv.map_off;
         if (p0 + kWavePixels <= sv.npix)
             slm_wave(sv.img, sv.mean, sv.var, out, p0, s.k0, stage[wave], s.fg, InputCheck{s.check, 1u << v});
@@ -327,7 +327,8 @@ template <int TX, int TY, int KZ, int S>
 hipError_t launch_pipe_t(const SlmArgs &sa, const FuseArgs &fa, int64_t max_npix, hipStream_t s)
 {
     PipeArgs p{};
-    const int64_t per_view = sa.n > 0 ? (max_npix + 4 * kWavePixels - 1) / (4 * kWavePixels) : 0;
+    constexpr int64_t kPixels = TX * TY / 64 * kWavePixels;         // of a likelihood workgroup
+    const int64_t per_view = sa.n > 0 ? (max_npix + kPixels - 1) / kPixels : 0;
     const int64_t slm_blocks = per_view * sa.n;
     const int64_t tiles = fa.post ? tile_count_of<TX, TY, KZ>(fa) : 0;
     p.slm_per_view = static_cast<int32_t>(per_view);
@@ -360,10 +361,11 @@ hipError_t launch_pipe_s(const SlmArgs &sa, const FuseArgs &fa, int tile, int64_
     switch (tile) {
     case 6: return launch_pipe_t<16, 16, 8, S>(sa, fa, max_npix, s);
     case 1: return launch_pipe_t<8, 32, 8, S>(sa, fa, max_npix, s);
+    case 2: return launch_pipe_t<8, 16, 4, S>(sa, fa, max_npix, s);
     case 3: return launch_pipe_t<8, 32, 2, S>(sa, fa, max_npix, s);
     case 4: return launch_pipe_t<32, 8, 4, S>(sa, fa, max_npix, s);
     case 5: return launch_pipe_t<16, 16, 4, S>(sa, fa, max_npix, s);
-    default: return launch_pipe_t<8, 32, 4, S>(sa, fa, max_npix, s);    // tile 0; tile 2 has 128 lanes
+    default: return launch_pipe_t<8, 32, 4, S>(sa, fa, max_npix, s);
     }
 }
 
