@@ -175,7 +175,6 @@ __device__ __forceinline__ void fuse_block(const Views &views, int n, const floa
                                            uint8_t *occ, float *arena, SBox *boxes)
 {
     const int t = static_cast<int>(threadIdx.x);
-    const int wave = t >> 6, lane = t & 63;
     const int i_lo = static_cast<int>(bi) * kSBX, j_lo = static_cast<int>(bj) * kSBY, k0 = static_cast<int>(bk) * kSBDepth;
     const int i = i_lo + t % kSBX, j = j_lo + t / kSBX;
     block_boxes(views, n, a, i_lo, j_lo, k0, boxes);
