@@ -379,7 +379,8 @@ void fill_geometry(const psfs_plan *p, int sampling, FuseArgs &a)
 // (step: the fusion runs beside a frame's likelihood). Of the column tiles the
 // 128-lane one pads ragged grids the least and leaves the shortest last round:
 // over 90 shapes 1.08 times as fast as tile 0 in fusions (80^3 x 8 views 9.4 / 7.0 us,
-// 112^3 x 8 17.3 / 14.5, 256^3 x 12 201 / 199.5), 1.04 times in steps (0.97 to 1.12).
+// 112^3 x 8 17.3 / 14.5, 256^3 x 12 201 / 199.5), 1.04 times in steps (0.97 to 1.12;
+// 128^3 x 8, which neither pads, 27.9 / 28.4).
 // Grids that give the CUs two of its workgroups at most take half as many voxels
 // per lane (64^3 x 12: 6.7 / 5.8 us; 80^3 x 8: 7.0 / 8.5).
 int launch_tile(const psfs_plan *p, bool step)
