@@ -57,7 +57,7 @@ PAPER_CONTEXT = {"scope": "whole pipeline per frame (reconstruction + colour + t
 # are taken again.
 PIPE_COUNTER_SOURCES = ("paper_1311_6811_amd/csrc/forward.hip", "paper_1311_6811_amd/csrc/kernels_common.h",
                         "paper_1311_6811_amd/csrc/psfs_internal.h")
-PIPE_COUNTERS = {"sources_sha256": "95d079bddedbe517c81e53b0e858043a209ef2465701b92068df4fe5d77d581a",
+PIPE_COUNTERS = {"sources_sha256": "d4b94cad256f646eeaa2937b2924788f03b2e28f5e5fee503ed1221c30087e8b",
                  "fetch_kib": 59464.4, "fetch_scale": 2.0, "write_kib": 80982.1, "write_scale": 1.0,
                  "l2_hit_rate": 0.661}
 

@@ -257,15 +257,16 @@ __global__ __launch_bounds__(kSBThreads) void pipe_block_kernel(SlmArgs s, FuseA
 // this pass's outputs. Bound by the FP64 projection's instructions. The column
 // kernels gather four taps of every voxel-view from the map, four loads with a
 // bounds test each: 61 us at 128^3 x 8 views of 640x480, 515 us at 224^3 x 12
-// of 1280x720; here 32 and 206 us. The arena of 7500 floats (30 KB) leaves room
-// for five workgroups per CU, as many as the registers allow: 8192 floats (four
-// workgroups) 32 and 219 us, 6000 floats (fewer views per barrier) 34 and 204 us.
+// of 1280x720; here 30 and 166 us. The arena of 7500 floats (30 KB) leaves room
+// for five workgroups per CU, as many as the registers allow (with boxes staged
+// pixel by pixel 32 and 206 us; 8192 floats, four workgroups, 32 and 219 us; 6000
+// floats, fewer views per barrier, 34 and 204 us).
 constexpr int kBilArena = 7500;
 
 template <int KZ>
 __global__ __launch_bounds__(kBoxThreads) void fuse_bilinear_kernel(BilinearArgs a)
 {
-    __shared__ float arena[kBilArena];
+    __shared__ __align__(16) float arena[kBilArena];
     __shared__ PixBox boxes[kMaxViews];
     const uint32_t nbx = static_cast<uint32_t>((a.nx + 15) / 16), nby = static_cast<uint32_t>((a.ny + 15) / 16);
     const uint32_t nbz = static_cast<uint32_t>((a.nz + KZ - 1) / KZ);
@@ -273,7 +274,7 @@ __global__ __launch_bounds__(kBoxThreads) void fuse_bilinear_kernel(BilinearArgs
     uint32_t bi, bj, bk;
     octant_tile(static_cast<uint32_t>(xcd_remap(blockIdx.x, nb)), nbx, nby, nbz, bi, bj, bk);
     const int i0 = static_cast<int>(bi) * 16, j0 = static_cast<int>(bj) * 16, k0 = static_cast<int>(bk) * KZ;
-    compute_boxes<16, 16, KZ>(a, i0, j0, k0, kBilArena, boxes);
+    compute_boxes<16, 16, KZ>(a, i0, j0, k0, kBilArena, true, boxes);
     const int i = i0 + static_cast<int>(threadIdx.x % 16), j = j0 + static_cast<int>(threadIdx.x / 16);
     const double Xd = centre64(a.ox, a.h, i), Yd = centre64(a.oy, a.h, j);
     float L[KZ];
