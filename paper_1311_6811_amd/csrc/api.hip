@@ -126,14 +126,6 @@ int64_t blocks_16x16x8(const psfs_grid &g)
     return static_cast<int64_t>((g.nx + 15) / 16) * ((g.ny + 15) / 16) * ((g.nz + 7) / 8);
 }
 
-constexpr int kNarrowTile = 2, kShallowTile = 3;    // 8 x 16 columns of 4 voxels, 8 x 32 of 2
-
-int64_t tile_workgroups(int tile, const psfs_grid &g)
-{
-    const TileCfg &c = tile_cfg(tile);
-    return static_cast<int64_t>((g.nx + c.tx - 1) / c.tx) * ((g.ny + c.ty - 1) / c.ty) * ((g.nz + c.kz - 1) / c.kz);
-}
-
 double mean_block_area(const psfs_camera *cams, int n, const psfs_grid &grid)
 {
     double area = 0.0;
@@ -162,6 +154,12 @@ bool block_pays(const psfs_camera *cams, int n, const psfs_grid &grid, bool step
     const double area = mean_block_area(cams, n, grid);
     return static_cast<double>(work) * std::fmin(area, 1000.0) >= (work < 30000 ? 13e6 : 8e6) &&
            area <= (step ? 4000.0 : 5000.0);
+}
+
+// Grids of few workgroups, where half as many voxels per lane are the faster way.
+bool small_grid(const psfs_grid &grid)
+{
+    return batch_bricks(grid.nx, grid.ny, grid.nz, kNarrowTile, false) <= 512;
 }
 
 // The boxes hold every pixel, the gathers of the column kernel only those that
@@ -388,7 +386,7 @@ int launch_tile(const psfs_plan *p, bool step)
     if (p->tile >= 0) return p->tile;
     if (p->params.sampling != PSFS_NEAREST) return default_tile();
     if (block_pays(p->cams, p->n, p->grid, step)) return block_tile();
-    return tile_workgroups(kNarrowTile, p->grid) <= 512 ? kShallowTile : kNarrowTile;
+    return small_grid(p->grid) ? kShallowTile : kNarrowTile;
 }
 
 int enqueue_fuse(const psfs_plan *p, const float *lmap, float *post, uint8_t *occ, hipStream_t s)

@@ -199,7 +199,10 @@ void build_table(psfs_batch *b)
         }
         b->frames.push_back(fr);
         b->slm_per_view.push_back(batch_slm_blocks_per_view(max_np));
-        b->tiles.push_back(nearest && tile == block_tile() && !b->block[f] ? default_tile() : tile);
+        // (column steps of larger grids stay on tile 0: the narrow tile's two-wave likelihood
+        // workgroups, each with its own reads of the table, made 24 frames 946 -> 956 us)
+        const int column = small_grid(u.grid) ? kShallowTile : default_tile();
+        b->tiles.push_back(nearest && tile == block_tile() && !b->block[f] ? column : tile);
         b->fuse_tiles.push_back(batch_bricks(u.grid.nx, u.grid.ny, u.grid.nz, b->tiles.back(), nearest && b->tiles.back() == block_tile()));
     }
     b->map_floats = map_off;

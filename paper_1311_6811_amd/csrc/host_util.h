@@ -26,6 +26,8 @@ bool grid_inside(const ViewGeom &g, const psfs_grid &grid);
 // Whether the block tile is the better one for the one-frame nearest fusion, and
 // boxes staged in LDS for the bilinear fusion.
 bool block_pays(const psfs_camera *cams, int n, const psfs_grid &grid, bool step);
+constexpr int kNarrowTile = 2, kShallowTile = 3;    // 8 x 16 columns of 4 voxels, 8 x 32 of 2
+bool small_grid(const psfs_grid &grid);
 bool bilinear_boxes_pay(const psfs_camera *cams, int n, const psfs_grid &grid);
 
 // Autotuner cache (tune_cache.hip): $PSFS_AUTOTUNE_CACHE, else
