@@ -119,10 +119,15 @@ __device__ __forceinline__ void block_boxes(const Views &views, int n, const Gri
             const bool pieces = (g.W & 3) == 0 || x1 + 3 < g.W;
             const int xa = pieces ? x0 & ~3 : x0;
             const int bw = pieces ? (x1 - xa + 4) & ~3 : x1 - xa + 1, bh = y1 - y0 + 1;
+            const bool inside = x0 >= 0 && y0 >= 0 && x1 < g.W && y1 < g.H;
+            // a kEdge entry is computed from y w + x in FP32, exact below 2^24: rows past
+            // 56000 of a box 300 pixels wide are not
+            const float rows = static_cast<float>(max(-y0, y1) + 1), cols = static_cast<float>(max(-xa, x1));
+            const bool exact = inside || fmaf(rows, static_cast<float>(bw), cols) < 16777216.0f;
             if (x1 < 0 || x0 >= g.W || y1 < 0 || y0 >= g.H)
                 b.mode = kMiss;
-            else if (bw <= kSArena && bh <= kSArena && bw * bh <= kSArena)
-                b = SBox{xa, y0, bw, bw * bh, x0 >= 0 && y0 >= 0 && x1 < g.W && y1 < g.H ? kInside : kEdge, pieces};
+            else if (exact && bw <= kSArena && bh <= kSArena && bw * bh <= kSArena)
+                b = SBox{xa, y0, bw, bw * bh, inside ? kInside : kEdge, pieces};
         }
     }
     boxes[v] = b;
@@ -233,7 +238,7 @@ __device__ __forceinline__ void fuse_block(const Views &views, int n, const floa
                             e[kk] = static_cast<int>(__umul24(y, static_cast<uint32_t>(b.w)) + x) + base;
                         }
                     } else {
-                        // exact in FP32 (integers below 2^24); the clamp keeps a read in the box
+                        // exact in FP32 (integers below 2^24, block_boxes); the clamp keeps a read in the box
 #pragma unroll
                         for (int kk = 0; kk < kSBChunk; ++kk) {
                             const float r = __builtin_amdgcn_rcpf(fmaf(g.P[10], Z[kk], cx));
