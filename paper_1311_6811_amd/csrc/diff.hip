@@ -171,7 +171,7 @@ __global__ __launch_bounds__(kBlock) void diff_fwd_kernel(DiffArgs a)
 #pragma unroll
     for (int kk = 0; kk < kFZ; ++kk) L[kk] = a.L0;
     __syncthreads();
-    add_bilinear<kFZ, kFwdArena>(a, Xd, Yd, q.kb, arena, boxes, L);
+    add_bilinear<Taps::kDifferentiable, kFZ, kFwdArena>(a, Xd, Yd, q.kb, arena, boxes, L);
 
     double part = 0.0;
     if (q.i < a.nx && q.j < a.ny) {
@@ -280,7 +280,7 @@ __device__ __forceinline__ void box_voxels(const DiffArgs &a, const Proj64 &p, c
         if (gv[kk] == 0.0f) continue;
         const double Zd = centre64(a.oz, a.h, kb + kk);
         Tap4 t;
-        project64_front(p, Zd, t);
+        project64_front<Taps::kDifferentiable>(p, Zd, t);
         const int e = min(max(static_cast<int>(fma(t.y0, wd, t.x0 - od)), 0), emax);
         const float l00 = map_box[e], l10 = map_box[e + 1], l01 = map_box[e + box.w], l11 = map_box[e + box.w + 1];
         if (SCATTER && scatters(gv[kk], qscale)) {
@@ -306,7 +306,7 @@ __device__ __forceinline__ void map_voxels(const DiffArgs &a, const ViewGeom &g,
         if (gv[kk] == 0.0f) continue;
         const double Zd = centre64(a.oz, a.h, kb + kk);
         Tap4 t;
-        if (!project64(p, Zd, t)) continue;
+        if (!project64<Taps::kDifferentiable>(p, Zd, t)) continue;
         if (!(t.x0 >= -1.0 && t.x0 < g.W && t.y0 >= -1.0 && t.y0 < g.H)) continue;
         const int ix = static_cast<int>(t.x0), iy = static_cast<int>(t.y0);
         const bool xin0 = ix >= 0, xin1 = ix + 1 < g.W, yin0 = iy >= 0, yin1 = iy + 1 < g.H;

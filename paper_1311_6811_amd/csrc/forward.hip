@@ -281,7 +281,7 @@ __global__ __launch_bounds__(kBoxThreads) void fuse_bilinear_kernel(BilinearArgs
 #pragma unroll
     for (int kk = 0; kk < KZ; ++kk) L[kk] = a.L0;
     __syncthreads();
-    add_bilinear<KZ, kBilArena>(a, Xd, Yd, k0, arena, boxes, L);
+    add_bilinear<Taps::kPosterior, KZ, kBilArena>(a, Xd, Yd, k0, arena, boxes, L);
     if (i >= a.nx || j >= a.ny) return;
     const int64_t plane = static_cast<int64_t>(a.nx) * a.ny;
     int64_t idx = (static_cast<int64_t>(k0) * a.ny + j) * a.nx + i;

@@ -164,7 +164,7 @@ __device__ __forceinline__ int stage_group(const Args &a, int v0, int v_hi, cons
 // block. The views are taken in groups whose boxes fit the CAP floats of
 // `arena` together: their boxes are loaded at once, and one barrier waits for
 // the group. A view without a valid box is sampled from its map.
-template <int KZ, int CAP, class Args>
+template <Taps T, int KZ, int CAP, class Args>
 __device__ __forceinline__ void add_bilinear(const Args &a, double Xd, double Yd, int kb, float *arena,
                                              const PixBox *boxes, float (&L)[KZ])
 {
@@ -189,7 +189,7 @@ __device__ __forceinline__ void add_bilinear(const Args &a, double Xd, double Yd
                 for (int kk = 0; kk < KZ; ++kk) {
                     const double Zd = centre64(a.oz, a.h, kb + kk);
                     Tap4 t;
-                    project64_front(p, Zd, t);
+                    project64_front<T>(p, Zd, t);
                     const int e = min(max(static_cast<int>(fma(t.y0, wd, t.x0 - od)), 0), emax);
                     const float *s = arena + off + e;
                     const float top = fmaf(t.fx, s[1] - s[0], s[0]);
@@ -202,7 +202,7 @@ __device__ __forceinline__ void add_bilinear(const Args &a, double Xd, double Yd
                 for (int kk = 0; kk < KZ; ++kk) {
                     const double Zd = centre64(a.oz, a.h, kb + kk);
                     Tap4 t;
-                    if (!project64(p, Zd, t)) continue;
+                    if (!project64<T>(p, Zd, t)) continue;
                     L[kk] += bilinear_sample(a.lmap + g.map_off, g.W, g.H, t.x0, t.y0, t.fx, t.fy);
                 }
             }
