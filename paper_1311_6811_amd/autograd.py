@@ -69,10 +69,10 @@ class DiffPlan(Plan):
         self.sizes = list(sizes)
 
     def takes(self, P: torch.Tensor) -> bool:
-        """P lies on the current GPU and the plan's cameras have this plan's
-        sizes (they do after its first call): the forward can then read the
-        matrices beside its own work."""
-        return (P.is_cuda and P.get_device() == torch.cuda.current_device() and len(P) == len(self.sizes)
+        """P holds a 3 x 4 matrix per view on the current GPU and the plan's
+        cameras have this plan's sizes (they do after its first call): the
+        forward can then read the matrices beside its own work."""
+        return (P.is_cuda and P.get_device() == torch.cuda.current_device() and P.numel() == 12 * len(self.sizes)
                 and self._hw == [(c.height, c.width) for c in self.sizes])
 
 
