@@ -329,6 +329,17 @@ int open_mail(CameraMail &m)
     return PSFS_OK;
 }
 
+// A copy into host memory that outlives the call: waited for wherever the call
+// ends before it has seen the copy arrive.
+struct PendingCopy {
+    hipStream_t stream;
+    bool pending = false;
+    ~PendingCopy()
+    {
+        if (pending) hipStreamSynchronize(stream);
+    }
+};
+
 int enqueue_likelihood(const psfs_plan *p, const uint8_t *const *images, float *lmap, hipStream_t s,
                        bool use_fg = true)
 {
@@ -1171,10 +1182,12 @@ int psfs_diff_forward_at(psfs_plan *plan, int n, psfs_camera *cams, const float 
     // The matrices travel to the host (the kernels take them as arguments, and
     // a non-finite one is refused) while the likelihood maps, which do not
     // depend on them, are computed.
+    PendingCopy copy{s};
     if (n > 0) {
         if ((rc = open_mail(plan->mail))) return rc;
         next.mail = plan->mail;
         hipError_t e = hipMemcpyAsync(plan->mail.P, P_dev, sizeof(float) * 12 * n, hipMemcpyDeviceToHost, s);
+        copy.pending = e == hipSuccess;
         if (e == hipSuccess) e = hipEventRecord(plan->mail.arrived, s);
         if (e != hipSuccess) return hip_fail(e, "reading the camera matrices");
     }
@@ -1182,6 +1195,7 @@ int psfs_diff_forward_at(psfs_plan *plan, int n, psfs_camera *cams, const float 
     if (n > 0) {
         hipError_t e = hipEventSynchronize(plan->mail.arrived);
         if (e != hipSuccess) return hip_fail(e, "waiting for the camera matrices");
+        copy.pending = false;
         for (int k = 0; k < n; ++k) {
             std::memcpy(next.cams[k].P, plan->mail.P + 12 * k, sizeof(next.cams[k].P));
             if ((rc = check_camera(k, next.cams[k]))) return rc;

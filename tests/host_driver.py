@@ -1,0 +1,114 @@
+"""Runs the library's host code against tests/hip_double.c, in a process of its
+own without torch (which would bring the real runtime along):
+
+    python tests/host_driver.py <double.so> <check> [<JSON argument>]
+
+prints the check's result as JSON."""
+import ctypes as C
+import importlib.util
+import json
+import math
+import os
+import subprocess
+import sys
+import tempfile
+
+import numpy as np
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+sys.path.insert(0, ROOT)
+from synth import scene as S  # noqa: E402
+
+
+def check(tmp_path_factory, name, arg=None):
+    """The result of a check, from a test."""
+    out = tmp_path_factory.getbasetemp() / "hip_double.so"
+    if not out.exists():
+        subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                        os.path.join(ROOT, "tests", "hip_double.c"), "-o", str(out)], check=True)
+    env = dict(os.environ)
+    env.setdefault("PSFS_AUTOTUNE_CACHE", os.path.join(tempfile.mkdtemp(dir=tmp_path_factory.getbasetemp()), "tune.json"))
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), str(out), name, json.dumps(arg)],
+                       capture_output=True, text=True, timeout=120, env=env)
+    assert r.returncode == 0, r.stderr[-2000:]
+    return json.loads(r.stdout.splitlines()[-1])
+
+
+def _load(double):
+    spec = importlib.util.spec_from_file_location("psfs_signatures", os.path.join(ROOT, "paper_1311_6811_amd", "_lib.py"))
+    L = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(L)
+    dbl = C.CDLL(double, mode=C.RTLD_GLOBAL)
+    dbl.dbl_launch.restype, dbl.dbl_cost.argtypes = C.c_char_p, [C.c_char_p, C.c_float]
+    return L, L.lib(), dbl
+
+
+FAKE = 1 << 20                  # a device address that nothing reads
+
+
+class Host:
+    def __init__(self, double):
+        self.L, self.lib, self.dbl = _load(double)
+
+    def cameras(self, cams):
+        arr = (self.L.psfs_camera * max(len(cams), 1))()
+        for a, c in zip(arr, cams):
+            a.width, a.height, a.P = c.width, c.height, tuple(np.asarray(c.P, np.float32).reshape(12).tolist())
+        return arr
+
+    def grid(self, nx, ny, nz, side=2.0):
+        h = np.float32(side / max(nx, ny, nz))
+        return self.L.psfs_grid(nx, ny, nz, tuple(float(np.float32(-0.5 * h * d)) for d in (nx, ny, nz)), float(h))
+
+    def params(self, sampling=0):
+        return self.L.psfs_params(0.5, -3.0 * math.log(256.0), 0.5, sampling)
+
+    def plan(self, cams, grid, sampling=0, backgrounds=True):
+        h = C.c_void_p()
+        assert self.lib.psfs_plan_create(C.byref(h)) == 0
+        assert self.lib.psfs_set_cameras(h, len(cams), self.cameras(cams)) == 0
+        assert self.lib.psfs_set_grid(h, C.byref(grid)) == 0
+        assert self.lib.psfs_set_params(h, C.byref(self.params(sampling))) == 0
+        for k in range(len(cams) if backgrounds else 0):
+            assert self.lib.psfs_set_background(h, k, FAKE, FAKE) == 0
+        return h
+
+    def fakes(self, n):
+        return self.L.ptr_array([FAKE] * n)
+
+    def launches(self):
+        """[(kernel, grid, workgroup)] since the last look."""
+        out = []
+        for k in range(self.dbl.dbl_launches()):
+            dim = (C.c_uint * 6)()
+            name = self.dbl.dbl_launch(k, dim).decode()
+            out.append((name, list(dim[:3]), list(dim[3:])))
+        self.dbl.dbl_reset()
+        return out
+
+
+def diff_forward_at(host, arg):
+    """psfs_diff_forward_at with a failing runtime: the status, copies still under
+    way at its return and whether the plan had taken the views (its likelihood
+    then finds backgrounds)."""
+    cams = S.ring_rig(2, 100.0, 32, 24)
+    plan = host.plan(cams, host.grid(8, 8, 8), 1, backgrounds=False)
+    P = np.stack([np.asarray(c.P, np.float32) + 1 for c in cams]).astype(np.float32)
+    ws = host.lib.psfs_diff_workspace_bytes(plan)
+    bg, ims = host.fakes(2), host.fakes(2)
+    if arg["fail"] == "record":
+        host.dbl.dbl_fail_record(1)
+    elif arg["fail"]:
+        host.dbl.dbl_fail_launch(arg["fail"])
+    taken = host.cameras(cams)
+    rc = host.lib.psfs_diff_forward_at(plan, 2, taken, P.ctypes.data, bg, bg, ims, FAKE, None, FAKE, FAKE, FAKE, ws, None)
+    pending = host.dbl.dbl_pending()
+    host.dbl.dbl_reset()
+    ready = host.lib.psfs_likelihood(plan, ims, FAKE, None) == 0
+    got = [list(c.P) for c in taken] == P.reshape(2, 12).tolist()
+    host.lib.psfs_plan_destroy(plan)
+    return dict(rc=rc, pending=pending, ready=ready, matrices=got)
+
+
+if __name__ == "__main__":
+    print(json.dumps(globals()[sys.argv[2]](Host(sys.argv[1]), json.loads(sys.argv[3]))))
