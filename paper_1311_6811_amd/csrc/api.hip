@@ -1203,10 +1203,10 @@ int psfs_diff_forward_at(psfs_plan *plan, int n, psfs_camera *cams, const float 
     }
     if ((rc = prepare_diff(&next, images_dev, labels_dev, sub, workspace_dev, workspace_bytes, a, L))) return rc;
     a.logits = logits_dev;
-    *plan = next;
-    for (int k = 0; k < n; ++k) cams[k] = next.cams[k];
     hipError_t e = launch_diff_forward(a, loss_dev, s);
     if (e != hipSuccess) return hip_fail(e, "differentiable forward launch");
+    *plan = next;
+    for (int k = 0; k < n; ++k) cams[k] = next.cams[k];
     return PSFS_OK;
     PSFS_GUARD_END
 }
