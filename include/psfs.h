@@ -495,8 +495,10 @@ int psfs_batch_tune(psfs_batch *batch, void *workspace_dev, size_t workspace_byt
  * or -1 for the tuned/default choice. A tile is a workgroup of tx x ty voxel
  * columns of kz voxels each. On the 16 x 16 x 8 tile the one-frame nearest
  * paths of a plan or a batch take two such blocks per workgroup, stage their
- * per-view pixel boxes in LDS and read them there; the other tiles gather from
- * the maps directly. The default follows the grid and the rig. */
+ * per-view pixel boxes in LDS and read them there, and so does the bilinear
+ * fusion of psfs_fuse and psfs_reconstruct with blocks of 8, 4 or 2 slices; the
+ * other tiles gather from the maps directly. The default follows the grid and
+ * the rig. */
 int psfs_tile_count(void);
 int psfs_tile_describe(int tile, int32_t *tx, int32_t *ty, int32_t *kz);
 /* Fusion tile of a plan's one-frame paths (psfs_fuse, psfs_reconstruct,

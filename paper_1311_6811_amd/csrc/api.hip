@@ -395,7 +395,8 @@ void fill_geometry(const psfs_plan *p, int sampling, FuseArgs &a)
 int launch_tile(const psfs_plan *p, bool step)
 {
     if (p->tile >= 0) return p->tile;
-    if (p->params.sampling != PSFS_NEAREST) return default_tile();
+    if (p->params.sampling != PSFS_NEAREST)
+        return !step && bilinear_boxes_pay(p->cams, p->n, p->grid) ? block_tile() : default_tile();
     if (block_pays(p->cams, p->n, p->grid, step)) return block_tile();
     return small_grid(p->grid) ? kShallowTile : kNarrowTile;
 }
@@ -410,8 +411,7 @@ int enqueue_fuse(const psfs_plan *p, const float *lmap, float *post, uint8_t *oc
     a.lmap = lmap;
     a.post = post;
     a.occ = occ;
-    const bool boxes = p->params.sampling == PSFS_BILINEAR && bilinear_boxes_pay(p->cams, p->n, p->grid);
-    hipError_t e = launch_fuse(a, launch_tile(p, false), p->params.sampling, boxes, s);
+    hipError_t e = launch_fuse(a, launch_tile(p, false), p->params.sampling, s);
     if (e != hipSuccess) return hip_fail(e, "fusion kernel launch");
     return PSFS_OK;
 }

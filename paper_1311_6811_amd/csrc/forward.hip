@@ -304,9 +304,8 @@ __global__ __launch_bounds__(256) void threshold_kernel(const float *post, int64
 
 // Tile kBlockTile is the kSBX x kSBY x kSBZ voxel block: the one-frame
 // nearest paths fuse it, kSBStack to a workgroup, from pixel boxes staged in LDS,
-// the pipelined bilinear step with 16 x 16 columns of 8 voxels. Bilinear fusion
-// by itself runs from boxes (launch_fuse_bilinear) or on tile 0's columns,
-// whatever the tile.
+// as does bilinear fusion by itself (launch_fuse_bilinear); the pipelined bilinear
+// step runs 16 x 16 columns of 8 voxels on it.
 constexpr TileCfg kTiles[] = {
     {8, 32, 4}, {8, 32, 8}, {8, 16, 4}, {8, 32, 2}, {32, 8, 4}, {16, 16, 4}, {kSBX, kSBY, kSBZ},
 };
@@ -398,20 +397,21 @@ hipError_t launch_fuse_bilinear(const FuseArgs &f, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_fuse_nearest(const FuseArgs &a, int tile, hipStream_t s)
+template <int S>
+hipError_t launch_fuse_s(const FuseArgs &a, int tile, hipStream_t s)
 {
-    if (tile == kBlockTile) return launch_fuse_block(a, s);
     const TileCfg &c = kTiles[tile];
     const int64_t nb = static_cast<int64_t>((a.nx + c.tx - 1) / c.tx) * ((a.ny + c.ty - 1) / c.ty) *
                        ((a.nz + c.kz - 1) / c.kz);
+    if (nb == 0) return hipSuccess;
     const dim3 grid(static_cast<unsigned>(nb)), block(c.tx * c.ty);
     switch (tile) {
-    case 0: hipLaunchKernelGGL((fuse_kernel<8, 32, 4, PSFS_NEAREST>), grid, block, 0, s, a); break;
-    case 1: hipLaunchKernelGGL((fuse_kernel<8, 32, 8, PSFS_NEAREST>), grid, block, 0, s, a); break;
-    case 2: hipLaunchKernelGGL((fuse_kernel<8, 16, 4, PSFS_NEAREST>), grid, block, 0, s, a); break;
-    case 3: hipLaunchKernelGGL((fuse_kernel<8, 32, 2, PSFS_NEAREST>), grid, block, 0, s, a); break;
-    case 4: hipLaunchKernelGGL((fuse_kernel<32, 8, 4, PSFS_NEAREST>), grid, block, 0, s, a); break;
-    case 5: hipLaunchKernelGGL((fuse_kernel<16, 16, 4, PSFS_NEAREST>), grid, block, 0, s, a); break;
+    case 0: hipLaunchKernelGGL((fuse_kernel<8, 32, 4, S>), grid, block, 0, s, a); break;
+    case 1: hipLaunchKernelGGL((fuse_kernel<8, 32, 8, S>), grid, block, 0, s, a); break;
+    case 2: hipLaunchKernelGGL((fuse_kernel<8, 16, 4, S>), grid, block, 0, s, a); break;
+    case 3: hipLaunchKernelGGL((fuse_kernel<8, 32, 2, S>), grid, block, 0, s, a); break;
+    case 4: hipLaunchKernelGGL((fuse_kernel<32, 8, 4, S>), grid, block, 0, s, a); break;
+    case 5: hipLaunchKernelGGL((fuse_kernel<16, 16, 4, S>), grid, block, 0, s, a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -432,14 +432,11 @@ hipError_t launch_slm(const SlmArgs &a, int64_t max_npix, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_fuse(const FuseArgs &a, int tile, int sampling, bool boxes, hipStream_t s)
+hipError_t launch_fuse(const FuseArgs &a, int tile, int sampling, hipStream_t s)
 {
-    if (sampling == PSFS_NEAREST) return launch_fuse_nearest(a, tile, s);
-    if (boxes) return launch_fuse_bilinear(a, s);
-    const int64_t nb = tile_count_of<8, 32, 4>(a);
-    if (nb == 0) return hipSuccess;
-    hipLaunchKernelGGL((fuse_kernel<8, 32, 4, PSFS_BILINEAR>), dim3(static_cast<unsigned>(nb)), dim3(256), 0, s, a);
-    return hipGetLastError();
+    if (sampling == PSFS_NEAREST)
+        return tile == kBlockTile ? launch_fuse_block(a, s) : launch_fuse_s<PSFS_NEAREST>(a, tile, s);
+    return tile == kBlockTile ? launch_fuse_bilinear(a, s) : launch_fuse_s<PSFS_BILINEAR>(a, tile, s);
 }
 
 hipError_t launch_pipeline(const SlmArgs &sa, const FuseArgs &fa, int tile, int sampling, int64_t max_npix,

@@ -216,8 +216,7 @@ int default_tile();
 int block_tile();                       // the tile that fuses from pixel boxes staged in LDS
 
 hipError_t launch_slm(const SlmArgs &a, int64_t max_npix, hipStream_t s);
-// boxes: bilinear sampling from pixel boxes staged in LDS (else column by column).
-hipError_t launch_fuse(const FuseArgs &a, int tile, int sampling, bool boxes, hipStream_t s);
+hipError_t launch_fuse(const FuseArgs &a, int tile, int sampling, hipStream_t s);
 // sa.n == 0: no likelihood part; fa.post == nullptr: no fusion part.
 hipError_t launch_pipeline(const SlmArgs &sa, const FuseArgs &fa, int tile, int sampling, int64_t max_npix,
                            hipStream_t s);

@@ -110,5 +110,22 @@ def diff_forward_at(host, arg):
     return dict(rc=rc, pending=pending, ready=ready, matrices=got)
 
 
+def fusion_kernels(host, arg):
+    """The kernel that psfs_fuse launches on every tile (-1 too), and the tile
+    that psfs_get_tile then reports."""
+    cams = S.ring_rig(arg["n"], 0.9375 * arg["W"], arg["W"], arg["H"])
+    plan = host.plan(cams, host.grid(*arg["grid"]), arg["sampling"])
+    out = []
+    for tile in range(-1, host.lib.psfs_tile_count()):
+        assert host.lib.psfs_set_tile(plan, tile) == 0
+        reported = host.lib.psfs_get_tile(plan)
+        host.launches()
+        assert host.lib.psfs_fuse(plan, FAKE, FAKE, FAKE, None) == 0
+        (name, grid, group), = host.launches()
+        out.append((tile, reported, name, grid, group))
+    host.lib.psfs_plan_destroy(plan)
+    return out
+
+
 if __name__ == "__main__":
     print(json.dumps(globals()[sys.argv[2]](Host(sys.argv[1]), json.loads(sys.argv[3]))))
