@@ -26,7 +26,7 @@ struct psfs_batch {
     int device = -1;
     int cus = 0;
     int tile = 0;
-    bool automatic = true;                  // no tile was set: nearest frames run the block tile
+    bool automatic = true;                  // no tile was set: each nearest frame runs the tile that suits it
     std::vector<char> block;                // per user frame: block_pays at creation (the launches depend on it)
     std::vector<psfs_frame> user;           // caller's frame structs (pointers to their arrays not kept)
     std::vector<int> order;                 // order[i] = user frame placed i-th in the chain (chain_order)
@@ -144,11 +144,22 @@ void take_frames(psfs_batch *b, int nframes, const psfs_frame *frames)
     }
 }
 
-// The tile the chain runs; on the block tile the nearest frames that tile 0
-// fuses faster run that one.
+// What the launches of a chain depend on beside the frames' shapes: the tile of
+// every frame, or -1 when each runs the one that suits it (frame_tile).
 int chain_tile(const psfs_batch *b)
 {
-    return b->automatic && b->params.sampling == PSFS_NEAREST ? block_tile() : b->tile;
+    return b->automatic && b->params.sampling == PSFS_NEAREST ? -1 : b->tile;
+}
+
+// Tile of user frame f. (Column steps of larger grids are on tile 0: the narrow
+// tile's two-wave likelihood workgroups, each with its own reads of the table,
+// made 24 frames 946 -> 956 us.)
+int frame_tile(const psfs_batch *b, int f)
+{
+    const int tile = chain_tile(b);
+    if (tile >= 0) return tile;
+    if (b->block[f]) return block_tile();
+    return small_grid(b->user[f].grid) ? kShallowTile : default_tile();
 }
 
 // Builds the descriptor table (and the per-frame launch sizes) for the
@@ -163,7 +174,6 @@ void build_table(psfs_batch *b)
     b->fuse_tiles.clear();
     b->tiles.clear();
     int64_t map_off = 0;
-    const int tile = chain_tile(b);
     for (int oi = 0; oi < nf; ++oi) {
         const int f = b->order[oi];
         const psfs_frame &u = b->user[f];
@@ -199,10 +209,7 @@ void build_table(psfs_batch *b)
         }
         b->frames.push_back(fr);
         b->slm_per_view.push_back(batch_slm_blocks_per_view(max_np));
-        // (column steps of larger grids stay on tile 0: the narrow tile's two-wave likelihood
-        // workgroups, each with its own reads of the table, made 24 frames 946 -> 956 us)
-        const int column = small_grid(u.grid) ? kShallowTile : default_tile();
-        b->tiles.push_back(nearest && tile == block_tile() && !b->block[f] ? column : tile);
+        b->tiles.push_back(frame_tile(b, f));
         b->fuse_tiles.push_back(batch_bricks(u.grid.nx, u.grid.ny, u.grid.nz, b->tiles.back(), nearest && b->tiles.back() == block_tile()));
     }
     b->map_floats = map_off;

@@ -127,5 +127,34 @@ def fusion_kernels(host, arg):
     return out
 
 
+def batch_kernels(host, arg):
+    """Of a batch of these frames (grid, views, image size) on every tile (-1
+    too): the tile that psfs_batch_get_tile reports, the kernels of a run and of
+    the run after a same-shape update."""
+    frames = [(S.ring_rig(n, 0.9375 * W, W, H), host.grid(*grid)) for grid, n, W, H in arg["frames"]]
+    arr = (host.L.psfs_frame * len(frames))()
+    keep = []
+    for a, (cams, grid) in zip(arr, frames):
+        keep += [host.cameras(cams), host.fakes(len(cams))]
+        a.grid, a.n, a.cams = grid, len(cams), keep[-2]
+        a.images_dev = a.mean_dev = a.var_dev = keep[-1]
+        a.posterior_dev = FAKE
+    h = C.c_void_p()
+    assert host.lib.psfs_batch_create(C.byref(h), C.byref(host.params(arg["sampling"])), len(frames), arr) == 0
+    nbytes = host.lib.psfs_batch_workspace_bytes(h)
+    out = []
+    for tile in arg.get("tiles") or [*range(-1, host.lib.psfs_tile_count()), -1]:
+        assert host.lib.psfs_batch_set_tile(h, tile) == 0
+        runs = []
+        for _ in range(2):
+            host.launches()
+            assert host.lib.psfs_batch_run(h, FAKE, nbytes, None) == 0
+            runs.append(host.launches())
+            assert host.lib.psfs_batch_update(h, len(frames), arr) == 0
+        out.append((tile, host.lib.psfs_batch_get_tile(h), *runs))
+    host.lib.psfs_batch_destroy(h)
+    return out
+
+
 if __name__ == "__main__":
     print(json.dumps(globals()[sys.argv[2]](Host(sys.argv[1]), json.loads(sys.argv[3]))))

@@ -8,9 +8,9 @@ TILES = [(8, 32, 4), (8, 32, 8), (8, 16, 4), (8, 32, 2), (32, 8, 4), (16, 16, 4)
 
 def tile_of(name):
     """The tile whose kernel this is."""
-    if "fuse_block_kernel" in name or "fuse_bilinear_kernel" in name:
+    if any(part in name for part in ("fuse_block_kernel", "fuse_bilinear_kernel", "pipe_block_kernel")):
         return 6
-    return [k for k, (x, y, z) in enumerate(TILES) if f"fuse_kernelILi{x}ELi{y}ELi{z}ELi" in name][0]
+    return [k for k, (x, y, z) in enumerate(TILES) if f"_kernelILi{x}ELi{y}ELi{z}ELi" in name][0]
 
 
 @pytest.mark.parametrize("sampling", [0, 1])
@@ -18,3 +18,20 @@ def tile_of(name):
 def test_a_set_tile_is_the_one_that_fuses(tmp_path_factory, sampling, grid, n, W, H):
     for tile, _, name, _, _ in check(tmp_path_factory, "fusion_kernels", dict(grid=grid, n=n, W=W, H=H, sampling=sampling)):
         assert tile == -1 or tile_of(name) == tile, name
+
+
+BATCH = [((160, 160, 160), 12, 640, 480), ((40, 40, 40), 4, 320, 240), ((128, 128, 128), 6, 640, 480), ((208, 200, 192), 8, 643, 477)]
+
+
+@pytest.mark.parametrize("sampling", [0, 1])
+def test_a_set_tile_is_the_one_that_every_frame_of_a_batch_runs(tmp_path_factory, sampling):
+    runs = check(tmp_path_factory, "batch_kernels", dict(frames=BATCH, sampling=sampling))
+    for tile, reported, first, again in runs:
+        assert first == again
+        if tile >= 0:
+            fusions = [name for name, _, _ in first if "slm" not in name]
+            assert {tile_of(name) for name in fusions} == {tile} and reported == tile
+    # -1 gives the batch its own choice back, whatever was set in between
+    assert runs[0][2:] == runs[-1][2:]
+    if sampling == 0:
+        assert len({tile_of(name) for name, _, _ in runs[0][2]}) == 3       # blocks, 2 voxels per lane, tile 0
