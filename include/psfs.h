@@ -476,7 +476,10 @@ int psfs_batch_update(psfs_batch *batch, int nframes, const psfs_frame *frames);
 /* Waits for the batch's outstanding work on the device, then frees it. NULL-safe. */
 void psfs_batch_destroy(psfs_batch *batch);
 
-/* Fusion tile of the batch (index into the tile table below; -1 = default). */
+/* Fusion tile of the batch (index into the tile table below; -1 = default: with
+ * nearest sampling each frame runs the tile that suits its grid and rig).
+ * psfs_batch_get_tile returns the tile in use, by default that of the frame with
+ * the most voxels times views. */
 int psfs_batch_set_tile(psfs_batch *batch, int tile);
 int psfs_batch_get_tile(const psfs_batch *batch);
 
@@ -505,7 +508,10 @@ int psfs_tile_describe(int tile, int32_t *tx, int32_t *ty, int32_t *kz);
  * psfs_pipeline_step); -1 = default. The two- and four-frame steps use fixed
  * tiles. Tiles never change results, only speed. */
 int psfs_set_tile(psfs_plan *plan, int tile);
-int psfs_get_tile(const psfs_plan *plan);     /* the tile in use, or a negative psfs_status */
+/* The tile that psfs_fuse and psfs_reconstruct run, or a negative psfs_status (by
+ * default psfs_pipeline_step may run another one; tile 0 while the plan has no
+ * grid or cameras that a default could follow). */
+int psfs_get_tile(const psfs_plan *plan);
 
 /* Plan autotuner: computes the plan's likelihood maps of `images_dev` once,
  * then times the fusion with every tile (2 warm-up + 5 timed launches each,

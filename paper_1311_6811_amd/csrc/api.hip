@@ -1274,7 +1274,8 @@ int psfs_set_tile(psfs_plan *plan, int tile)
 int psfs_get_tile(const psfs_plan *plan)
 {
     if (!plan) return fail(PSFS_E_ARG, "plan is NULL");
-    return plan->tile >= 0 ? plan->tile : default_tile();
+    if (plan->tile < 0 && (plan->n < 0 || !plan->has_grid)) return default_tile();
+    return launch_tile(plan, false);
 }
 
 size_t psfs_tune_workspace_bytes(const psfs_plan *plan)

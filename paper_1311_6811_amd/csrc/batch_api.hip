@@ -468,7 +468,17 @@ int psfs_batch_set_tile(psfs_batch *b, int tile)
 int psfs_batch_get_tile(const psfs_batch *b)
 {
     if (!b) return fail(PSFS_E_ARG, "batch is NULL");
-    return b->tile;
+    int largest = 0;
+    double most = -1.0;
+    for (size_t f = 0; f < b->user.size(); ++f) {
+        const psfs_frame &u = b->user[f];
+        const double work = static_cast<double>(u.grid.nx) * u.grid.ny * u.grid.nz * u.n;
+        if (work > most) {
+            most = work;
+            largest = static_cast<int>(f);
+        }
+    }
+    return frame_tile(b, largest);
 }
 
 int psfs_batch_tune(psfs_batch *b, void *workspace_dev, size_t workspace_bytes_, void *stream, int force,

@@ -35,3 +35,21 @@ def test_a_set_tile_is_the_one_that_every_frame_of_a_batch_runs(tmp_path_factory
     assert runs[0][2:] == runs[-1][2:]
     if sampling == 0:
         assert len({tile_of(name) for name, _, _ in runs[0][2]}) == 3       # blocks, 2 voxels per lane, tile 0
+
+
+@pytest.mark.parametrize("sampling", [0, 1])
+@pytest.mark.parametrize("grid,n,W,H,nearest,bilinear", [
+    ((40, 33, 20), 3, 320, 240, 3, 6), ((128, 128, 128), 8, 640, 480, 2, 6), ((200, 200, 200), 12, 1280, 720, 6, 6),
+    ((64, 64, 64), 4, 1280, 720, 3, 0)])
+def test_the_reported_tile_is_the_one_that_fuses(tmp_path_factory, sampling, grid, n, W, H, nearest, bilinear):
+    for tile, reported, name, _, _ in check(tmp_path_factory, "fusion_kernels", dict(grid=grid, n=n, W=W, H=H, sampling=sampling)):
+        assert reported == tile_of(name) == (tile if tile >= 0 else bilinear if sampling else nearest)
+
+
+@pytest.mark.parametrize("frames", [BATCH, BATCH[:2], BATCH[1:2], BATCH[2:3], BATCH[1:3]])
+def test_the_reported_tile_of_a_batch_is_that_of_its_largest_frame(tmp_path_factory, frames):
+    largest = max(frames, key=lambda f: f[0][0] * f[0][1] * f[0][2] * f[1])
+    args = [dict(frames=f, sampling=0, tiles=[-1]) for f in (frames, [largest])]
+    (_, reported, _, _), = check(tmp_path_factory, "batch_kernels", args[0])
+    (_, _, alone, _), = check(tmp_path_factory, "batch_kernels", args[1])
+    assert {reported} == {tile_of(name) for name, _, _ in alone}
