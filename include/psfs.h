@@ -514,14 +514,19 @@ int psfs_set_tile(psfs_plan *plan, int tile);
 int psfs_get_tile(const psfs_plan *plan);
 
 /* Plan autotuner: computes the plan's likelihood maps of `images_dev` once,
- * then times the fusion with every tile (2 warm-up + 5 timed launches each,
- * HIP events on `stream`, blocking) and sets the fastest on the plan. The
- * choice is cached in the same JSON file as the batch tuner's, keyed by
- * device, CU count, sampling, grid edge class (ceil log2 of the longest grid
- * side), view count and image class (ceil log2 of the largest view's pixel
- * count); a cached choice is applied without timing unless force != 0.
+ * then times the fusion alone and the one-frame step with every tile (2 warm-up
+ * + 5 timed launches each, HIP events on `stream`, blocking) and sets the fastest
+ * on the plan, one for psfs_fuse and psfs_reconstruct (*best_tile) and one for
+ * psfs_pipeline_step; a tile replaces the default where it is 2 % faster. The
+ * choices are cached in the same JSON file as the batch tuner's, keyed by
+ * device, CU count, revision of the kernels, sampling, grid edge class (ceil log2
+ * of the longest grid side), view count, image class (ceil log2 of the largest
+ * view's pixel count) and the default tiles; cached choices are applied without
+ * timing unless force != 0.
  * workspace_dev: psfs_tune_workspace_bytes(plan) bytes, 256-byte aligned
- * (maps, a posterior and an occupancy grid; overwritten). */
+ * (maps, a posterior and an occupancy grid; overwritten), and for the step
+ * psfs_workspace_bytes(plan) more (its next maps): without them it is not timed
+ * and keeps its default tile. */
 size_t psfs_tune_workspace_bytes(const psfs_plan *plan);
 int psfs_tune(psfs_plan *plan, const uint8_t *const *images_dev, void *workspace_dev, size_t workspace_bytes,
               void *stream, int force, int *best_tile);

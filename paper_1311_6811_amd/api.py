@@ -143,10 +143,12 @@ class Plan:
         return L.check(L.lib().psfs_get_tile(self._h))
 
     def tune(self, images: Sequence[torch.Tensor], force: bool = False) -> int:
-        """Times the one-frame fusion with every tile on these images (or
-        takes the cached choice) and keeps the fastest; returns its index."""
+        """Times the one-frame fusion and step with every tile on these images
+        (or takes the cached choices) and keeps the fastest of each; returns
+        the fusion's index."""
         ims = self._images(images)
-        ws = torch.empty(max(int(L.lib().psfs_tune_workspace_bytes(self._h)), 256), dtype=torch.uint8, device="cuda")
+        nbytes = int(L.lib().psfs_tune_workspace_bytes(self._h)) + self.workspace_bytes()
+        ws = torch.empty(max(nbytes, 256), dtype=torch.uint8, device="cuda")
         best = C.c_int32(-1)
         L.check(L.lib().psfs_tune(self._h, ims, ws.data_ptr(), ws.numel(), _stream(), int(bool(force)),
                                   C.byref(best)))

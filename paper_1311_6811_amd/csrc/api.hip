@@ -33,7 +33,7 @@ struct psfs_plan {
     const float *var[PSFS_MAX_VIEWS] = {};
     const float *fg = nullptr;                      // learned foreground model (log density per bin)
     uint32_t *check = nullptr;                      // input-check flags (caller's device word), or off
-    int tile = -1;
+    int tile = -1, step_tile = -1;                  // of a fusion alone and of a one-frame step; -1: launch_tile
     CameraMail mail;
 };
 
@@ -384,7 +384,7 @@ void fill_geometry(const psfs_plan *p, int sampling, FuseArgs &a)
     a.tau = p->params.threshold;
 }
 
-// The plan's tile, or the best one for its grid and rig when none was set
+// The plan's tile, or the one for its grid and rig when none was set or tuned
 // (step: the fusion runs beside a frame's likelihood). Of the column tiles the
 // 128-lane one pads ragged grids the least and leaves the shortest last round:
 // over 90 shapes 1.08 times as fast as tile 0 in fusions (80^3 x 8 views 9.4 / 7.0 us,
@@ -394,7 +394,8 @@ void fill_geometry(const psfs_plan *p, int sampling, FuseArgs &a)
 // per lane (64^3 x 12: 6.7 / 5.8 us; 80^3 x 8: 7.0 / 8.5).
 int launch_tile(const psfs_plan *p, bool step)
 {
-    if (p->tile >= 0) return p->tile;
+    const int set = step ? p->step_tile : p->tile;
+    if (set >= 0) return set;
     if (p->params.sampling != PSFS_NEAREST)
         return !step && bilinear_boxes_pay(p->cams, p->n, p->grid) ? block_tile() : default_tile();
     if (block_pays(p->cams, p->n, p->grid, step)) return block_tile();
@@ -413,6 +414,27 @@ int enqueue_fuse(const psfs_plan *p, const float *lmap, float *post, uint8_t *oc
     a.occ = occ;
     hipError_t e = launch_fuse(a, launch_tile(p, false), p->params.sampling, s);
     if (e != hipSuccess) return hip_fail(e, "fusion kernel launch");
+    return PSFS_OK;
+}
+
+// Likelihood maps of `images` into `next` beside the fusion of the maps `cur`;
+// without images or a posterior, the other part alone.
+int enqueue_step(const psfs_plan *p, const uint8_t *const *images, float *next, const float *cur, float *post,
+                 uint8_t *occ, hipStream_t s)
+{
+    SlmArgs sa{};
+    int64_t max_np = 0;
+    if (images && p->n > 0) max_np = fill_slm(p, images, next, sa);
+    FuseArgs fa{};
+    fill_geometry(p, p->params.sampling, fa);
+    fa.lmap = cur;
+    fa.post = nvox(p->grid) > 0 ? post : nullptr;
+    fa.occ = fa.post ? occ : nullptr;
+    if (sa.n == 0 && !fa.post) return PSFS_OK;
+    int rc = check_device();
+    if (rc) return rc;
+    hipError_t e = launch_pipeline(sa, fa, launch_tile(p, true), p->params.sampling, max_np, s);
+    if (e != hipSuccess) return hip_fail(e, "pipelined kernel launch");
     return PSFS_OK;
 }
 
@@ -516,6 +538,39 @@ int static_scratch(float **out)
         g_scratch_dev[dev] = ptr;
     }
     *out = static_cast<float *>(g_scratch_dev[dev]);
+    return PSFS_OK;
+}
+
+// The tile for which `launch` (2 warm-up and 5 timed launches) is fastest, into
+// *choice (plan->tile or plan->step_tile, which `launch` reads): a tile replaces
+// the default `first`, left as -1, where it is 2 % faster, more than equal
+// kernels differ by.
+template <class F>
+int tune_tile(int *choice, int first, F &&launch, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
+{
+    float best_ms = 0.0f;
+    int best = -1;
+    for (int i = -1; i < tile_count(); ++i) {
+        const int t = i < 0 ? first : i;
+        if (i == first) continue;
+        *choice = t;
+        int rc = PSFS_OK;
+        for (int w = 0; w < 2 && rc == PSFS_OK; ++w) rc = launch();
+        if (rc) return rc;
+        hipEventRecord(e0, s);
+        for (int r = 0; r < 5 && rc == PSFS_OK; ++r) rc = launch();
+        hipEventRecord(e1, s);
+        if (rc) return rc;
+        hipError_t e = hipEventSynchronize(e1);
+        if (e != hipSuccess) return hip_fail(e, "hipEventSynchronize");
+        float ms = 0.0f;
+        hipEventElapsedTime(&ms, e0, e1);
+        if (i < 0 || ms < (best < 0 ? 0.98f : 1.0f) * best_ms) {
+            best_ms = ms;
+            best = i;
+        }
+    }
+    *choice = best;
     return PSFS_OK;
 }
 
@@ -776,19 +831,7 @@ int psfs_pipeline_step(psfs_plan *plan, const uint8_t *const *images_dev, float 
         const uintptr_t len = static_cast<uintptr_t>(maps) * sizeof(float);
         if (a0 < b0 + len && b0 < a0 + len) return fail(PSFS_E_ARG, "lmap_next and lmap_cur overlap");
     }
-    SlmArgs sa{};
-    int64_t max_np = 0;
-    if (next && plan->n > 0) max_np = fill_slm(plan, images_dev, lmap_next_dev, sa);
-    FuseArgs fa{};
-    fill_geometry(plan, plan->params.sampling, fa);
-    fa.lmap = lmap_cur_dev;
-    fa.post = (cur && nvox(plan->grid) > 0) ? posterior_dev : nullptr;
-    fa.occ = fa.post ? occ_dev : nullptr;
-    if (sa.n == 0 && !fa.post) return PSFS_OK;
-    if ((rc = check_device())) return rc;
-    hipError_t e = launch_pipeline(sa, fa, launch_tile(plan, true), plan->params.sampling, max_np, static_cast<hipStream_t>(stream));
-    if (e != hipSuccess) return hip_fail(e, "pipelined kernel launch");
-    return PSFS_OK;
+    return enqueue_step(plan, images_dev, lmap_next_dev, lmap_cur_dev, posterior_dev, occ_dev, static_cast<hipStream_t>(stream));
     PSFS_GUARD_END
 }
 
@@ -1267,7 +1310,7 @@ int psfs_set_tile(psfs_plan *plan, int tile)
 {
     if (!plan) return fail(PSFS_E_ARG, "plan is NULL");
     if (tile < -1 || tile >= tile_count()) return fail(PSFS_E_RANGE, "tile %d outside -1..%d", tile, tile_count() - 1);
-    plan->tile = tile;
+    plan->tile = plan->step_tile = tile;
     return PSFS_OK;
 }
 
@@ -1297,12 +1340,17 @@ int psfs_tune(psfs_plan *plan, const uint8_t *const *images_dev, void *workspace
     if (!workspace_dev || workspace_bytes < need || !aligned(workspace_dev, 256))
         return fail(PSFS_E_WORKSPACE, "tuning workspace needs %zu bytes, 256-byte aligned (got %zu)", need,
                     workspace_bytes);
-    // cache key: device, CU count, sampling, grid edge class, view count, image class
+    const bool steps = workspace_bytes >= need + psfs_workspace_bytes(plan);    // room for a step's next maps
     int dev = 0, cus = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return hip_fail(e, "device query");
     if ((rc = check_device())) return rc;
+    const int keep[2] = {plan->tile, plan->step_tile};
+    plan->tile = plan->step_tile = -1;
+    const int first = launch_tile(plan, false), first_step = launch_tile(plan, true);
+    // cache key: device, CU count, the kernels' revision, sampling, grid edge class, view
+    // count, image class and the default tiles
     auto log2ceil = [](int64_t x) {
         int c = 0;
         while ((int64_t(1) << c) < x) ++c;
@@ -1310,17 +1358,22 @@ int psfs_tune(psfs_plan *plan, const uint8_t *const *images_dev, void *workspace
     };
     int64_t edge = std::max({plan->grid.nx, plan->grid.ny, plan->grid.nz}), px = 1;
     for (int k = 0; k < plan->n; ++k) px = std::max<int64_t>(px, static_cast<int64_t>(plan->cams[k].width) * plan->cams[k].height);
-    char key[160];
-    std::snprintf(key, sizeof(key), "gfx950/%dcu/plan/s%d/e%d/n%d/i%d", cus, plan->params.sampling, log2ceil(edge),
-                  plan->n, log2ceil(px));
-    const std::string path = tune_cache_path();
+    char buf[160];
+    std::snprintf(buf, sizeof(buf), "gfx950/%dcu/plan/r%d/s%d/e%d/n%d/i%d/d%d.%d", cus, kTileRevision,
+                  plan->params.sampling, log2ceil(edge), plan->n, log2ceil(px), first, first_step);
+    const std::string key = buf, step_key = key + "/step", path = tune_cache_path();
     if (!force) {
         std::lock_guard<std::mutex> lock(tune_cache_mutex());
         const auto m = read_tune_cache(path);
-        const auto it = m.find(key);
-        if (it != m.end() && it->second >= 0 && it->second < tile_count()) {
-            plan->tile = it->second;
-            if (best_tile) *best_tile = it->second;
+        auto cached = [&](const std::string &k) {
+            const auto it = m.find(k);
+            return it != m.end() && it->second >= 0 && it->second < tile_count() ? it->second : -1;
+        };
+        const int t = cached(key), ts = cached(step_key);
+        if (t >= 0 && (ts >= 0 || !steps)) {
+            plan->tile = t == first ? -1 : t;
+            plan->step_tile = ts == first_step ? -1 : ts;
+            if (best_tile) *best_tile = t;
             return PSFS_OK;
         }
     }
@@ -1329,45 +1382,34 @@ int psfs_tune(psfs_plan *plan, const uint8_t *const *images_dev, void *workspace
     const size_t v = static_cast<size_t>(nvox(plan->grid));
     float *post = reinterpret_cast<float *>(base + align256(psfs_workspace_bytes(plan)));
     uint8_t *occ = reinterpret_cast<uint8_t *>(base + align256(psfs_workspace_bytes(plan)) + align256(4 * v));
+    float *next = reinterpret_cast<float *>(base + need);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // the maps do not depend on the tile: one likelihood pass, then each tile's fusion
-    if ((rc = enqueue_likelihood(plan, images_dev, lmap, s))) return rc;
     hipEvent_t e0 = nullptr, e1 = nullptr;
-    e = hipEventCreate(&e0);
-    if (e == hipSuccess) e = hipEventCreate(&e1);
-    if (e != hipSuccess) {
-        if (e0) hipEventDestroy(e0);
-        return hip_fail(e, "hipEventCreate");
+    // the maps do not depend on the tile: one likelihood pass, then each tile's fusion and step
+    rc = enqueue_likelihood(plan, images_dev, lmap, s);
+    if (rc == PSFS_OK) {
+        e = hipEventCreate(&e0);
+        if (e == hipSuccess) e = hipEventCreate(&e1);
+        if (e != hipSuccess) rc = hip_fail(e, "hipEventCreate");
     }
-    const int keep = plan->tile;
-    float best_ms = 1e30f;
-    int best = default_tile();
-    for (int t = 0; t < tile_count() && rc == PSFS_OK; ++t) {
-        plan->tile = t;
-        for (int w = 0; w < 2 && rc == PSFS_OK; ++w) rc = enqueue_fuse(plan, lmap, post, occ, s);
-        if (rc) break;
-        const int reps = 5;
-        hipEventRecord(e0, s);
-        for (int r = 0; r < reps && rc == PSFS_OK; ++r) rc = enqueue_fuse(plan, lmap, post, occ, s);
-        hipEventRecord(e1, s);
-        if (rc) break;
-        e = hipEventSynchronize(e1);
-        if (e != hipSuccess) { rc = hip_fail(e, "hipEventSynchronize"); break; }
-        float ms = 0.0f;
-        hipEventElapsedTime(&ms, e0, e1);
-        if (ms < best_ms) { best_ms = ms; best = t; }
-    }
-    hipEventDestroy(e0);
-    hipEventDestroy(e1);
+    if (rc == PSFS_OK)
+        rc = tune_tile(&plan->tile, first, [&] { return enqueue_fuse(plan, lmap, post, occ, s); }, s, e0, e1);
+    if (rc == PSFS_OK && steps)
+        rc = tune_tile(&plan->step_tile, first_step,
+                       [&] { return enqueue_step(plan, images_dev, next, lmap, post, occ, s); }, s, e0, e1);
+    if (e0) hipEventDestroy(e0);
+    if (e1) hipEventDestroy(e1);
     if (rc) {
-        plan->tile = keep;
+        plan->tile = keep[0];
+        plan->step_tile = keep[1];
         return rc;
     }
-    plan->tile = best;
+    const int best = launch_tile(plan, false);
     {
         std::lock_guard<std::mutex> lock(tune_cache_mutex());
         auto m = read_tune_cache(path);
         m[key] = best;
+        if (steps) m[step_key] = launch_tile(plan, true);
         write_tune_cache(path, m);
     }
     if (best_tile) *best_tile = best;

@@ -30,6 +30,10 @@ constexpr int kNarrowTile = 2, kShallowTile = 3;    // 8 x 16 columns of 4 voxel
 bool small_grid(const psfs_grid &grid);
 bool bilinear_boxes_pay(const psfs_camera *cams, int n, const psfs_grid &grid);
 
+// Part of the autotuners' cache keys: raised when the kernel behind a tile changes,
+// so that choices timed on the older one are not applied.
+constexpr int kTileRevision = 2;
+
 // Autotuner cache (tune_cache.hip): $PSFS_AUTOTUNE_CACHE, else
 // $HOME/.cache/psfs/autotune.json; callers hold tune_cache_mutex() around
 // a read-modify-write.

@@ -127,6 +127,41 @@ def fusion_kernels(host, arg):
     return out
 
 
+def _sequence(host, plan, n):
+    """Kernels of a fusion and of a one-frame step."""
+    host.launches()
+    assert host.lib.psfs_fuse(plan, FAKE, FAKE, FAKE, None) == 0
+    assert host.lib.psfs_pipeline_step(plan, host.fakes(n), FAKE, FAKE + (1 << 30), FAKE, None, None) == 0
+    return [name for name, _, _ in host.launches()]
+
+
+def tuned_plan(host, arg):
+    """A plan tuned while launches take `costs` [(part of the name, ms)]: the tile
+    returned and reported, the kernels it then runs, those of a second plan
+    tuned from the cache, and of one that was not tuned; the cache."""
+    cams = S.ring_rig(arg["n"], 0.9375 * arg["W"], arg["W"], arg["H"])
+    out = {}
+    if arg.get("cache"):
+        with open(os.environ["PSFS_AUTOTUNE_CACHE"], "w") as f:
+            json.dump(arg["cache"], f)
+    for name in ("timed", "cached", "untuned"):
+        plan = host.plan(cams, host.grid(*arg["grid"]), arg["sampling"])
+        best = C.c_int32(-1)
+        if name != "untuned":
+            for part, ms in arg["costs"] if name == "timed" else []:
+                host.dbl.dbl_cost(part.encode(), ms)
+            ws = host.lib.psfs_tune_workspace_bytes(plan) + (0 if arg.get("short") else host.lib.psfs_workspace_bytes(plan))
+            rc = host.lib.psfs_tune(plan, host.fakes(arg["n"]), FAKE, ws, None, 0, C.byref(best))
+            assert rc == 0, host.lib.psfs_last_error()
+        launched = len(host.launches())
+        out[name] = dict(best=best.value, reported=host.lib.psfs_get_tile(plan), launched=launched,
+                         kernels=_sequence(host, plan, arg["n"]))
+        host.lib.psfs_plan_destroy(plan)
+    with open(os.environ["PSFS_AUTOTUNE_CACHE"]) as f:
+        out["cache"] = json.load(f)
+    return out
+
+
 def batch_kernels(host, arg):
     """Of a batch of these frames (grid, views, image size) on every tile (-1
     too): the tile that psfs_batch_get_tile reports, the kernels of a run and of

@@ -53,3 +53,47 @@ def test_the_reported_tile_of_a_batch_is_that_of_its_largest_frame(tmp_path_fact
     (_, reported, _, _), = check(tmp_path_factory, "batch_kernels", args[0])
     (_, _, alone, _), = check(tmp_path_factory, "batch_kernels", args[1])
     assert {reported} == {tile_of(name) for name, _, _ in alone}
+
+
+def _tile_kernel(tile):
+    return "_kernelILi%dELi%dELi%dELi" % TILES[tile]
+
+
+MIDDLE = dict(grid=(144, 144, 144), n=8, W=640, H=480)       # blocks for the fusion alone, columns for a step
+
+
+@pytest.mark.parametrize("fusion,step", [(4, 1), (1, 6), (6, 6), (5, 5)])
+def test_the_plan_tuner_times_what_it_sets(tmp_path_factory, fusion, step):
+    """The fastest fusion and the fastest step, each for its own call."""
+    name = lambda t, of: ("fuse" if of else "pipe") + ("_block_kernel" if t == 6 else _tile_kernel(t))
+    got = check(tmp_path_factory, "tuned_plan", dict(MIDDLE, sampling=0, costs=[(name(fusion, True), 0.5), (name(step, False), 0.5)]))
+    for k in ("timed", "cached"):
+        assert got[k]["best"] == got[k]["reported"] == fusion
+        assert [tile_of(x) for x in got[k]["kernels"]] == [fusion, step]
+    assert got["timed"]["launched"] > 2 * 7 and got["cached"]["launched"] == 0
+
+
+@pytest.mark.parametrize("sampling", [0, 1])
+def test_a_tuned_plan_is_the_untuned_one_when_no_tile_is_clearly_faster(tmp_path_factory, sampling):
+    """All launches take as long, but for one that is 1 % faster: noise."""
+    got = check(tmp_path_factory, "tuned_plan", dict(MIDDLE, sampling=sampling, costs=[(_tile_kernel(4), 0.99)]))
+    assert got["timed"]["kernels"] == got["cached"]["kernels"] == got["untuned"]["kernels"]
+
+
+def test_the_bilinear_tuner_times_different_kernels(tmp_path_factory):
+    got = check(tmp_path_factory, "tuned_plan", dict(MIDDLE, sampling=1, costs=[("fuse" + _tile_kernel(3), 0.5), ("pipe" + _tile_kernel(1), 0.5)]))
+    assert got["timed"]["best"] == 3 and [tile_of(x) for x in got["timed"]["kernels"]] == [3, 1]
+
+
+def test_choices_cached_for_other_kernels_are_not_applied(tmp_path_factory):
+    """Entries under the keys that named neither the kernels nor the default tiles."""
+    old = {f"gfx950/256cu/plan/s0/e8/n8/i{i}": 1 for i in range(24)}
+    got = check(tmp_path_factory, "tuned_plan", dict(MIDDLE, sampling=0, cache=old, costs=[("fuse" + _tile_kernel(4), 0.5)]))
+    assert got["timed"]["best"] == 4 and set(old.items()) <= set(got["cache"].items())
+
+
+def test_the_smallest_workspace_tunes_the_fusion_alone(tmp_path_factory):
+    """Maps, a posterior and an occupancy grid were enough before the step was timed."""
+    got = check(tmp_path_factory, "tuned_plan", dict(MIDDLE, sampling=0, short=True, costs=[("fuse" + _tile_kernel(4), 0.5), ("pipe" + _tile_kernel(1), 0.5)]))
+    assert got["timed"]["best"] == 4
+    assert got["timed"]["kernels"][1] == got["untuned"]["kernels"][1]
