@@ -483,10 +483,11 @@ void psfs_batch_destroy(psfs_batch *batch);
 int psfs_batch_set_tile(psfs_batch *batch, int tile);
 int psfs_batch_get_tile(const psfs_batch *batch);
 
-/* Autotuner: times every fusion tile on this batch (2 warm-up + 5 timed runs
- * each, HIP events on `stream`, blocking) and keeps the fastest. The choice is
- * cached on disk as JSON keyed by device, CU count, sampling and a hash of the
- * shape signature (file: $PSFS_AUTOTUNE_CACHE, else
+/* Autotuner: times the default and every fusion tile on this batch (2 warm-up +
+ * 5 timed runs each, HIP events on `stream`, blocking) and keeps the fastest, the
+ * default where no tile is 2 % faster; *best_tile as psfs_batch_get_tile. The
+ * choice is cached on disk as JSON keyed by device, CU count, revision of the
+ * kernels, sampling and a hash of the shape signature (file: $PSFS_AUTOTUNE_CACHE, else
  * $HOME/.cache/psfs/autotune.json); a cached choice is reused without timing
  * unless force != 0. Tiles never change results, only speed. */
 int psfs_batch_tune(psfs_batch *batch, void *workspace_dev, size_t workspace_bytes, void *stream, int force,

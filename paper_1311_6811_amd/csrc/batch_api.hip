@@ -323,7 +323,7 @@ std::string cache_key(const psfs_batch *b)
         }
     }
     char buf[128];
-    std::snprintf(buf, sizeof(buf), "gfx950/%dcu/chain/s%d/%016llx", b->cus, b->params.sampling,
+    std::snprintf(buf, sizeof(buf), "gfx950/%dcu/chain/r%d/s%d/%016llx", b->cus, kTileRevision, b->params.sampling,
                   static_cast<unsigned long long>(h));
     return buf;
 }
@@ -493,9 +493,9 @@ int psfs_batch_tune(psfs_batch *b, void *workspace_dev, size_t workspace_bytes_,
         std::lock_guard<std::mutex> lock(tune_cache_mutex());
         const auto m = read_tune_cache(path);
         const auto it = m.find(key);
-        if (it != m.end() && it->second >= 0 && it->second < tile_count()) {
+        if (it != m.end() && it->second >= -1 && it->second < tile_count()) {
             if ((rc = psfs_batch_set_tile(b, it->second))) return rc;
-            if (best_tile) *best_tile = it->second;
+            if (best_tile) *best_tile = psfs_batch_get_tile(b);
             return PSFS_OK;
         }
     }
@@ -503,9 +503,11 @@ int psfs_batch_tune(psfs_batch *b, void *workspace_dev, size_t workspace_bytes_,
     hipError_t e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
     if (e != hipSuccess) return hip_fail(e, "hipEventCreate");
-    float best_ms = 1e30f;
-    int best = b->tile;
-    for (int t = 0; t < tile_count() && rc == PSFS_OK; ++t) {
+    // the default (-1) first; a tile replaces it where it is 2 % faster, more than
+    // equal runs differ by
+    float best_ms = 0.0f;
+    int best = -1;
+    for (int t = -1; t < tile_count() && rc == PSFS_OK; ++t) {
         if ((rc = psfs_batch_set_tile(b, t))) break;
         if ((rc = upload_table(b, s))) break;
         for (int w = 0; w < 2 && rc == PSFS_OK; ++w) rc = run_eager(b, workspace_dev, s);
@@ -519,7 +521,7 @@ int psfs_batch_tune(psfs_batch *b, void *workspace_dev, size_t workspace_bytes_,
         if (e != hipSuccess) { rc = hip_fail(e, "hipEventSynchronize"); break; }
         float ms = 0.0f;
         hipEventElapsedTime(&ms, e0, e1);
-        if (ms < best_ms) { best_ms = ms; best = t; }
+        if (t < 0 || ms < (best < 0 ? 0.98f : 1.0f) * best_ms) { best_ms = ms; best = t; }
     }
     hipEventDestroy(e0);
     hipEventDestroy(e1);
@@ -531,7 +533,7 @@ int psfs_batch_tune(psfs_batch *b, void *workspace_dev, size_t workspace_bytes_,
         m[key] = best;
         write_tune_cache(path, m);
     }
-    if (best_tile) *best_tile = best;
+    if (best_tile) *best_tile = psfs_batch_get_tile(b);
     return PSFS_OK;
     PSFS_GUARD_END
 }

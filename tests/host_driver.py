@@ -162,10 +162,7 @@ def tuned_plan(host, arg):
     return out
 
 
-def batch_kernels(host, arg):
-    """Of a batch of these frames (grid, views, image size) on every tile (-1
-    too): the tile that psfs_batch_get_tile reports, the kernels of a run and of
-    the run after a same-shape update."""
+def _batch(host, arg):
     frames = [(S.ring_rig(n, 0.9375 * W, W, H), host.grid(*grid)) for grid, n, W, H in arg["frames"]]
     arr = (host.L.psfs_frame * len(frames))()
     keep = []
@@ -176,6 +173,38 @@ def batch_kernels(host, arg):
         a.posterior_dev = FAKE
     h = C.c_void_p()
     assert host.lib.psfs_batch_create(C.byref(h), C.byref(host.params(arg["sampling"])), len(frames), arr) == 0
+    return h, arr, keep
+
+
+def tuned_batch(host, arg):
+    """As tuned_plan, for a batch; the kernels are those of a run."""
+    out = {}
+    if arg.get("cache"):
+        with open(os.environ["PSFS_AUTOTUNE_CACHE"], "w") as f:
+            json.dump(arg["cache"], f)
+    for name in ("timed", "cached", "untuned"):
+        h, _, _ = _batch(host, arg)
+        nbytes = host.lib.psfs_batch_workspace_bytes(h)
+        best = C.c_int32(-1)
+        if name != "untuned":
+            for part, ms in arg["costs"] if name == "timed" else []:
+                host.dbl.dbl_cost(part.encode(), ms)
+            assert host.lib.psfs_batch_tune(h, FAKE, nbytes, None, 0, C.byref(best)) == 0
+        launched = len(host.launches())
+        assert host.lib.psfs_batch_run(h, FAKE, nbytes, None) == 0
+        out[name] = dict(best=best.value, reported=host.lib.psfs_batch_get_tile(h), launched=launched,
+                         kernels=[k for k, _, _ in host.launches()])
+        host.lib.psfs_batch_destroy(h)
+    with open(os.environ["PSFS_AUTOTUNE_CACHE"]) as f:
+        out["cache"] = json.load(f)
+    return out
+
+
+def batch_kernels(host, arg):
+    """Of a batch of these frames (grid, views, image size) on every tile (-1
+    too): the tile that psfs_batch_get_tile reports, the kernels of a run and of
+    the run after a same-shape update."""
+    h, arr, _keep = _batch(host, arg)
     nbytes = host.lib.psfs_batch_workspace_bytes(h)
     out = []
     for tile in arg.get("tiles") or [*range(-1, host.lib.psfs_tile_count()), -1]:
@@ -185,7 +214,7 @@ def batch_kernels(host, arg):
             host.launches()
             assert host.lib.psfs_batch_run(h, FAKE, nbytes, None) == 0
             runs.append(host.launches())
-            assert host.lib.psfs_batch_update(h, len(frames), arr) == 0
+            assert host.lib.psfs_batch_update(h, len(arr), arr) == 0
         out.append((tile, host.lib.psfs_batch_get_tile(h), *runs))
     host.lib.psfs_batch_destroy(h)
     return out

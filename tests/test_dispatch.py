@@ -97,3 +97,29 @@ def test_the_smallest_workspace_tunes_the_fusion_alone(tmp_path_factory):
     got = check(tmp_path_factory, "tuned_plan", dict(MIDDLE, sampling=0, short=True, costs=[("fuse" + _tile_kernel(4), 0.5), ("pipe" + _tile_kernel(1), 0.5)]))
     assert got["timed"]["best"] == 4
     assert got["timed"]["kernels"][1] == got["untuned"]["kernels"][1]
+
+
+def test_the_batch_tuner_knows_the_default(tmp_path_factory):
+    """Where no tile is clearly faster than the tiles that suit the frames, the
+    batch keeps these, also from the cache."""
+    got = check(tmp_path_factory, "tuned_batch", dict(frames=BATCH, sampling=0, costs=[(_tile_kernel(4), 0.99)]))
+    assert got["timed"]["kernels"] == got["cached"]["kernels"] == got["untuned"]["kernels"]
+    assert got["timed"]["best"] == got["timed"]["reported"] == got["untuned"]["reported"] == 6
+    assert got["timed"]["launched"] > 0 and got["cached"]["launched"] == 0
+
+
+@pytest.mark.parametrize("sampling", [0, 1])
+def test_the_batch_tuner_keeps_a_faster_tile(tmp_path_factory, sampling):
+    for tile in (4, 6):
+        part = "batch_pipe_block" if tile == 6 and sampling == 0 else _tile_kernel(tile)
+        got = check(tmp_path_factory, "tuned_batch", dict(frames=BATCH, sampling=sampling, costs=[(part, 0.5)]))
+        for k in ("timed", "cached"):
+            assert got[k]["best"] == got[k]["reported"] == tile and {tile_of(x) for x in got[k]["kernels"]} == {tile}
+
+
+def test_batch_choices_cached_for_other_kernels_are_not_applied(tmp_path_factory):
+    first = check(tmp_path_factory, "tuned_batch", dict(frames=BATCH, sampling=0, costs=[(_tile_kernel(4), 0.5)]))
+    (key, _), = first["cache"].items()
+    old = {key.replace("/r2", ""): 1}
+    got = check(tmp_path_factory, "tuned_batch", dict(frames=BATCH, sampling=0, costs=[(_tile_kernel(4), 0.5)], cache=old))
+    assert list(old) != [key] and got["timed"]["best"] == 4
