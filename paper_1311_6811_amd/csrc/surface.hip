@@ -37,6 +37,14 @@ constexpr int kScanMin = 4096;                      // more blocks: offsets from
 
 __device__ __forceinline__ uint32_t byte_at(uint32_t w, int b) { return (w >> (8 * b)) & 0xffu; }
 
+// A smoothing launch is as wide as kSmoothWide workgroups at most: an axis of
+// 2^32 lanes or more is refused, which thin grids of many planes reach (1 x 1 x 2^25
+// voxels).
+constexpr int64_t kSmoothWide = int64_t(1) << 20;
+
+// Workgroup of a smoothing launch; those past the last tile have nothing to do.
+__device__ __forceinline__ uint32_t smooth_group() { return blockIdx.y * gridDim.x + blockIdx.x; }
+
 // 3x3x3 mean over the in-grid neighbours and threshold. A wave owns a tile of
 // 64 x-columns (one per lane) by TY rows by TZ planes. It loads the x-windows
 // of the TY + 2 rows by TZ + 2 planes it needs at clamped in-grid addresses, all
@@ -52,7 +60,8 @@ __global__ __launch_bounds__(256) void smooth_kernel(SurfArgs a)
 {
     const uint32_t nxb = (static_cast<uint32_t>(a.nx) + 63) / 64, nyb = (static_cast<uint32_t>(a.ny) + TY - 1) / TY;
     const uint32_t per_z = (nxb * nyb + 3) / 4, nzb = (static_cast<uint32_t>(a.nz) + TZ - 1) / TZ;
-    const uint32_t b = static_cast<uint32_t>(xcd_remap(blockIdx.x, static_cast<int64_t>(per_z) * nzb)), bz = b / per_z;
+    if (smooth_group() >= per_z * nzb) return;
+    const uint32_t b = static_cast<uint32_t>(xcd_remap(smooth_group(), static_cast<int64_t>(per_z) * nzb)), bz = b / per_z;
     // the wave's tile and rows in scalar registers (tile counts are below 2^31)
     const uint32_t tile = (b - bz * per_z) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (tile >= nxb * nyb) return;                                  // whole waves
@@ -144,7 +153,8 @@ __global__ __launch_bounds__(256) void smooth4_kernel(SurfArgs a)
     const uint32_t nx = static_cast<uint32_t>(a.nx), ny = static_cast<uint32_t>(a.ny), nz = static_cast<uint32_t>(a.nz);
     const uint32_t nxb = (nx + 4 * LX - 1) / (4 * LX), nyb = (ny + kRows - 1) / kRows;
     const uint32_t per_z = (nxb * nyb + 3) / 4, nzb = (nz + TZ - 1) / TZ;
-    const uint32_t b = static_cast<uint32_t>(xcd_remap(blockIdx.x, static_cast<int64_t>(per_z) * nzb)), bz = b / per_z;
+    if (smooth_group() >= per_z * nzb) return;
+    const uint32_t b = static_cast<uint32_t>(xcd_remap(smooth_group(), static_cast<int64_t>(per_z) * nzb)), bz = b / per_z;
     const uint32_t tile = (b - bz * per_z) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (tile >= nxb * nyb) return;                      // whole waves
     const uint32_t lane = threadIdx.x & 63, lx = lane % LX, ly = lane / LX;
@@ -459,9 +469,12 @@ hipError_t launch_surface(const SurfArgs &a, hipStream_t s)
     }
     const bool pieces = a.nx % 4 == 0 && reinterpret_cast<uintptr_t>(a.post) % 16 == 0 &&
                         reinterpret_cast<uintptr_t>(a.smoothed) % 16 == 0 && reinterpret_cast<uintptr_t>(a.occ) % 4 == 0;
+    const int64_t nx = a.nx, ny = a.ny, nz = a.nz;
     auto smooth_grid = [&](int span, int rows, int tz) {
-        const int64_t tiles = static_cast<int64_t>((a.nx + span - 1) / span) * ((a.ny + rows - 1) / rows);
-        return dim3(static_cast<unsigned>((tiles + 3) / 4 * ((a.nz + tz - 1) / tz)));
+        const int64_t tiles = ((nx + span - 1) / span) * ((ny + rows - 1) / rows);
+        const int64_t groups = (tiles + 3) / 4 * ((nz + tz - 1) / tz);
+        return dim3(static_cast<unsigned>(groups < kSmoothWide ? groups : kSmoothWide),
+                    static_cast<unsigned>((groups + kSmoothWide - 1) / kSmoothWide));
     };
     if (pieces && a.nx > 128)
         hipLaunchKernelGGL((smooth4_kernel<64, kPieceY, kPieceZ>), smooth_grid(256, kPieceY, kPieceZ), dim3(256), 0, s, a);

@@ -127,6 +127,15 @@ def fusion_kernels(host, arg):
     return out
 
 
+def surface_launches(host, arg):
+    """Kernels of psfs_surface with their grids and workgroups."""
+    plan = host.plan([], host.grid(*arg["grid"]), 0)
+    nbytes = host.lib.psfs_surface_workspace_bytes(plan)
+    host.launches()
+    assert host.lib.psfs_surface(plan, FAKE, FAKE, FAKE, FAKE, 8, FAKE, FAKE, nbytes, None) == 0
+    return host.launches()
+
+
 def _sequence(host, plan, n):
     """Kernels of a fusion and of a one-frame step."""
     host.launches()

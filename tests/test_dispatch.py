@@ -123,3 +123,12 @@ def test_batch_choices_cached_for_other_kernels_are_not_applied(tmp_path_factory
     old = {key.replace("/r2", ""): 1}
     got = check(tmp_path_factory, "tuned_batch", dict(frames=BATCH, sampling=0, costs=[(_tile_kernel(4), 0.5)], cache=old))
     assert list(old) != [key] and got["timed"]["best"] == 4
+
+
+@pytest.mark.parametrize("grid", [(1, 1, 2 ** 25), (1, 1, 2 ** 31 - 1), (2, 32768, 32767), (4, 1, 2 ** 29 - 1), (3, 5, 10 ** 8), (1, 2 ** 30, 1), (60, 1, 2 ** 25)])
+def test_no_axis_of_a_surface_launch_reaches_two_to_the_32(tmp_path_factory, grid):
+    for name, groups, lanes in check(tmp_path_factory, "surface_launches", dict(grid=grid)):
+        assert all(g * b < 2 ** 32 for g, b in zip(groups, lanes)), (name, groups, lanes)
+        assert groups[1] <= 65535 and groups[2] <= 65535
+        if "smooth" in name:                                # 16 voxels or more to a workgroup, few idle ones
+            assert groups[0] * groups[1] <= grid[0] * grid[1] * grid[2] / 2 + 2 ** 20
