@@ -123,8 +123,14 @@ double block_area(const psfs_camera &c, const psfs_grid &grid)
 
 int64_t blocks_16x16x8(const psfs_grid &g)
 {
-    return static_cast<int64_t>((g.nx + 15) / 16) * ((g.ny + 15) / 16) * ((g.nz + 7) / 8);
+    const int64_t nx = g.nx, ny = g.ny, nz = g.nz;
+    return ((nx + 15) / 16) * ((ny + 15) / 16) * ((nz + 7) / 8);
 }
+
+// Grids that are mostly the padding of such blocks (2^22 hold 2^33 voxels): their
+// launches would reach the 2^32 lanes that one axis can have before the column
+// tiles' do (1 x 2^28 x 1 voxels).
+bool blocks_fit(const psfs_grid &g) { return blocks_16x16x8(g) < (int64_t(1) << 22); }
 
 double mean_block_area(const psfs_camera *cams, int n, const psfs_grid &grid)
 {
@@ -150,7 +156,7 @@ double mean_block_area(const psfs_camera *cams, int n, const psfs_grid &grid)
 bool block_pays(const psfs_camera *cams, int n, const psfs_grid &grid, bool step)
 {
     const int64_t blocks = blocks_16x16x8(grid), work = blocks * (n + 4);
-    if (n == 0 || blocks < (step ? 2400 : 1400)) return false;
+    if (n == 0 || blocks < (step ? 2400 : 1400) || !blocks_fit(grid)) return false;
     const double area = mean_block_area(cams, n, grid);
     return static_cast<double>(work) * std::fmin(area, 1000.0) >= (work < 30000 ? 13e6 : 8e6) &&
            area <= (step ? 4000.0 : 5000.0);
@@ -170,7 +176,7 @@ bool small_grid(const psfs_grid &grid)
 bool bilinear_boxes_pay(const psfs_camera *cams, int n, const psfs_grid &grid)
 {
     const double area = mean_block_area(cams, n, grid);
-    return area <= 4200.0 || (area <= 6500.0 && blocks_16x16x8(grid) >= 500);
+    return blocks_fit(grid) && (area <= 4200.0 || (area <= 6500.0 && blocks_16x16x8(grid) >= 500));
 }
 
 // The projection maps the box of the centres into the hull of its 8 projected

@@ -132,3 +132,12 @@ def test_no_axis_of_a_surface_launch_reaches_two_to_the_32(tmp_path_factory, gri
         assert groups[1] <= 65535 and groups[2] <= 65535
         if "smooth" in name:                                # 16 voxels or more to a workgroup, few idle ones
             assert groups[0] * groups[1] <= grid[0] * grid[1] * grid[2] / 2 + 2 ** 20
+
+
+@pytest.mark.parametrize("sampling", [0, 1])
+@pytest.mark.parametrize("grid", [(1, 2 ** 28, 1), (2, 2 ** 28, 1), (8, 2 ** 28 - 1, 1), (1, 2 ** 28, 4), (2 ** 27 - 8, 1, 1), (1, 1, 2 ** 26 - 8)])
+def test_the_default_fuses_what_tile_0_fuses(tmp_path_factory, sampling, grid):
+    """Long rows of few columns, of which a tile of 8 x 32 columns holds twice as many as one of 16 x 16."""
+    for tile, _, name, groups, lanes in check(tmp_path_factory, "fusion_kernels", dict(grid=grid, n=4, W=320, H=240, sampling=sampling)):
+        if tile in (-1, 0):
+            assert groups[0] * lanes[0] < 2 ** 32, (tile, name, groups, lanes)

@@ -37,3 +37,16 @@ def test_surface_of_a_column_of_planes(nx):
     occ = want > 0.3
     assert torch.equal(s.occ.view(nz, nx), occ[:, None].to(torch.uint8).expand(nz, nx))
     assert int(s.count) == nx * int(occ.sum())              # every voxel is on the grid's border
+
+
+@pytest.mark.parametrize("sampling", [psfs.NEAREST, psfs.BILINEAR])
+def test_fusion_of_one_long_row_of_columns(sampling):
+    ny = 2 ** 28
+    P = np.array([[0, 0, 0, 20.0], [0, 2.0 ** -24, 0, 3.0], [0, 0, 0, 1.0]], np.float32)
+    plan = psfs.Plan([S.ring_rig(1, 100.0, 40, 30)[0].with_P(P)], _Grid(1, ny, 1), sampling=sampling)
+    lmap = torch.full((plan.lmap_floats(),), 0.5, device="cuda")
+    post, occ = plan.fuse(lmap)
+    auto = (post[0, ::4096, 0].clone(), int(occ.sum()))
+    plan.set_tile(0)
+    plan.fuse(lmap, post, occ)
+    assert torch.equal(auto[0], post[0, ::4096, 0]) and auto[1] == int(occ.sum()) == ny
