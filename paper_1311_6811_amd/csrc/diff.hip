@@ -165,7 +165,7 @@ __global__ __launch_bounds__(kBlock) void diff_fwd_kernel(DiffArgs a)
     __shared__ __align__(16) float arena[kFwdArena];
     __shared__ PixBox boxes[kMaxViews];
     const Coords q = block_coords<false>(a.nx, a.ny, a.nz);
-    compute_boxes<kFX, kFY, kFZ>(a, q.bi, q.bj, q.kb, kFwdArena, true, boxes);
+    compute_boxes<kFX, kFY, kFZ>(a, q.bi, q.bj, q.kb, kFwdArena, true, true, boxes);
     const double Xd = centre64(a.ox, a.h, q.i), Yd = centre64(a.oy, a.h, q.j);
     float L[kFZ];
 #pragma unroll
@@ -412,7 +412,7 @@ __global__ __launch_bounds__(kBlock) void diff_bwd_kernel(DiffArgs a)
             a.cam_part[static_cast<int64_t>(blockIdx.x) * a.n * 12 + e] = 0.0f;
         return;
     }
-    compute_boxes<kFX, kFY, kFZ>(a, q.bi, q.bj, q.kb, block_hot ? kBoxCap : kGroup, !block_hot, boxes);
+    compute_boxes<kFX, kFY, kFZ>(a, q.bi, q.bj, q.kb, block_hot ? kBoxCap : kGroup, !block_hot, false, boxes);
 
     if (block_hot) {
         float *map_box = arena;

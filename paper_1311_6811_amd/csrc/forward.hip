@@ -274,7 +274,7 @@ __global__ __launch_bounds__(kBoxThreads) void fuse_bilinear_kernel(BilinearArgs
     uint32_t bi, bj, bk;
     octant_tile(static_cast<uint32_t>(xcd_remap(blockIdx.x, nb)), nbx, nby, nbz, bi, bj, bk);
     const int i0 = static_cast<int>(bi) * 16, j0 = static_cast<int>(bj) * 16, k0 = static_cast<int>(bk) * KZ;
-    compute_boxes<16, 16, KZ>(a, i0, j0, k0, kBilArena, true, boxes);
+    compute_boxes<16, 16, KZ>(a, i0, j0, k0, kBilArena, true, true, boxes);
     const int i = i0 + static_cast<int>(threadIdx.x % 16), j = j0 + static_cast<int>(threadIdx.x / 16);
     const double Xd = centre64(a.ox, a.h, i), Yd = centre64(a.oy, a.h, j);
     float L[KZ];
