@@ -99,26 +99,52 @@ size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
 namespace {
 
-// Pixels of view c's box around the 16 x 16 x 8 voxel block in the middle of the
-// grid; a large number when a corner is not in front of the camera.
-double block_area(const psfs_camera &c, const psfs_grid &grid)
+// The projection of the box of extent `size` voxels around the middle of the grid:
+// false when a corner is not in front of the camera.
+bool project_box(const psfs_camera &c, const psfs_grid &grid, const int (&size)[3], double (&lo)[2], double (&hi)[2])
 {
-    const int dims[3] = {grid.nx, grid.ny, grid.nz}, edge[3] = {16, 16, 8};
-    double lo[2] = {0.0, 0.0}, hi[2] = {0.0, 0.0};
+    const int dims[3] = {grid.nx, grid.ny, grid.nz};
     for (int corner = 0; corner < 8; ++corner) {
         double row[3] = {c.P[3], c.P[7], c.P[11]};
         for (int d = 0; d < 3; ++d) {
-            const double x = grid.origin[d] + grid.voxel * (0.5 * dims[d] + ((corner >> d) & 1 ? 0.5 : -0.5) * edge[d]);
+            const double x = grid.origin[d] + grid.voxel * (0.5 * dims[d] + ((corner >> d) & 1 ? 0.5 : -0.5) * size[d]);
             for (int r = 0; r < 3; ++r) row[r] += c.P[4 * r + d] * x;
         }
-        if (!(row[2] > 0.0)) return 1e9;
+        if (!(row[2] > 0.0)) return false;
         for (int r = 0; r < 2; ++r) {
             const double u = row[r] / row[2];
             lo[r] = corner == 0 || u < lo[r] ? u : lo[r];
             hi[r] = corner == 0 || u > hi[r] ? u : hi[r];
         }
     }
+    return true;
+}
+
+// Pixels of view c's box around the 16 x 16 x 8 voxel block in the middle of the
+// grid; a large number when a corner is not in front of the camera.
+double block_area(const psfs_camera &c, const psfs_grid &grid)
+{
+    double lo[2], hi[2];
+    if (!project_box(c, grid, {16, 16, 8}, lo, hi)) return 1e9;
     return std::fmin(1e9, (hi[0] - lo[0] + 4.0) * (hi[1] - lo[1] + 2.0));
+}
+
+// About the part of the grid that the views see: of the box around its
+// projection, what lies in the image, on average (0 for a grid that reaches behind
+// a camera).
+double visible_part(const psfs_camera *cams, int n, const psfs_grid &grid)
+{
+    double sum = 0.0;
+    for (int k = 0; k < n; ++k) {
+        double lo[2], hi[2], part = 1.0;
+        if (!project_box(cams[k], grid, {grid.nx, grid.ny, grid.nz}, lo, hi)) continue;
+        for (int r = 0; r < 2; ++r) {
+            const double in = std::fmin(hi[r], r == 0 ? cams[k].width : cams[k].height) - std::fmax(lo[r], 0.0);
+            part *= in > 0.0 && hi[r] > lo[r] ? in / (hi[r] - lo[r]) : 0.0;
+        }
+        sum += part / n;
+    }
+    return sum;
 }
 
 int64_t blocks_16x16x8(const psfs_grid &g)
@@ -171,12 +197,22 @@ bool small_grid(const psfs_grid &grid)
 // The boxes hold every pixel, the gathers of the column kernel only those that
 // the voxels read: with few voxels per pixel the gathers win. Column kernel against
 // boxes: 80^3 x 8 views of 640x480 (boxes of 3900 pixels for a block of 8 slices)
-// 28 / 26 us, 64^3 x 8 (6000) 18 / 24 us; at 1280x720 112^3 x 8 (5400) 64 / 42 us, 96^3 x 4
-// (5600) 19 / 22 us, 64^3 x 4 (12700) 11 / 19 us.
+// 27 / 19 us, 64^3 x 8 (6000) 17 / 17 us; at 1280x720 112^3 x 8 (5400) 62 / 35 us, 96^3 x 4
+// (5600) 18 / 16 us, 64^3 x 4 (12700) 10 / 17 us.
+// Blocks 16 voxels wide take twice the lanes of a tile 8 wide on grids of at most 8
+// rows: they win where latency counts, not work (3 x 265 x 94 x 16 views 29.4 / 24.0,
+// 6 x 266 x 487 x 2 9.6 / 12.3, 5 x 233 x 233 x 3 8.9 / 10.3). Voxels that no view sees cost
+// the column kernel less (75 x 49 x 48 x 12 views that see an eighth 16.2 / 26.2,
+// 99 x 103 x 116 x 11 a hundredth 38.1 / 32.2, 139 x 124 x 152 x 2 a twelfth 18.5 / 20.6).
 bool bilinear_boxes_pay(const psfs_camera *cams, int n, const psfs_grid &grid)
 {
     const double area = mean_block_area(cams, n, grid);
-    return blocks_fit(grid) && (area <= 4200.0 || (area <= 6500.0 && blocks_16x16x8(grid) >= 500));
+    const int64_t blocks = blocks_16x16x8(grid);
+    if (!blocks_fit(grid) || !(area <= 4200.0 || (area <= 6500.0 && blocks >= 500))) return false;
+    const int64_t wide = ((int64_t(grid.nx) + 15) / 16) * ((int64_t(grid.ny) + 15) / 16);
+    const int64_t narrow = ((int64_t(grid.nx) + 7) / 8) * ((int64_t(grid.ny) + 31) / 32);
+    if (2 * wide > 3 * narrow && (blocks >= 300 || n < 4)) return false;
+    return n == 0 || (blocks >= 256 && n > 2) || visible_part(cams, n, grid) >= 0.2;
 }
 
 // The projection maps the box of the centres into the hull of its 8 projected

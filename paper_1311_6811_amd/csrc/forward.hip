@@ -312,7 +312,8 @@ constexpr TileCfg kTiles[] = {
 constexpr int kBlockTile = 6;
 // Bilinear blocks are 8 voxels deep when at least kBilBlocks of them (two per
 // CU) cover the grid, else 4 or 2 deep: on a 64^3 grid, whose 128 blocks of 8
-// would use half of the CUs, 2 deep takes 8.6 us.
+// would use half of the CUs, 2 deep takes 8.6 us. Grids of few slices take no
+// deeper ones than hold them.
 constexpr int64_t kBilBlocks = 512;
 
 hipError_t launch_fuse_block(const FuseArgs &a, hipStream_t s)
@@ -386,7 +387,7 @@ hipError_t launch_fuse_bilinear(const FuseArgs &f, hipStream_t s)
     a.tau = f.tau;
     const int64_t columns = static_cast<int64_t>((a.nx + 15) / 16) * ((a.ny + 15) / 16);
     auto blocks = [&](int kz) { return columns * ((a.nz + kz - 1) / kz); };
-    const int kz = blocks(8) >= kBilBlocks ? 8 : blocks(4) >= kBilBlocks ? 4 : 2;
+    const int kz = a.nz > 4 && blocks(8) >= kBilBlocks ? 8 : a.nz > 2 && blocks(4) >= kBilBlocks ? 4 : 2;
     const dim3 grid(static_cast<unsigned>(blocks(kz))), block(kBoxThreads);
     if (grid.x == 0) return hipSuccess;
     switch (kz) {

@@ -15,6 +15,8 @@ BLOCK = 6
     (1, 1, 1, 1, "ring", 320, 240),                  # one voxel
     (17, 16, 9, 16, "ring", 320, 240),               # 2 deep, all views
     (61, 53, 47, 5, "ring", 321, 243),               # 2 deep, ragged
+    (300, 290, 2, 4, "ring", 320, 240),              # 2 deep, flat
+    (301, 290, 3, 4, "ring", 320, 240),              # 4 deep, flat
     (96, 90, 64, 4, "ring", 320, 240),               # 4 deep
     (100, 90, 64, 3, "inside", 320, 240),            # 4 deep, voxels behind the cameras
     (110, 81, 95, 16, "close", 643, 477),            # 4 deep, all views, most of them looking past the grid

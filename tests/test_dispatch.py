@@ -141,3 +141,20 @@ def test_the_default_fuses_what_tile_0_fuses(tmp_path_factory, sampling, grid):
     for tile, _, name, groups, lanes in check(tmp_path_factory, "fusion_kernels", dict(grid=grid, n=4, W=320, H=240, sampling=sampling)):
         if tile in (-1, 0):
             assert groups[0] * lanes[0] < 2 ** 32, (tile, name, groups, lanes)
+
+
+@pytest.mark.parametrize("grid,n,W,H,side,kernel", [
+    ((700, 700, 1), 6, 640, 480, 2.0, "fuse_bilinear_kernelILi2E"),      # no deeper than the grid
+    ((700, 700, 2), 6, 640, 480, 2.0, "fuse_bilinear_kernelILi2E"),
+    ((700, 700, 3), 6, 640, 480, 2.0, "fuse_bilinear_kernelILi4E"),
+    ((700, 700, 5), 6, 640, 480, 2.0, "fuse_bilinear_kernelILi8E"),
+    ((128, 128, 128), 8, 640, 480, 2.0, "fuse_bilinear_kernelILi8E"),
+    ((5, 233, 233), 3, 320, 240, 2.0, _tile_kernel(0)),                  # blocks twice as wide as the grid: work
+    ((2, 300, 300), 8, 320, 240, 2.0, _tile_kernel(0)),
+    ((3, 100, 90), 12, 320, 240, 2.0, "fuse_bilinear_kernel"),           # latency
+    ((67, 56, 55), 11, 114, 86, 4.9, _tile_kernel(0)),                   # hardly in view
+    ((67, 56, 55), 11, 114, 86, 2.0, "fuse_bilinear_kernel"),
+])
+def test_bilinear_boxes_where_they_pay(tmp_path_factory, grid, n, W, H, side, kernel):
+    runs = check(tmp_path_factory, "fusion_kernels", dict(grid=[*grid, side], n=n, W=W, H=H, sampling=1))
+    assert kernel in runs[0][2]
