@@ -194,6 +194,12 @@ bool small_grid(const psfs_grid &grid)
     return batch_bricks(grid.nx, grid.ny, grid.nz, kNarrowTile, false) <= 512;
 }
 
+// Grids that give the CUs more than two workgroups of the two- and four-frame steps.
+bool many_waves(const psfs_grid &grid)
+{
+    return batch_bricks(grid.nx, grid.ny, grid.nz, kWideTile, false) > 512;
+}
+
 // The boxes hold every pixel, the gathers of the column kernel only those that
 // the voxels read: with few voxels per pixel the gathers win. Column kernel against
 // boxes: 80^3 x 8 views of 640x480 (boxes of 3900 pixels for a block of 8 slices)
@@ -222,12 +228,11 @@ bool bilinear_boxes_pay(const psfs_camera *cams, int n, const psfs_grid &grid)
 // kept free at the image's border.
 bool grid_inside(const ViewGeom &g, const psfs_grid &grid)
 {
-    const int dims[3] = {grid.nx, grid.ny, grid.nz}, pad[3] = {32, 32, 8};      // largest tile along each axis
+    const int dims[3] = {grid.nx, grid.ny, grid.nz};
     double lo[3], hi[3];
     for (int d = 0; d < 3; ++d) {
-        const int64_t n = (static_cast<int64_t>(dims[d]) + pad[d] - 1) / pad[d] * pad[d];
         lo[d] = grid.origin[d] + grid.voxel * 0.5;
-        hi[d] = grid.origin[d] + grid.voxel * (static_cast<double>(n) - 0.5);
+        hi[d] = grid.origin[d] + grid.voxel * (static_cast<double>(dims[d]) - 0.5);
     }
     for (int corner = 0; corner < 8; ++corner) {
         const double X[3] = {corner & 1 ? hi[0] : lo[0], corner & 2 ? hi[1] : lo[1], corner & 4 ? hi[2] : lo[2]};
@@ -414,6 +419,7 @@ void fill_geometry(const psfs_plan *p, int sampling, FuseArgs &a)
         g.map_off = map_offset(p, k);
         if (sampling == PSFS_NEAREST && p->has_grid && grid_inside(g, p->grid)) a.inside |= 1u << k;
     }
+    if (sampling == PSFS_NEAREST && p->has_grid && many_waves(p->grid)) a.inside |= kSkipUnseen;
     a.nx = p->grid.nx;
     a.ny = p->grid.ny;
     a.nz = p->grid.nz;

@@ -19,15 +19,17 @@ bool finite_all(const float *v, int n);
 int check_device();
 int64_t padded_pixels(int width, int height);
 size_t align256(size_t x);
-// Whether every voxel centre of the grid, and every phantom one of the tiles that
-// reach past its edge, projects into view g (nearest sampling: P pre-offset)
-// with room for the FP32 rounding of its projection.
+// Whether every voxel centre of the grid projects into view g (nearest sampling:
+// P pre-offset) with room for the FP32 rounding of its projection. (The column
+// kernels' lanes past the grid's edge take its last voxels' place.)
 bool grid_inside(const ViewGeom &g, const psfs_grid &grid);
 // Whether the block tile is the better one for the one-frame nearest fusion, and
 // boxes staged in LDS for the bilinear fusion.
 bool block_pays(const psfs_camera *cams, int n, const psfs_grid &grid, bool step);
 constexpr int kNarrowTile = 2, kShallowTile = 3;    // 8 x 16 columns of 4 voxels, 8 x 32 of 2
+constexpr int kWideTile = 4;                        // 32 x 8 of 4: the two- and four-frame steps
 bool small_grid(const psfs_grid &grid);
+bool many_waves(const psfs_grid &grid);
 bool bilinear_boxes_pay(const psfs_camera *cams, int n, const psfs_grid &grid);
 
 // Part of the autotuners' cache keys: raised when the kernel behind a tile changes,

@@ -1,6 +1,8 @@
 // Device helpers shared by the forward and differentiable kernels.
 #pragma once
 
+#include <type_traits>
+
 #include "psfs_internal.h"
 
 namespace psfs {
@@ -600,24 +602,17 @@ __device__ __forceinline__ double centre64(float o, float h, int i)
 
 // Byte offsets (pixel y W + x times SCALE) of the pixels that a lane's KZ voxels
 // (depths Z[kk], projection rows ax, bx, cx at their column) read in view g;
-// 0xFFFFFFFF outside the image. Returns whether every voxel of the wave is
-// known to be inside, so that no offset is 0xFFFFFFFF.
-// `inside`: the host found the whole grid inside this view (grid_inside).
-// Otherwise the wave tests its segments' ends: with both depths positive the
-// projection maps a segment into the segment between its projected ends, so
-// ends at least 1/64 px inside the image (in nearest-pixel coordinates u + 1/2,
-// v + 1/2: the P rows are pre-offset) have every voxel between them inside, the
-// FP32 error of a projection being ~1e-4 px; phantom lanes past the grid edge
-// count like any other. Only if one is not inside is each voxel tested. Both
-// ways pick the same pixel: inside the image truncation is the floor.
-// (A test of the wave's box by its lanes before the loop read the views'
-// matrices lane by lane: 5 us of the 20 us fusion at 128^3 x 8 views, 12 of 211
-// at 256^3 x 12, where testing every voxel of every view takes 228.)
+// 0xFFFFFFFF outside the image. `inside`: the host found the whole grid inside
+// this view (grid_inside), so that truncation is the floor; otherwise each voxel
+// is tested. (Testing every voxel of every view: 256^3 x 12 228 us against 199.
+// Two finer tests of a wave cost more than they save: of its box by its lanes before
+// the loop, 5 us of the 20 us fusion at 128^3 x 8 views, and of its segments' ends in
+// each view that is not inside, 40^3 x 14 views 7.1 -> 8.4 us, 128^3 x 8 17.9 -> 18.2,
+// 256^3 of four times the images' extent the same.)
 template <int KZ, uint32_t SCALE>
-__device__ __forceinline__ bool nearest_offsets(const ViewGeom &g, float ax, float bx, float cx, const float (&Z)[KZ],
+__device__ __forceinline__ void nearest_offsets(const ViewGeom &g, float ax, float bx, float cx, const float (&Z)[KZ],
                                                 bool inside, uint32_t (&off)[KZ])
 {
-    constexpr float kMargin = 1.0f / 64.0f;
     const uint32_t W = static_cast<uint32_t>(g.W), H = static_cast<uint32_t>(g.H);
     float c[KZ], u[KZ], w[KZ];
 #pragma unroll
@@ -626,14 +621,6 @@ __device__ __forceinline__ bool nearest_offsets(const ViewGeom &g, float ax, flo
         const float r = __builtin_amdgcn_rcpf(c[kk]);
         u[kk] = fmaf(g.P[2], Z[kk], ax) * r;
         w[kk] = fmaf(g.P[6], Z[kk], bx) * r;
-    }
-    if (!inside) {
-        const float ue = static_cast<float>(g.W) - kMargin, we = static_cast<float>(g.H) - kMargin;
-        bool ok = true;                             // NaN fails every comparison
-#pragma unroll
-        for (int kk = 0; kk < KZ; kk += KZ - 1)
-            ok = ok && c[kk] > 0.0f && u[kk] >= kMargin && u[kk] <= ue && w[kk] >= kMargin && w[kk] <= we;
-        inside = __all(ok);
     }
     if (inside) {
 #pragma unroll
@@ -647,7 +634,16 @@ __device__ __forceinline__ bool nearest_offsets(const ViewGeom &g, float ax, flo
             off[kk] = ok ? (__umul24(static_cast<uint32_t>(y), W) + static_cast<uint32_t>(x)) * SCALE : 0xFFFFFFFFu;
         }
     }
-    return inside;
+}
+
+// Whether no voxel of the wave is seen by a view (offsets of nearest_offsets).
+template <int KZ>
+__device__ __forceinline__ bool unseen(const uint32_t (&off)[KZ])
+{
+    bool seen = false;
+#pragma unroll
+    for (int kk = 0; kk < KZ; ++kk) seen = seen || off[kk] != 0xFFFFFFFFu;
+    return !__any(seen);
 }
 
 // Eq. 3-9 for one lane's column segment of KZ voxels, (i, j, k0..k0+KZ-1):
@@ -657,17 +653,18 @@ __device__ __forceinline__ bool nearest_offsets(const ViewGeom &g, float ax, flo
 // order is fixed and the fast and checked nearest paths pick the same pixel,
 // so every lane layout and work decomposition produces the same bits.
 // views(v) returns the ViewGeom of view v (P pre-offset by half of row 2 for
-// nearest sampling). The lanes of a wave form a TX x (64/TX) slab of columns.
+// nearest sampling). The lanes of a wave form a TX x (64/TX) slab of columns; what
+// reaches past the grid's edge projects as the last voxel of its row does.
 template <int TX, int KZ, int SAMPLING, class Views>
 __device__ __forceinline__ void fuse_column(const Views &views, int n, const float *lmap, const GridDesc &a, int i,
                                             int j, int k0, float L0, float tau, float *post, uint8_t *occ)
 {
-    const float X = a.ox + a.h * (static_cast<float>(i) + 0.5f);
-    const float Y = a.oy + a.h * (static_cast<float>(j) + 0.5f);
+    const float X = a.ox + a.h * (static_cast<float>(min(i, a.nx - 1)) + 0.5f);
+    const float Y = a.oy + a.h * (static_cast<float>(min(j, a.ny - 1)) + 0.5f);
     float Z[KZ], L[KZ];
 #pragma unroll
     for (int kk = 0; kk < KZ; ++kk) {
-        Z[kk] = a.oz + a.h * (static_cast<float>(k0 + kk) + 0.5f);
+        Z[kk] = a.oz + a.h * (static_cast<float>(min(k0 + kk, a.nz - 1)) + 0.5f);
         L[kk] = L0;
     }
 
@@ -799,12 +796,12 @@ __device__ __forceinline__ void fuse_column_pair(const Views &views, int n, cons
                                                  int i, int j, int k0, float L0, float tau, float *post_a,
                                                  uint8_t *occ_a, float *post_b, uint8_t *occ_b, float *wave_stage)
 {
-    const float X = a.ox + a.h * (static_cast<float>(i) + 0.5f);
-    const float Y = a.oy + a.h * (static_cast<float>(j) + 0.5f);
+    const float X = a.ox + a.h * (static_cast<float>(min(i, a.nx - 1)) + 0.5f);
+    const float Y = a.oy + a.h * (static_cast<float>(min(j, a.ny - 1)) + 0.5f);
     float Z[KZ], La[KZ], Lb[KZ];
 #pragma unroll
     for (int kk = 0; kk < KZ; ++kk) {
-        Z[kk] = a.oz + a.h * (static_cast<float>(k0 + kk) + 0.5f);
+        Z[kk] = a.oz + a.h * (static_cast<float>(min(k0 + kk, a.nz - 1)) + 0.5f);
         La[kk] = L0;
         Lb[kk] = L0;
     }
@@ -812,27 +809,45 @@ __device__ __forceinline__ void fuse_column_pair(const Views &views, int n, cons
     const int lane = static_cast<int>(threadIdx.x & 63);
     const int pos = quad_lane_pos(lane);
     const int i_lo = i - (pos % TX), j_lo = j - (pos / TX);
-    for (int v = 0; v < n; ++v) {
-        const ViewGeom &g = views(v);
-        const float2 *map = reinterpret_cast<const float2 *>(lmap2) + g.map_off;
-        const float ax = fmaf(g.P[0], X, fmaf(g.P[1], Y, g.P[3]));
-        const float bx = fmaf(g.P[4], X, fmaf(g.P[5], Y, g.P[7]));
-        const float cx = fmaf(g.P[8], X, fmaf(g.P[9], Y, g.P[11]));
-        uint32_t pix[KZ];
-        float2 val[KZ];
-        if (nearest_offsets<KZ, 1>(g, ax, bx, cx, Z, (a.inside & (1u << v)) != 0, pix)) {
+    // On grids of enough workgroups to hide the test, a wave passes over the views
+    // that see none of its voxels (kSkipUnseen; two frames of 256^3 of four times the
+    // images' extent 118 -> 112 us, but of 24^3 x 12 views 14.0 -> 14.6).
+    auto add_views = [&](auto skip) {
+        constexpr bool SKIP = decltype(skip)::value;
+        for (int v = 0; v < n; ++v) {
+            const ViewGeom &g = views(v);
+            const float2 *map = reinterpret_cast<const float2 *>(lmap2) + g.map_off;
+            const float ax = fmaf(g.P[0], X, fmaf(g.P[1], Y, g.P[3]));
+            const float bx = fmaf(g.P[4], X, fmaf(g.P[5], Y, g.P[7]));
+            const float cx = fmaf(g.P[8], X, fmaf(g.P[9], Y, g.P[11]));
+            const bool inside = (a.inside & (1u << v)) != 0;
+            const uint32_t pixels = static_cast<uint32_t>(g.W) * static_cast<uint32_t>(g.H);
+            uint32_t off[KZ];
+            float2 val[KZ];
+            if (pixels < (1u << 29)) {
+                // raw buffer loads with 32-bit byte offsets, as fuse_column
+                nearest_offsets<KZ, 8>(g, ax, bx, cx, Z, inside, off);
+                if (SKIP && !inside && unseen(off)) continue;
+                const __amdgpu_buffer_rsrc_t rsrc = map_rsrc(reinterpret_cast<const float *>(map), pixels * 8u);
 #pragma unroll
-            for (int kk = 0; kk < KZ; ++kk) val[kk] = map[pix[kk]];
-        } else {
+                for (int kk = 0; kk < KZ; ++kk)
+                    val[kk] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, static_cast<int>(off[kk]), 0, 0));
+            } else {
+                nearest_offsets<KZ, 1>(g, ax, bx, cx, Z, inside, off);
 #pragma unroll
-            for (int kk = 0; kk < KZ; ++kk) val[kk] = pix[kk] != 0xFFFFFFFFu ? map[pix[kk]] : make_float2(0.0f, 0.0f);
+                for (int kk = 0; kk < KZ; ++kk) val[kk] = off[kk] != 0xFFFFFFFFu ? map[off[kk]] : make_float2(0.0f, 0.0f);
+            }
+#pragma unroll
+            for (int kk = 0; kk < KZ; ++kk) {
+                La[kk] += val[kk].x;
+                Lb[kk] += val[kk].y;
+            }
         }
-#pragma unroll
-        for (int kk = 0; kk < KZ; ++kk) {
-            La[kk] += val[kk].x;
-            Lb[kk] += val[kk].y;
-        }
-    }
+    };
+    if (a.inside & kSkipUnseen)
+        add_views(std::true_type{});
+    else
+        add_views(std::false_type{});
     // A wave whose 32 x 2 x 4 voxels all lie in the grid regroups both frames'
     // outputs through LDS and stores 16-byte pieces of rows, as fuse_column_quad
     // does.
@@ -894,12 +909,12 @@ __device__ __forceinline__ void fuse_column_quad(const Views &views, int n, cons
                                                  int i, int j, int k0, float L0, float tau, float *const (&post)[4],
                                                  uint8_t *const (&occ)[4], float *wave_stage)
 {
-    const float X = a.ox + a.h * (static_cast<float>(i) + 0.5f);
-    const float Y = a.oy + a.h * (static_cast<float>(j) + 0.5f);
+    const float X = a.ox + a.h * (static_cast<float>(min(i, a.nx - 1)) + 0.5f);
+    const float Y = a.oy + a.h * (static_cast<float>(min(j, a.ny - 1)) + 0.5f);
     float Z[KZ], L[KZ][4];
 #pragma unroll
     for (int kk = 0; kk < KZ; ++kk) {
-        Z[kk] = a.oz + a.h * (static_cast<float>(k0 + kk) + 0.5f);
+        Z[kk] = a.oz + a.h * (static_cast<float>(min(k0 + kk, a.nz - 1)) + 0.5f);
 #pragma unroll
         for (int f = 0; f < 4; ++f) L[kk][f] = L0;
     }
@@ -907,30 +922,40 @@ __device__ __forceinline__ void fuse_column_quad(const Views &views, int n, cons
     const int lane = static_cast<int>(threadIdx.x & 63);
     const int pos = quad_lane_pos(lane);
     const int i_lo = i - (pos % TX), j_lo = j - (pos / TX);
-    for (int v = 0; v < n; ++v) {
-        const ViewGeom &g = views(v);
-        // raw buffer loads with 32-bit byte offsets (the host takes this path
-        // only when every view's quad map is below 4 GiB); an offset past
-        // the end returns 0, which is what a voxel-view outside its image adds
-        const __amdgpu_buffer_rsrc_t rsrc = map_rsrc(
-            lmap4 + 4 * g.map_off, static_cast<uint32_t>(g.W) * static_cast<uint32_t>(g.H) * 16u);
-        const float ax = fmaf(g.P[0], X, fmaf(g.P[1], Y, g.P[3]));
-        const float bx = fmaf(g.P[4], X, fmaf(g.P[5], Y, g.P[7]));
-        const float cx = fmaf(g.P[8], X, fmaf(g.P[9], Y, g.P[11]));
-        uint32_t off[KZ];
-        nearest_offsets<KZ, 16>(g, ax, bx, cx, Z, (a.inside & (1u << v)) != 0, off);
-        f32x4 val[KZ];
+    // as fuse_column_pair (four frames of 160^3 x 8 views that mostly look past it 65.3 -> 61.3 us)
+    auto add_views = [&](auto skip) {
+        constexpr bool SKIP = decltype(skip)::value;
+        for (int v = 0; v < n; ++v) {
+            const ViewGeom &g = views(v);
+            // raw buffer loads with 32-bit byte offsets (the host takes this path
+            // only when every view's quad map is below 4 GiB); an offset past
+            // the end returns 0, which is what a voxel-view outside its image adds
+            const __amdgpu_buffer_rsrc_t rsrc = map_rsrc(
+                lmap4 + 4 * g.map_off, static_cast<uint32_t>(g.W) * static_cast<uint32_t>(g.H) * 16u);
+            const float ax = fmaf(g.P[0], X, fmaf(g.P[1], Y, g.P[3]));
+            const float bx = fmaf(g.P[4], X, fmaf(g.P[5], Y, g.P[7]));
+            const float cx = fmaf(g.P[8], X, fmaf(g.P[9], Y, g.P[11]));
+            uint32_t off[KZ];
+            const bool inside = (a.inside & (1u << v)) != 0;
+            nearest_offsets<KZ, 16>(g, ax, bx, cx, Z, inside, off);
+            if (SKIP && !inside && unseen(off)) continue;
+            f32x4 val[KZ];
 #pragma unroll
-        for (int kk = 0; kk < KZ; ++kk)
-            val[kk] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, static_cast<int>(off[kk]), 0, 0));
+            for (int kk = 0; kk < KZ; ++kk)
+                val[kk] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, static_cast<int>(off[kk]), 0, 0));
 #pragma unroll
-        for (int kk = 0; kk < KZ; ++kk) {
-            L[kk][0] += val[kk].x;
-            L[kk][1] += val[kk].y;
-            L[kk][2] += val[kk].z;
-            L[kk][3] += val[kk].w;
+            for (int kk = 0; kk < KZ; ++kk) {
+                L[kk][0] += val[kk].x;
+                L[kk][1] += val[kk].y;
+                L[kk][2] += val[kk].z;
+                L[kk][3] += val[kk].w;
+            }
         }
-    }
+    };
+    if (a.inside & kSkipUnseen)
+        add_views(std::true_type{});
+    else
+        add_views(std::false_type{});
     // A wave whose 32 x 2 x KZ voxels all lie in the grid regroups its outputs
     // through LDS so that each store instruction writes 16-byte pieces of rows
     // (8 rows of 32 posteriors, or 4 frames x 8 rows of 32 occupancy bytes): one

@@ -52,10 +52,14 @@ struct ViewGeom {
     int64_t map_off;
 };
 
+// GridDesc::inside and FuseArgs::inside: bit v where the whole grid is inside view v
+// (nearest sampling; grid_inside), and kSkipUnseen (two- and four-frame steps).
+constexpr uint32_t kSkipUnseen = 1u << 31;
+
 struct GridDesc {
     int nx, ny, nz;
     float ox, oy, oz, h;                // grid origin (corner) and voxel edge
-    uint32_t inside;                    // bit v: the whole grid is inside view v (grid_inside)
+    uint32_t inside;
 };
 
 struct FuseArgs {
@@ -67,7 +71,7 @@ struct FuseArgs {
     float ox, oy, oz, h;                // grid origin (corner) and voxel edge
     float L0;                           // logit(prior)
     float tau;                          // threshold on the posterior
-    uint32_t inside;                    // bit v: the whole grid is inside view v (nearest; grid_inside)
+    uint32_t inside;
 };
 
 // Bilinear fusion from staged pixel boxes: FuseArgs with the camera matrices

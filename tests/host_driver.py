@@ -136,6 +136,35 @@ def surface_launches(host, arg):
     return host.launches()
 
 
+def inside(host, arg):
+    """For random rigs and grids: what the host says of "the whole grid is inside
+    the view", and what FP32 projections of every voxel centre say, as the kernels
+    form them. Returns [said, and how many centres fall outside]."""
+    class ViewGeom(C.Structure):
+        _fields_ = [("P", C.c_float * 12), ("W", C.c_int32), ("H", C.c_int32), ("map_off", C.c_int64)]
+    f = host.lib._ZN4psfs4host11grid_insideERKNS_8ViewGeomERK9psfs_grid
+    f.restype = C.c_bool
+    rng = np.random.default_rng(arg["seed"])
+    out = []
+    for _ in range(arg["count"]):
+        dims = rng.integers(1, 40, 3)
+        grid = host.grid(*[int(d) for d in dims], side=float(rng.uniform(0.5, 6.0)))
+        W, H = (int(x) for x in rng.choice([(320, 240), (641, 479), (65535, 900)]))
+        cam = S.ring_rig(8, 0.9375 * W * rng.uniform(0.5, 1.5), W, H, float(rng.uniform(1.5, 6.0)))[int(rng.integers(8))]
+        P = np.asarray(cam.P, np.float64).reshape(3, 4)
+        P[:2] += 0.5 * P[2]
+        g = ViewGeom(tuple(P.astype(np.float32).reshape(12).tolist()), W, H, 0)
+        P = np.array(list(g.P), np.float32).reshape(3, 4)
+        x, y, z = (np.float32(grid.origin[d]) + np.float32(grid.voxel) * (np.arange(dims[d]).astype(np.float32) + np.float32(0.5))
+                   for d in range(3))
+        rows = [P[r, 0] * x[None, None, :] + (P[r, 1] * y[None, :, None] + P[r, 3]) + P[r, 2] * z[:, None, None] for r in range(3)]
+        with np.errstate(divide="ignore", invalid="ignore"):
+            u, v = rows[0] / rows[2], rows[1] / rows[2]
+        seen = (rows[2] > 0) & (u >= 0) & (u < W) & (v >= 0) & (v < H)
+        out.append((bool(f(C.byref(g), C.byref(grid))), int((~seen).sum())))
+    return out
+
+
 def _sequence(host, plan, n):
     """Kernels of a fusion and of a one-frame step."""
     host.launches()

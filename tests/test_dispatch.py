@@ -158,3 +158,12 @@ def test_the_default_fuses_what_tile_0_fuses(tmp_path_factory, sampling, grid):
 def test_bilinear_boxes_where_they_pay(tmp_path_factory, grid, n, W, H, side, kernel):
     runs = check(tmp_path_factory, "fusion_kernels", dict(grid=[*grid, side], n=n, W=W, H=H, sampling=1))
     assert kernel in runs[0][2]
+
+
+def test_the_views_that_hold_the_whole_grid(tmp_path_factory):
+    """Of the grid itself, however far the tiles reach past its edge; never of a view
+    that misses a voxel."""
+    got = check(tmp_path_factory, "inside", dict(seed=3, count=400))
+    assert not [missed for said, missed in got if said and missed]
+    held = [said for said, missed in got if not missed]
+    assert len(held) > 100 and sum(held) > 0.95 * len(held)
