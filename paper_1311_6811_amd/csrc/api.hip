@@ -2,6 +2,7 @@
 // kernel launches behind the C ABI of psfs.h. Every entry point validates its
 // arguments before enqueueing anything and never lets an exception escape.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -23,6 +24,20 @@ struct CameraMail {
     int device = -1;
 };
 
+// What the launches of a plan follow from its cameras, grid and sampling: found
+// by the first call that needs it (rules()), forgotten when one of them is set.
+// One word, so that threads which use a plan together find the same.
+struct PlanRules {
+    std::atomic<uint64_t> word{0};
+    PlanRules() = default;
+    PlanRules(const PlanRules &o) : word(o.word.load()) {}
+    PlanRules &operator=(const PlanRules &o)
+    {
+        word = o.word.load();
+        return *this;
+    }
+};
+
 struct psfs_plan {
     int n = -1;                                     // -1: cameras not set
     psfs_camera cams[PSFS_MAX_VIEWS];
@@ -35,6 +50,7 @@ struct psfs_plan {
     uint32_t *check = nullptr;                      // input-check flags (caller's device word), or off
     int tile = -1, step_tile = -1;                  // of a fusion alone and of a one-frame step; -1: launch_tile
     CameraMail mail;
+    mutable PlanRules rules;
 };
 
 namespace psfs {
@@ -400,26 +416,72 @@ int enqueue_likelihood(const psfs_plan *p, const uint8_t *const *images, float *
     return PSFS_OK;
 }
 
+ViewGeom view_geometry(const psfs_plan *p, int k, int sampling)
+{
+    ViewGeom g;
+    const float *P = p->cams[k].P;
+    for (int e = 0; e < 12; ++e) g.P[e] = P[e];
+    if (sampling == PSFS_NEAREST) {
+        // floor((row0 + row2/2).X / row2.X) = floor(u + 1/2)
+        for (int c = 0; c < 4; ++c) {
+            g.P[c] = static_cast<float>(static_cast<double>(P[c]) + 0.5 * P[8 + c]);
+            g.P[4 + c] = static_cast<float>(static_cast<double>(P[4 + c]) + 0.5 * P[8 + c]);
+        }
+    }
+    g.W = p->cams[k].width;
+    g.H = p->cams[k].height;
+    g.map_off = map_offset(p, k);
+    return g;
+}
+
+struct Rules {
+    uint32_t inside;                                // FuseArgs::inside
+    int tile, step_tile;
+};
+
+// The views that hold the grid, and the tiles for its grid and rig, of a fusion and
+// of a step (beside a frame's likelihood). Of the column tiles the
+// 128-lane one pads ragged grids the least and leaves the shortest last round:
+// over 90 shapes 1.08 times as fast as tile 0 in fusions (80^3 x 8 views 9.4 / 7.0 us,
+// 112^3 x 8 17.3 / 14.5, 256^3 x 12 201 / 199.5), 1.04 times in steps (0.97 to 1.12;
+// 128^3 x 8, which neither pads, 27.9 / 28.4).
+// Grids that give the CUs two of its workgroups at most take half as many voxels
+// per lane (64^3 x 12: 6.7 / 5.8 us; 80^3 x 8: 7.0 / 8.5).
+Rules find_rules(const psfs_plan *p)
+{
+    Rules r{0, default_tile(), default_tile()};
+    if (p->params.sampling != PSFS_NEAREST) {
+        if (bilinear_boxes_pay(p->cams, p->n, p->grid)) r.tile = block_tile();
+        return r;
+    }
+    for (int k = 0; k < p->n; ++k)
+        if (grid_inside(view_geometry(p, k, PSFS_NEAREST), p->grid)) r.inside |= 1u << k;
+    if (many_waves(p->grid)) r.inside |= kSkipUnseen;
+    const int column = small_grid(p->grid) ? kShallowTile : kNarrowTile;
+    r.tile = block_pays(p->cams, p->n, p->grid, false) ? block_tile() : column;
+    r.step_tile = block_pays(p->cams, p->n, p->grid, true) ? block_tile() : column;
+    return r;
+}
+
+// The rules of a plan with cameras and a grid. (Found in every call they cost its
+// host side 0.3 us of 0.7 with 8 views and 0.5 of 0.9 with 16.)
+Rules rules(const psfs_plan *p)
+{
+    constexpr uint64_t kFound = uint64_t(1) << 63;
+    uint64_t w = p->rules.word.load(std::memory_order_relaxed);
+    if (!w) {
+        const Rules r = find_rules(p);
+        w = kFound | static_cast<uint64_t>(r.inside) | static_cast<uint64_t>(r.tile) << 32 | static_cast<uint64_t>(r.step_tile) << 40;
+        p->rules.word.store(w, std::memory_order_relaxed);
+    }
+    return Rules{static_cast<uint32_t>(w), static_cast<int>(w >> 32 & 0xff), static_cast<int>(w >> 40 & 0xff)};
+}
+
 void fill_geometry(const psfs_plan *p, int sampling, FuseArgs &a)
 {
     a.n = p->n;
-    for (int k = 0; k < p->n; ++k) {
-        ViewGeom &g = a.view[k];
-        const float *P = p->cams[k].P;
-        for (int e = 0; e < 12; ++e) g.P[e] = P[e];
-        if (sampling == PSFS_NEAREST) {
-            // floor((row0 + row2/2).X / row2.X) = floor(u + 1/2)
-            for (int c = 0; c < 4; ++c) {
-                g.P[c] = static_cast<float>(static_cast<double>(P[c]) + 0.5 * P[8 + c]);
-                g.P[4 + c] = static_cast<float>(static_cast<double>(P[4 + c]) + 0.5 * P[8 + c]);
-            }
-        }
-        g.W = p->cams[k].width;
-        g.H = p->cams[k].height;
-        g.map_off = map_offset(p, k);
-        if (sampling == PSFS_NEAREST && p->has_grid && grid_inside(g, p->grid)) a.inside |= 1u << k;
-    }
-    if (sampling == PSFS_NEAREST && p->has_grid && many_waves(p->grid)) a.inside |= kSkipUnseen;
+    for (int k = 0; k < p->n; ++k) a.view[k] = view_geometry(p, k, sampling);
+    if (sampling == PSFS_NEAREST && p->has_grid) a.inside = rules(p).inside;
     a.nx = p->grid.nx;
     a.ny = p->grid.ny;
     a.nz = p->grid.nz;
@@ -432,22 +494,11 @@ void fill_geometry(const psfs_plan *p, int sampling, FuseArgs &a)
     a.tau = p->params.threshold;
 }
 
-// The plan's tile, or the one for its grid and rig when none was set or tuned
-// (step: the fusion runs beside a frame's likelihood). Of the column tiles the
-// 128-lane one pads ragged grids the least and leaves the shortest last round:
-// over 90 shapes 1.08 times as fast as tile 0 in fusions (80^3 x 8 views 9.4 / 7.0 us,
-// 112^3 x 8 17.3 / 14.5, 256^3 x 12 201 / 199.5), 1.04 times in steps (0.97 to 1.12;
-// 128^3 x 8, which neither pads, 27.9 / 28.4).
-// Grids that give the CUs two of its workgroups at most take half as many voxels
-// per lane (64^3 x 12: 6.7 / 5.8 us; 80^3 x 8: 7.0 / 8.5).
+// The plan's tile: the one that was set or tuned, or the rules'.
 int launch_tile(const psfs_plan *p, bool step)
 {
     const int set = step ? p->step_tile : p->tile;
-    if (set >= 0) return set;
-    if (p->params.sampling != PSFS_NEAREST)
-        return !step && bilinear_boxes_pay(p->cams, p->n, p->grid) ? block_tile() : default_tile();
-    if (block_pays(p->cams, p->n, p->grid, step)) return block_tile();
-    return small_grid(p->grid) ? kShallowTile : kNarrowTile;
+    return set >= 0 ? set : step ? rules(p).step_tile : rules(p).tile;
 }
 
 int enqueue_fuse(const psfs_plan *p, const float *lmap, float *post, uint8_t *occ, hipStream_t s)
@@ -679,6 +730,7 @@ int psfs_set_cameras(psfs_plan *plan, int n, const psfs_camera *cams)
     if (n > 0 && !cams) return fail(PSFS_E_ARG, "cams is NULL");
     for (int k = 0; k < n; ++k)
         if (int rc = check_camera(k, cams[k])) return rc;
+    plan->rules.word = 0;
     plan->n = n;
     for (int k = 0; k < n; ++k) plan->cams[k] = cams[k];
     for (int k = 0; k < PSFS_MAX_VIEWS; ++k) plan->mean[k] = plan->var[k] = nullptr;
@@ -692,6 +744,7 @@ int psfs_set_grid(psfs_plan *plan, const psfs_grid *g)
         return fail(PSFS_E_RANGE, "grid %dx%dx%d out of range", g->nx, g->ny, g->nz);
     if (!(g->voxel > 0.0f) || !std::isfinite(g->voxel) || !finite_all(g->origin, 3))
         return fail(PSFS_E_RANGE, "grid voxel size or origin invalid");
+    plan->rules.word = 0;
     plan->grid = *g;
     plan->has_grid = true;
     return PSFS_OK;
@@ -705,6 +758,7 @@ int psfs_set_params(psfs_plan *plan, const psfs_params *prm)
     if (!(prm->threshold >= 0.0f && prm->threshold <= 1.0f)) return fail(PSFS_E_RANGE, "threshold must lie in [0,1]");
     if (prm->sampling != PSFS_NEAREST && prm->sampling != PSFS_BILINEAR)
         return fail(PSFS_E_ARG, "unknown sampling %d", prm->sampling);
+    plan->rules.word = 0;
     plan->params = *prm;
     return PSFS_OK;
 }
@@ -1255,6 +1309,7 @@ int psfs_diff_forward_at(psfs_plan *plan, int n, psfs_camera *cams, const float 
     if (n > 0 && (!cams || !P_dev || !aligned(P_dev, 4))) return fail(PSFS_E_ARG, "cams or P is NULL");
     if (n > 0 && (!mean_dev || !var_dev)) return fail(PSFS_E_ARG, "background array is NULL");
     psfs_plan next = *plan;                         // the plan takes the views once all of them are valid
+    next.rules.word = 0;
     for (int k = 0; k < n; ++k) {
         if (cams[k].width != plan->cams[k].width || cams[k].height != plan->cams[k].height)
             return fail(PSFS_E_ARG, "view %d is %dx%d, the plan's is %dx%d", k, cams[k].width, cams[k].height,
