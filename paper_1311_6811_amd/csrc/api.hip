@@ -210,10 +210,12 @@ bool small_grid(const psfs_grid &grid)
     return batch_bricks(grid.nx, grid.ny, grid.nz, kNarrowTile, false) <= 512;
 }
 
-// Grids that give the CUs more than two workgroups of the two- and four-frame steps.
+// Grids that give the CUs more than eight workgroups of the two- and four-frame
+// steps, where a wave's test for views that see none of it pays (two frames: 80^3 x 13
+// views 12.5 us without, 13.1 with; 160^3 x 8 that mostly look past it 43.4 / 39.2).
 bool many_waves(const psfs_grid &grid)
 {
-    return batch_bricks(grid.nx, grid.ny, grid.nz, kWideTile, false) > 512;
+    return batch_bricks(grid.nx, grid.ny, grid.nz, kWideTile, false) > 2048;
 }
 
 // The boxes hold every pixel, the gathers of the column kernel only those that

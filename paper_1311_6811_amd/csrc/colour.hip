@@ -43,8 +43,8 @@ __device__ __forceinline__ bool locate(const ColourArgs &a, const ViewGeom &g, i
     const float cx = fmaf(g.P[8], X, fmaf(g.P[9], Y, g.P[11]));
     const float c = fmaf(g.P[10], Z, cx);
     const float r = __builtin_amdgcn_rcpf(c);
-    const int x = static_cast<int>(floorf(fmaf(g.P[2], Z, ax) * r));
-    const int y = static_cast<int>(floorf(fmaf(g.P[6], Z, bx) * r));
+    const int x = floor_int(fmaf(g.P[2], Z, ax) * r);
+    const int y = floor_int(fmaf(g.P[6], Z, bx) * r);
     if (!(c > 0.0f) || static_cast<uint32_t>(x) >= static_cast<uint32_t>(g.W) ||
         static_cast<uint32_t>(y) >= static_cast<uint32_t>(g.H))
         return false;

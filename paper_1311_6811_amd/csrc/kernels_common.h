@@ -600,6 +600,16 @@ __device__ __forceinline__ double centre64(float o, float h, int i)
     return fma(static_cast<double>(h), i + 0.5, static_cast<double>(o));
 }
 
+// Floor of a float as an int, saturated, in one instruction: a NaN too, which only
+// an overflow of FP32 makes of a coordinate, is no pixel of any image. (In place of
+// floorf and a conversion: 240^3 x 14 views that see a part of it 64 -> 58 us.)
+__device__ __forceinline__ int floor_int(float v)
+{
+    int r;
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(r) : "v"(v));
+    return r;
+}
+
 // Byte offsets (pixel y W + x times SCALE) of the pixels that a lane's KZ voxels
 // (depths Z[kk], projection rows ax, bx, cx at their column) read in view g;
 // 0xFFFFFFFF outside the image. `inside`: the host found the whole grid inside
@@ -629,11 +639,20 @@ __device__ __forceinline__ void nearest_offsets(const ViewGeom &g, float ax, flo
     } else {
 #pragma unroll
         for (int kk = 0; kk < KZ; ++kk) {
-            const int x = static_cast<int>(floorf(u[kk])), y = static_cast<int>(floorf(w[kk]));
+            const int x = floor_int(u[kk]), y = floor_int(w[kk]);
             const bool ok = c[kk] > 0.0f && static_cast<uint32_t>(x) < W && static_cast<uint32_t>(y) < H;
             off[kk] = ok ? (__umul24(static_cast<uint32_t>(y), W) + static_cast<uint32_t>(x)) * SCALE : 0xFFFFFFFFu;
         }
     }
+}
+
+// Start of a view's map, there before the view's branches: a load of its offset
+// that sinks behind them is waited for once more.
+template <class T>
+__device__ __forceinline__ const T *map_start(const T *p)
+{
+    asm volatile("" : "+s"(p));
+    return p;
 }
 
 // Whether no voxel of the wave is seen by a view (offsets of nearest_offsets).
@@ -816,7 +835,7 @@ __device__ __forceinline__ void fuse_column_pair(const Views &views, int n, cons
         constexpr bool SKIP = decltype(skip)::value;
         for (int v = 0; v < n; ++v) {
             const ViewGeom &g = views(v);
-            const float2 *map = reinterpret_cast<const float2 *>(lmap2) + g.map_off;
+            const float2 *map = map_start(reinterpret_cast<const float2 *>(lmap2) + g.map_off);
             const float ax = fmaf(g.P[0], X, fmaf(g.P[1], Y, g.P[3]));
             const float bx = fmaf(g.P[4], X, fmaf(g.P[5], Y, g.P[7]));
             const float cx = fmaf(g.P[8], X, fmaf(g.P[9], Y, g.P[11]));
@@ -931,7 +950,7 @@ __device__ __forceinline__ void fuse_column_quad(const Views &views, int n, cons
             // only when every view's quad map is below 4 GiB); an offset past
             // the end returns 0, which is what a voxel-view outside its image adds
             const __amdgpu_buffer_rsrc_t rsrc = map_rsrc(
-                lmap4 + 4 * g.map_off, static_cast<uint32_t>(g.W) * static_cast<uint32_t>(g.H) * 16u);
+                map_start(lmap4 + 4 * g.map_off), static_cast<uint32_t>(g.W) * static_cast<uint32_t>(g.H) * 16u);
             const float ax = fmaf(g.P[0], X, fmaf(g.P[1], Y, g.P[3]));
             const float bx = fmaf(g.P[4], X, fmaf(g.P[5], Y, g.P[7]));
             const float cx = fmaf(g.P[8], X, fmaf(g.P[9], Y, g.P[11]));
