@@ -154,6 +154,10 @@ def test_the_default_fuses_what_tile_0_fuses(tmp_path_factory, sampling, grid):
     ((3, 100, 90), 12, 320, 240, 2.0, "fuse_bilinear_kernel"),           # latency
     ((67, 56, 55), 11, 114, 86, 4.9, _tile_kernel(0)),                   # hardly in view
     ((67, 56, 55), 11, 114, 86, 2.0, "fuse_bilinear_kernel"),
+    ((71, 51, 69), 1, 255, 191, 2.0, _tile_kernel(0)),                   # one or two views
+    ((69, 83, 67), 2, 102, 76, 3.5, _tile_kernel(0)),
+    ((256, 256, 256), 1, 320, 240, 5.0, "fuse_bilinear_kernelILi8E"),
+    ((128, 128, 128), 2, 320, 240, 2.0, "fuse_bilinear_kernelILi8E"),
 ])
 def test_bilinear_boxes_where_they_pay(tmp_path_factory, grid, n, W, H, side, kernel):
     runs = check(tmp_path_factory, "fusion_kernels", dict(grid=[*grid, side], n=n, W=W, H=H, sampling=1))
