@@ -443,7 +443,7 @@ __global__ __launch_bounds__(kBlock) void diff_bwd_kernel(DiffArgs a)
         __syncthreads();                    // boxes visible
         float *red = arena + kGroup + wave * kRed;
         for (int v0 = v_lo; v0 < v_hi;) {
-            const int v1 = stage_group<kGroup>(a, v0, v_hi, boxes, arena);
+            const int v1 = stage_group<kGroup>(a, v0, v_hi, views_with(boxes, v_lo, v_hi, 1), boxes, arena);
             __syncthreads();                // every wave's loads have landed
             int off = 0;
             for (int v = v0; v < v1; ++v) {

@@ -147,22 +147,35 @@ __device__ __forceinline__ void stage_box_async(float *lds, const PixBox &b, con
     }
 }
 
-// Starts staging the boxes of views v0, v0 + 1, ... (below v_hi) that fit the
-// CAP floats of `arena` together, one after another; returns the first view
-// that is left for the next group. Views without a valid box, or with one that
-// misses the image, take no room.
-template <int CAP, class Args>
-__device__ __forceinline__ int stage_group(const Args &a, int v0, int v_hi, const PixBox *boxes, float *arena)
+// The views of [v_lo, v_hi) whose box has the given `ok`, as bits.
+__device__ __forceinline__ uint32_t views_with(const PixBox *boxes, int v_lo, int v_hi, int ok)
 {
-    int v = v0, off = 0;
-    for (; v < v_hi; ++v) {
+    static_assert(kMaxViews <= 32, "a bit per view");
+    const int v = v_lo + static_cast<int>(threadIdx.x & 63);
+    return static_cast<uint32_t>(__ballot(v < v_hi && boxes[v < v_hi ? v : v_lo].ok == ok)) << v_lo;
+}
+
+// Bits [v0, v1).
+__device__ __forceinline__ uint32_t view_range(int v0, int v1)
+{
+    return static_cast<uint32_t>((uint64_t(1) << v1) - (uint64_t(1) << v0));
+}
+
+// Starts staging the boxes of the views `boxed` from v0 on that fit the CAP floats
+// of `arena` together, one after another; returns the first view that is left for
+// the next group (v_hi when there is none).
+template <int CAP, class Args>
+__device__ __forceinline__ int stage_group(const Args &a, int v0, int v_hi, uint32_t boxed, const PixBox *boxes, float *arena)
+{
+    int off = 0;
+    for (uint32_t m = boxed & view_range(v0, v_hi); m; m &= m - 1) {
+        const int v = __builtin_ctz(m);
         const PixBox box = read_box(boxes, v);
-        if (box.ok != 1) continue;
-        if (off + box.w * box.h > CAP) break;
+        if (off + box.w * box.h > CAP) return v;
         stage_box_async(arena + off, box, a.lmap + a.view[v].map_off, a.view[v].W, a.view[v].H);
         off += box_floats(box);
     }
-    return v;
+    return v_hi;
 }
 
 // L[kk] += the bilinear sample of every view, in view order, at the lane's
@@ -176,16 +189,17 @@ template <Taps T, int KZ, int CAP, class Args>
 __device__ __forceinline__ void add_bilinear(const Args &a, double Xd, double Yd, int kb, float *arena,
                                              const PixBox *boxes, float (&L)[KZ])
 {
+    const uint32_t boxed = views_with(boxes, 0, a.n, 1), sampled = boxed | views_with(boxes, 0, a.n, 0);
     for (int v0 = 0; v0 < a.n;) {
-        const int v1 = stage_group<CAP>(a, v0, a.n, boxes, arena);
+        const int v1 = stage_group<CAP>(a, v0, a.n, boxed, boxes, arena);
         __syncthreads();                    // every wave's loads have landed
         int off = 0;
-        for (int v = v0; v < v1; ++v) {
+        for (uint32_t m = sampled & view_range(v0, v1); m; m &= m - 1) {
+            const int v = __builtin_ctz(m);
             const ViewGeom &g = a.view[v];
             const Proj64 p = proj64_view(a, v, Xd, Yd);
-            const PixBox box = read_box(boxes, v);
-            if (box.ok == kMissed) continue;
-            if (box.ok) {
+            if (boxed >> v & 1) {
+                const PixBox box = read_box(boxes, v);
                 // box element of tap (x0, y0): (y0 - box.y0) w + (x0 - box.x0),
                 // exact in FP64 (integers far below 2^53). Every voxel centre
                 // of the workgroup is in front of the camera and has both taps
