@@ -283,7 +283,7 @@ __device__ __forceinline__ void box_voxels(const DiffArgs &a, const Proj64 &p, c
         project64_front<Taps::kDifferentiable>(p, Zd, t);
         const int e = min(max(static_cast<int>(fma(t.y0, wd, t.x0 - od)), 0), emax);
         const float l00 = map_box[e], l10 = map_box[e + 1], l01 = map_box[e + box.w], l11 = map_box[e + box.w + 1];
-        if (SCATTER && scatters(gv[kk], qscale)) {
+        if (SCATTER) {
             const TapTerms q = tap_terms(gv[kk], t.fx, t.fy, qscale);
             atomicAdd(&adj_box[e], q.q00);
             atomicAdd(&adj_box[e + 1], q.q10);
@@ -365,15 +365,19 @@ __device__ __forceinline__ void flush_box(const PixBox &box, int *adj_box, unsig
 
 // Workgroup (b, y): views [n y / gridDim.y, n (y + 1) / gridDim.y) of block b.
 // Bound by the instructions of the FP64 projection and of the camera terms.
-// Only voxels whose term can round to something (scatters) quantise and add
-// their four tap terms: away from the body the sigmoid differs from the label
-// by less than 2^-20, so most workgroups have no such voxel, and these need no
-// adjoint box, no flush and fewer barriers (their views' boxes are staged in
-// groups, as in the forward). Where a view's box is larger than its LDS, what
-// is left of the global atomics is the surface's. Backward pass (zeroing, this
-// kernel, pixel chain) at 160^3 x 8 views of 1280x720: 1706 -> 225 us; 224^3 x 12: 765 -> 458;
-// 128^3 x 8 of 640x480: 94 -> 87. Grids of fewer than kBwdBlocks blocks split
-// their views over gridDim.y (61 x 53 x 47 x 5 views, 96 blocks: 41 -> 26 us).
+// Away from the body the sigmoid differs from the label by less than 2^-20, so most
+// workgroups have no voxel whose term can round to something (scatters): these are
+// cold and need no adjoint box, no flush and fewer barriers; their views' boxes are
+// staged in groups, as in the forward, and views whose box misses the image are passed
+// over. In a hot workgroup every voxel adds its four tap terms to the view's box in
+// LDS (leaving out those that round to 0: 138 x 174 x 103 x 12 views, a fiftieth hot,
+// 151 us against 144). Where a view's box is larger than its LDS, what is left of the
+// global atomics is the surface's; there the terms of 0 are left out. Both kinds share one
+// loop over the views: in two of their own the kernel is 37 KB of instructions
+// against 28, and 138 x 174 x 103 x 12 takes 177 us hot against 166. Backward pass
+// (zeroing, this kernel, pixel chain) at 160^3 x 8 views of 1280x720: 1706 -> 225 us;
+// 224^3 x 12: 765 -> 458; 128^3 x 8 of 640x480: 94 -> 87. Grids of fewer than kBwdBlocks
+// blocks split their views over gridDim.y (61 x 53 x 47 x 5 views, 96 blocks: 41 -> 26 us).
 __global__ __launch_bounds__(kBlock) void diff_bwd_kernel(DiffArgs a)
 {
     constexpr int kRed = 12 * 64;                       // floats of one wave's camera reduction
@@ -404,63 +408,70 @@ __global__ __launch_bounds__(kBlock) void diff_bwd_kernel(DiffArgs a)
         }
     }
     const int wave = threadIdx.x >> 6;
+    __shared__ int seen[kWaves];
+    const int wave_seen = (__any(any) ? 1 : 0) | (__any(hot) ? 2 : 0);
+    if ((threadIdx.x & 63) == 0) seen[wave] = wave_seen;
+    __syncthreads();
+    int block_seen = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) block_seen |= seen[w];
+    block_seen = __builtin_amdgcn_readfirstlane(block_seen);
+    const bool block_any = block_seen != 0, block_hot = (block_seen & 2) != 0;
     // a workgroup with no voxel in the loss region contributes nothing
-    const bool block_any = __syncthreads_or(any ? 1 : 0) != 0;
-    const bool block_hot = __syncthreads_or(hot ? 1 : 0) != 0;
     if (!block_any) {
         for (int e = 12 * v_lo + static_cast<int>(threadIdx.x); e < 12 * v_hi; e += kBlock)
             a.cam_part[static_cast<int64_t>(blockIdx.x) * a.n * 12 + e] = 0.0f;
         return;
     }
-    compute_boxes<kFX, kFY, kFZ>(a, q.bi, q.bj, q.kb, block_hot ? kBoxCap : kGroup, !block_hot, false, boxes);
+    // not widened to pieces: a hot box is as wide to flush, and where boxes are large fewer fit
+    // a group (129^3 x 15 cold views 140 -> 135 us without, 128^3 x 8 75 both)
+    compute_boxes<kFX, kFY, kFZ>(a, q.bi, q.bj, q.kb, kBoxCap, false, !block_hot, boxes);
 
-    if (block_hot) {
-        float *map_box = arena;
-        int *adj_box = reinterpret_cast<int *>(arena + kBoxCap);
-        // the adjoint box starts at zero once; each view's flush clears the
-        // entries it reads, and a view scatters only inside its own box
+    int *adj_box = reinterpret_cast<int *>(arena + kBoxCap);
+    // the adjoint box starts at zero once; each view's flush clears the
+    // entries it reads, and a view scatters only inside its own box
+    if (block_hot)
         for (int e = threadIdx.x; e < kBoxCap; e += kBlock) adj_box[e] = 0;
-        __syncthreads();
-        for (int v = v_lo; v < v_hi; ++v) {
+    __syncthreads();                        // boxes visible
+    const uint32_t boxed = views_with(boxes, v_lo, v_hi, 1), missed = views_with(boxes, v_lo, v_hi, kMissed);
+    // each wave reduces in its own 768 floats: past the boxes of the group, or in the
+    // view's staged box once it is free
+    float *red = arena + (block_hot ? 0 : kGroup) + wave * kRed;
+    for (int v0 = v_lo; v0 < v_hi;) {
+        int v1 = v0 + 1;
+        if (!block_hot) {
+            v1 = stage_group<kGroup>(a, v0, v_hi, boxed, boxes, arena);
+            __syncthreads();                // every wave's loads have landed
+        }
+        int off = 0;
+        for (int v = v0; v < v1; ++v) {
+            if (missed >> v & 1) {          // samples that are all 0, and finite gradients
+                if ((threadIdx.x & 63) < 12) cam[wave][v * 12 + (threadIdx.x & 63)] = 0.0f;
+                continue;
+            }
             const ViewGeom &g = a.view[v];
             const Proj64 p = proj64_view(a, v, Xd, Yd);
-            const PixBox box = read_box(boxes, v);
             CamSums s;
-            __syncthreads();                // the previous view's flush and camera sums are done
-            if (box.ok) {
-                stage_box(map_box, box, a.lmap + g.map_off, g.W, g.H);
-                __syncthreads();
-                box_voxels<true>(a, p, box, map_box, adj_box, q.kb, gv, qscale, s);
-                __syncthreads();            // every scatter into the box is done
-                flush_box(box, adj_box, reinterpret_cast<unsigned long long *>(a.adj) + g.map_off, g.W, g.H);
-            } else {
+            if (!(boxed >> v & 1)) {
                 map_voxels(a, g, p, q.kb, gv, qscale, s);
-            }
-            // the staged box is free: each wave reduces in its own 768 floats of it
-            wave_camera_sums(s, X, Y, map_box + wave * kRed, &cam[wave][v * 12]);
-        }
-    } else {
-        __syncthreads();                    // boxes visible
-        float *red = arena + kGroup + wave * kRed;
-        for (int v0 = v_lo; v0 < v_hi;) {
-            const int v1 = stage_group<kGroup>(a, v0, v_hi, views_with(boxes, v_lo, v_hi, 1), boxes, arena);
-            __syncthreads();                // every wave's loads have landed
-            int off = 0;
-            for (int v = v0; v < v1; ++v) {
-                const Proj64 p = proj64_view(a, v, Xd, Yd);
+            } else {
                 const PixBox box = read_box(boxes, v);
-                CamSums s;
-                if (box.ok) {
+                if (block_hot) {
+                    __syncthreads();        // the previous views' flush and camera sums are done
+                    stage_box(arena, box, a.lmap + g.map_off, g.W, g.H);
+                    __syncthreads();
+                    box_voxels<true>(a, p, box, arena, adj_box, q.kb, gv, qscale, s);
+                    __syncthreads();        // every scatter into the box is done
+                    flush_box(box, adj_box, reinterpret_cast<unsigned long long *>(a.adj) + g.map_off, g.W, g.H);
+                } else {
                     box_voxels<false>(a, p, box, arena + off, nullptr, q.kb, gv, qscale, s);
                     off += box_floats(box);
-                } else {
-                    map_voxels(a, a.view[v], p, q.kb, gv, qscale, s);
                 }
-                wave_camera_sums(s, X, Y, red, &cam[wave][v * 12]);
             }
-            v0 = v1;
-            if (v0 < v_hi) __syncthreads(); // the group's reads are done
+            wave_camera_sums(s, X, Y, red, &cam[wave][v * 12]);
         }
+        v0 = v1;
+        if (!block_hot && v0 < v_hi) __syncthreads();   // the group's reads are done
     }
     __syncthreads();
     for (int e = 12 * v_lo + static_cast<int>(threadIdx.x); e < 12 * v_hi; e += kBlock) {
@@ -646,7 +657,10 @@ hipError_t launch_diff_backward(const DiffArgs &a, const ChainArgs &c, int64_t m
     }
     const int64_t nb = diff_bwd_blocks(a.nx, a.ny, a.nz);
     if (nb > 0 && a.n > 0) {
-        const int64_t split = std::min<int64_t>(a.n, (kBwdBlocks + nb - 1) / nb);
+        // with few views, what every workgroup does before them outweighs a second round
+        // of workgroups (640 blocks: 3 views 34.7 us in one, 40.7 in two; 13 views 51.1 / 45.3)
+        const int64_t fit = a.n >= 12 ? (kBwdBlocks + nb - 1) / nb : std::max<int64_t>(kBwdBlocks / nb, 1);
+        const int64_t split = std::min<int64_t>(a.n, fit);
         hipLaunchKernelGGL(diff_bwd_kernel, dim3(static_cast<unsigned>(nb), static_cast<unsigned>(split)), dim3(kBlock), 0, s, a);
     }
     if (a.n > 0) {
