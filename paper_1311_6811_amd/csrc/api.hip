@@ -228,7 +228,8 @@ bool many_waves(const psfs_grid &grid)
 // 6 x 266 x 487 x 2 9.6 / 12.3, 5 x 233 x 233 x 3 8.9 / 10.3). Voxels that no view sees cost
 // the column kernel less (75 x 49 x 48 x 12 views that see an eighth 16.2 / 26.2,
 // 99 x 103 x 116 x 11 a hundredth 38.1 / 32.2; with boxes of 3700 and 6200 pixels,
-// 88 x 85 x 79 x 6 a fiftieth 15.9 / 21.1, 97 x 108 x 149 x 3 nothing 14.9 / 17.6). With one or two views little is staged
+// 88 x 85 x 79 x 6 a fiftieth 15.9 / 21.1, 97 x 108 x 149 x 3 nothing 14.9 / 17.6;
+// 117 x 104 x 85 x 3 a tenth 11.9 / 14.5). With one or two views little is staged
 // at a time (1 view: 71 x 51 x 69 5.2 / 8.4, 144 x 93 x 152 with boxes of 5100 pixels 8.8 /
 // 11.8, 1500 blocks 18.7 / 13.8; 2 views: 69 x 83 x 67 7.1 / 7.8, 300 blocks 8.9 / 7.6, 1254
 // of 2900 pixels hardly in view 13.7 / 14.9, 1540 of 4100 26.0 / 20.6).
@@ -241,8 +242,8 @@ bool bilinear_boxes_pay(const psfs_camera *cams, int n, const psfs_grid &grid)
     const int64_t narrow = ((int64_t(grid.nx) + 7) / 8) * ((int64_t(grid.ny) + 31) / 32);
     if (2 * wide > 3 * narrow && (blocks >= 300 || n < 4)) return false;
     if (n > 2) {
-        if (blocks >= (area > 3000.0 ? 2000 : 256)) return true;
-        return visible_part(cams, n, grid) >= (blocks < 256 ? 0.3 : 0.1);
+        if (blocks >= (area > 3000.0 ? 2000 : n == 3 ? 1450 : 256)) return true;
+        return visible_part(cams, n, grid) >= (blocks < 256 || n == 3 ? 0.3 : 0.1);
     }
     if (blocks * n < 600 || (n == 1 && area > 2000.0)) return false;
     return blocks >= 1450 || (area <= 3000.0 && visible_part(cams, n, grid) >= 0.27);
