@@ -185,21 +185,25 @@ double mean_block_area(const psfs_camera *cams, int n, const psfs_grid &grid)
 
 // The block tile's cost per workgroup (boxes, one barrier per group of views) is
 // hidden only where the CUs run enough workgroups, and behind a step's likelihood
-// rounds only where they run several rounds of them. Column tile 0 / blocks, us:
-// fusion alone 128^3 x 8 views of 640x480 19.5 / 22, 144^3 x 8 28.9 / 24.3, 160^3 x 8 33.6 /
-// 27.8; as a step 144^3 x 8 37.7 / 39.8, 160^3 x 8 42.4 / 42.6, 176^3 x 6 43.2 / 34.7.
+// rounds only where they run several rounds of them. Column tile (find_rules) / blocks,
+// us: fusion alone 128^3 x 8 views of 640x480 19.4 / 22.3, 144^3 x 8 26.1 / 24.8, 160^3 x 8
+// 31.6 / 27.5; as a step 144^3 x 8 34.7 / 39.8, 160^3 x 8 41.1 / 42.7, 176^3 x 6 39.8 / 35.4.
 // What it saves are the column tile's L1 accesses, the more the further apart
 // neighbouring voxels project, with each view: 192^3 x 7 at 236x177 (boxes of 149
-// pixels) 34.4 / 35.3, x 8 at 320x240 (230) 43.6 / 36.9; 256^3 x 8 at 236x177 (129) 78 /
-// 68, x 1 at 643x477 (266) 30.8 / 25.1; 192^3 x 4 at 643x477 (434) 24.8 / 25.6; 144^3 x 4
-// (724) 14.9 / 15.2, x 6 (953) 23.1 / 19.6. Boxes of many pixels leave little room for a
-// group of views, and larger ones than the arena are gathered: 160^3 x 12 at 1280x720
-// (4400 pixels) fusion 59.7 / 50.6, step 108.6 / 116.4.
+// pixels) 32.3 / 34.1, x 8 at 320x240 (230) 40.7 / 37.1; 256^3 x 8 at 236x177 (129) 65.6 /
+// 67.7, 288 x 290 x 224 x 7 (126) 0.81 of the column's time; 256^3 x 1 at 643x477 (266) 29.2 /
+// 25.2; 192^3 x 4 at 643x477 (434) 25.6 / 25.8; 144^3 x 4 (724) 13.4 / 16.0, x 6 (953) 21.6 /
+// 20.3. Boxes of many pixels leave little room for a group of views, and larger ones than
+// the arena are gathered: 160^3 x 12 at 1280x720 (4400 pixels) fusion 54.0 / 43.6, step
+// 105 / 104; 144^3 x 6 (4100) fusion 21.7 / 26.0, 151 x 176 x 118 x 13 (2800) 47.7 / 50.9. Of 460
+// random grids of 60 to 300 voxels an edge, fused alone and as a step, the rule takes
+// blocks for 8 where they are more than 3 % slower (7.5 % at most).
 bool block_pays(const psfs_camera *cams, int n, const psfs_grid &grid, bool step)
 {
     const int64_t blocks = blocks_16x16x8(grid), work = blocks * (n + 4);
     if (n == 0 || blocks < (step ? 2400 : 1400) || !blocks_fit(grid)) return false;
     const double area = mean_block_area(cams, n, grid);
+    if (blocks < 1900 && area > 2500.0) return false;
     return static_cast<double>(work) * std::fmin(area, 1000.0) >= (work < 30000 ? 13e6 : 8e6) &&
            area <= (step ? 4000.0 : 5000.0);
 }
@@ -452,13 +456,13 @@ struct Rules {
 };
 
 // The views that hold the grid, and the tiles for its grid and rig, of a fusion and
-// of a step (beside a frame's likelihood). Of the column tiles the
-// 128-lane one pads ragged grids the least and leaves the shortest last round:
-// over 90 shapes 1.08 times as fast as tile 0 in fusions (80^3 x 8 views 9.4 / 7.0 us,
-// 112^3 x 8 17.3 / 14.5, 256^3 x 12 201 / 199.5), 1.04 times in steps (0.97 to 1.12;
-// 128^3 x 8, which neither pads, 27.9 / 28.4).
-// Grids that give the CUs two of its workgroups at most take half as many voxels
-// per lane (64^3 x 12: 6.7 / 5.8 us; 80^3 x 8: 7.0 / 8.5).
+// of a step (beside a frame's likelihood). Of the column tiles the 128-lane one pads
+// ragged grids the least and leaves the shortest last round: over 460 random grids its
+// fusions take 0.96 of tile 0's time (80^3 x 8 views 9.9 / 8.0 us, 112^3 x 8 17.2 / 15.1,
+// 256^3 x 12 186.2 / 186.7), its steps 0.97 (0.9 to 1.07; 128^3 x 8, which neither pads,
+// 28.7 / 29.5; tile 0 for all that it does not pad more is slower on average). Grids that
+// give the CUs two of its workgroups at most take half as many voxels per lane (64^3 x
+// 12: 8.1 / 7.1 us; 80^3 x 8: 8.0 / 9.2).
 Rules find_rules(const psfs_plan *p)
 {
     Rules r{0, default_tile(), default_tile()};

@@ -94,8 +94,8 @@ __global__ __launch_bounds__(TX * TY) void batch_pipe_kernel(BatchArgs a, int fl
 // As batch_pipe_kernel, the fusion from pixel boxes staged in LDS (block_tile.h):
 // the steps of the block tile whose frame's grid and rig make that the faster way
 // (block_pays; the other steps run column tiles), and every step where that tile is
-// set. One kernel for both kinds of fusion
-// made every step ~10 % slower (its LDS and code serve the likelihood too).
+// set. One kernel for both kinds of fusion made every step ~10 % slower (its LDS and
+// code serve the likelihood too).
 __global__ __launch_bounds__(kSBThreads) void batch_pipe_block_kernel(BatchArgs a, int fl, int ff, PipeArgs p)
 {
     static_assert(kSBThreads == 256, "four waves per workgroup, as batch_slm_block and tile 0");

@@ -256,11 +256,11 @@ __global__ __launch_bounds__(kSBThreads) void pipe_block_kernel(SlmArgs s, FuseA
 // staged in LDS (add_bilinear): the differentiable forward's sampling with
 // this pass's outputs. Bound by the FP64 projection's instructions. The column
 // kernels gather four taps of every voxel-view from the map, four loads with a
-// bounds test each: 61 us at 128^3 x 8 views of 640x480, 515 us at 224^3 x 12
-// of 1280x720; here 30 and 166 us. The arena of 7500 floats (30 KB) leaves room
+// bounds test each: 62 us at 128^3 x 8 views of 640x480, 470 us at 224^3 x 12
+// of 1280x720; here 30 and 173 us. The arena of 7500 floats (30 KB) leaves room
 // for five workgroups per CU, as many as the registers allow (with boxes staged
-// pixel by pixel 32 and 206 us; 8192 floats, four workgroups, 32 and 219 us; 6000
-// floats, fewer views per barrier, 34 and 204 us).
+// pixel by pixel and one Newton step 32 and 206 us; 8192 floats, four workgroups, 32 and
+// 219 us; 6000 floats, fewer views per barrier, 34 and 204 us).
 constexpr int kBilArena = 7500;
 
 template <int KZ>

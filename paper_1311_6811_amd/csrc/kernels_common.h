@@ -787,8 +787,9 @@ __device__ __forceinline__ int quad_lane_pos(int l) { return (((l >> 1) & 1) << 
 
 // A 16-byte store of a piece of an output row at any address. Non-temporal where
 // the rows are made of whole aligned pieces; a line of any other rows is written in
-// parts by several stores, which then have to meet in the L2 (four frames at
-// 150^3 x 8 views: 81 us non-temporal, 74 us plain).
+// parts by several stores, which then have to meet in the L2 (non-temporal against
+// plain: four frames at 150^3 x 8 views 80 / 59 us, 222^3 x 10 218 / 159, 299 x 301 x 300 x 12
+// 713 / 675; two frames 48 / 45, 118 / 106 and, past what the caches hold, 366 / 390).
 typedef f32x4 f32x4_floats __attribute__((aligned(4)));
 typedef f32x4 f32x4_bytes __attribute__((aligned(1)));
 __device__ __forceinline__ void store_piece(f32x4 v, float *p, bool aligned)

@@ -119,9 +119,9 @@ __device__ __forceinline__ void box_rc(int e, int w, float inv_w, int &r, int &c
 // 16-byte pieces or of single pixels, one wave instruction per 64 consecutive
 // ones); a pixel outside the image gets an offset past the end of the map, which
 // loads 0. The values are there after the workgroup's next barrier. (Pixel by pixel
-// against in pieces: bilinear fusion 128^3 x 8 views of 640x480 33.3 / 30.0 us, 160^3 x 8
-// of 1280x720 67 / 53, 224^3 x 12 188 / 166; differentiable forward 55 / 51, 117 / 103,
-// 269 / 242.)
+// against in pieces: bilinear fusion 128^3 x 8 views of 640x480 33.9 / 30.3 us, 160^3 x 8
+// of 1280x720 65 / 51, 224^3 x 12 182 / 158; differentiable forward 58 / 54, 121 / 106,
+// 271 / 248.)
 __device__ __forceinline__ void stage_box_async(float *lds, const PixBox &b, const float *map, int W, int H)
 {
     const bool pieces = b.pieces != 0;

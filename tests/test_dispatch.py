@@ -171,3 +171,16 @@ def test_the_views_that_hold_the_whole_grid(tmp_path_factory):
     assert not [missed for said, missed in got if said and missed]
     held = [said for said, missed in got if not missed]
     assert len(held) > 100 and sum(held) > 0.95 * len(held)
+
+
+@pytest.mark.parametrize("grid,n,W,H,side,kernel", [
+    ((144, 144, 144), 8, 640, 480, 2.0, "fuse_block_kernel"),
+    ((144, 144, 144), 12, 1280, 720, 1.8, _tile_kernel(2)),              # few blocks of large boxes
+    ((160, 160, 160), 12, 1280, 720, 2.0, "fuse_block_kernel"),
+    ((128, 128, 128), 8, 640, 480, 2.0, _tile_kernel(2)),                # few blocks
+    ((192, 192, 192), 7, 236, 177, 2.0, _tile_kernel(2)),                # small boxes
+    ((256, 256, 256), 1, 643, 477, 2.0, "fuse_block_kernel"),
+])
+def test_blocks_where_they_pay(tmp_path_factory, grid, n, W, H, side, kernel):
+    runs = check(tmp_path_factory, "fusion_kernels", dict(grid=[*grid, side], n=n, W=W, H=H, sampling=0))
+    assert kernel in runs[0][2]
