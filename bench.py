@@ -49,7 +49,7 @@ PAPER_CONTEXT = {"scope": "whole pipeline per frame (reconstruction + colour + t
 # HBM traffic of one pipe_quad_kernel launch on this workload from two rocprofv3
 # --pmc runs (FETCH_SIZE, then WRITE_SIZE; KiB per dispatch, averaged over the
 # dispatches of `bench.py --steps 24 --warmup 6 --replays 5 --no-cpu --no-batch
-# --no-diff --no-c2 --calibrate-copy`), each scaled by what the counter reads for the
+# --calibrate-copy`), each scaled by what the counter reads for the
 # calibration kernel (torch.neg over 256 MiB: FETCH_SIZE 131080 KiB for 262144
 # KiB read, x2.0; WRITE_SIZE 262144 KiB for 262144 KiB written, x1.0). The
 # figures hold for the kernel sources they were taken on (SHA-256 of the files
@@ -57,9 +57,9 @@ PAPER_CONTEXT = {"scope": "whole pipeline per frame (reconstruction + colour + t
 # are taken again.
 PIPE_COUNTER_SOURCES = ("paper_1311_6811_amd/csrc/forward.hip", "paper_1311_6811_amd/csrc/kernels_common.h",
                         "paper_1311_6811_amd/csrc/psfs_internal.h")
-PIPE_COUNTERS = {"sources_sha256": "d4b94cad256f646eeaa2937b2924788f03b2e28f5e5fee503ed1221c30087e8b",
-                 "fetch_kib": 59464.4, "fetch_scale": 2.0, "write_kib": 80982.1, "write_scale": 1.0,
-                 "l2_hit_rate": 0.661}
+PIPE_COUNTERS = {"sources_sha256": "aff26ad261659b57320b8574fffa9eda2378605a019dba380d0315bd01f25368",
+                 "fetch_kib": 59470.1, "fetch_scale": 2.0, "write_kib": 81031.0, "write_scale": 1.0,
+                 "l2_hit_rate": 0.664}
 
 
 def sources_sha256() -> str:
